@@ -4,15 +4,28 @@
 // single-reduction form of Chronopoulos & Gear (J. Comput. Appl. Math. 25,
 // 1989), which in exact arithmetic produces the iterates of standard PCG:
 //
-//   p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s, u = M^-1 r
-//   w = A u;  gamma = (r, u), delta = (w, u)
-//   beta' = gamma' / gamma, alpha' = gamma' / (delta' - beta' gamma' / alpha)
+//   u_k = M^-1 r_k, w_k = A u_k; gamma_k = (r_k, u_k), delta_k = (u_k, w_k)
+//   beta_k = gamma_k / gamma_{k-1}
+//   alpha_k = gamma_k / (delta_k - beta_k gamma_k / alpha_{k-1})
+//
+// The direction p_k = u_k + beta_k p_{k-1} and its product A p_k are not
+// kept: A p_{k-1} = (r_{k-1} - r_k) / alpha_{k-1}, so the residual follows from
+// its own last two values (the three-term form of the same iterates),
+//   r_{k+1} = r_k + theta_k (r_k - r_{k-1}) - alpha_k w_k,
+//   theta_k = alpha_k beta_k / alpha_{k-1},
+// and x = sum_k alpha_k p_k is a combination of the u_k.  The last U_RING of
+// them stay where they were written (a ring of slots), and k_cg_flush adds
+// them to x (and forms the direction that later terms build on) in one pass
+// every U_RING - 1 iterations and before a true-residual check.  Per row and
+// iteration the vector work moves 96 bytes (r twice, w, the new r; with
+// Jacobi 32 more for 1/diag and u) and 30 for x, against 192 and 24 with p, s
+// and x kept: at N = 8e6 k_cg_vec 266 -> 131 us (learned).
 //
 // Per iteration three launches (four with the learned M^-1 product,
 // k_cg_apply), none with a cache write-back fence:
-//   k_cg_vec   every vector update, element-parallel (fully coalesced; x
-//              every other iteration), and the partial sums of (r, u) and
-//              (r, r) per sub-tile of 256 rows;
+//   k_cg_vec   the new residual (and u with Jacobi), element-parallel (fully
+//              coalesced), and the partial sums of (r, u) and (r, r) per
+//              sub-tile of 256 rows;
 //   k_cg_spmv  w = A u, by default entry-parallel (the sub-tile's entries
 //              striped over its threads, the products summed per row from
 //              LDS), or with a group of 1, 2, 4 or 8 lanes per CSR row (the
@@ -120,7 +133,8 @@ __global__ void k_cg_reset(DevPtrs d, double tol_override) {
   for (int r = threadIdx.x; r < d.nrep; r += blockDim.x) {
     CgRep& c = d.cg[r];
     for (int k = 0; k < 3; ++k) {
-      c.bb[k] = c.rr[k] = c.gamma[k] = c.alpha[k] = c.alpha_prev[k] = c.beta[k] = 0.0;
+      c.bb[k] = c.rr[k] = c.gamma[k] = c.alpha[k] = c.theta[k] = 0.0;
+      c.pend[k] = c.cbase[k] = 0;
       c.state[k] = 0;
       c.it[k] = 0;
     }
@@ -151,23 +165,18 @@ __device__ __forceinline__ void stv(T* p, T v) {
 
 // Element-parallel vector work of one sub-tile (3 * 256 consecutive doubles
 // of the AoS arrays; element e is row e/3, component e%3).  NT: the streams
-// that are not read again within the iteration (r, p, w, s, x, 1/diag) are
+// that are not read again within the iteration (r twice, w, 1/diag) are
 // loaded and stored as nontemporal, u (gathered by the product next) as
 // usual: on a working set larger than the last-level cache this streams
 // faster (measured at N = 8e6), below it the ordinary form keeps the
 // vectors cached; the autotuner picks.  Same bits either way.
-//   mode 0 (fresh start):   x = 0, r = b, p = s = 0, u = M^-1 r
-//   mode 1 (restart, r already = b - A x):   p = s = 0, u = M^-1 r
-//   mode 2 (iteration):     p = u + beta p, s = w + beta s, x += alpha p,
-//                           r -= alpha s, u = M^-1 r
+//   mode 0 (fresh start):   x = 0, r = b, u = M^-1 r
+//   mode 1 (restart, r already = b - A x):   u = M^-1 r
+//   mode 2 (iteration):     d.s = r + theta (r - d.s) - alpha w, u = M^-1 (new r)
+// In mode 2 the new residual overwrites the one before r; the host swaps the
+// two for the launches that follow, and points d.u at the next ring slot.
+// With theta = 0 (a first iteration) the old d.s is not read.
 // Partials (r, u) and (r, r) of the components touched.
-// x is updated every other iteration: in iteration j (j = it, counted per
-// component from the start) with j even the term alpha_j p_j is left
-// pending, with j odd x += alpha_{j-1} p_{j-1} + alpha_j p_j, p_{j-1} being
-// the p this iteration reads anyway; the x stream (48 bytes per row) is
-// touched in half the iterations.  k_cg_flush adds a pending term before
-// a true-residual check reads x; a start or restart zeroes p, so no pending
-// term outlives one.
 template <bool NT>
 __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
   const int sub = sub_of_block(d);
@@ -175,15 +184,13 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
   const int rid = d.blk_rep[sub / SUBS_PER_TILE];
   const CgRep& cr = d.cg[rid];
   if ((mode == 1 && !cr.restart) || (mode == 2 && !cr.run)) return;
-  bool on[3], xodd[3];
-  double al[3], ap[3], be[3];
+  bool on[3];
+  double al[3], th[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     on[k] = mode == 0 ? true : (mode == 1 ? cr.state[k] == 3 : cr.state[k] == 0);
     al[k] = cr.alpha[k];
-    ap[k] = cr.alpha_prev[k];
-    be[k] = cr.beta[k];
-    xodd[k] = (cr.it[k] & 1) != 0;
+    th[k] = cr.theta[k];
   }
   double v[6] = {0, 0, 0, 0, 0, 0};  // (r,u)[3], (r,r)[3]
   const int64_t base = (int64_t)sub * VEC_ELEMS;
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
   for (int q = 0; q < 3; ++q) {
     const int le = q * SUB_THREADS + threadIdx.x;
     const int k = le % 3;
-    if (!on[k]) continue;
+    if (!on_k(on, k)) continue;
     const int64_t e = base + le;
     // 1/diag only where this kernel applies Jacobi itself
     const double di =
@@ -202,23 +209,13 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
       rk = d.b[e];
       d.x[e] = 0.0;
       d.r[e] = rk;
-      d.p[e] = 0.0;
-      d.s[e] = 0.0;
     } else if (mode == 1) {
       rk = d.r[e];
-      d.p[e] = 0.0;
-      d.s[e] = 0.0;
     } else {
-      const double r0 = ldv<NT>(d.r + e);
-      const double uk0 = ext ? ldv<NT>(d.u + e) : di * r0;
-      const double pold = ldv<NT>(d.p + e);
-      const double pk = uk0 + be[k] * pold;
-      const double sk = ldv<NT>(d.w + e) + be[k] * ldv<NT>(d.s + e);
-      stv<NT>(d.p + e, pk);
-      stv<NT>(d.s + e, sk);
-      if (on_k(xodd, k)) stv<NT>(d.x + e, ldv<NT>(d.x + e) + (ap[k] * pold + al[k] * pk));
-      rk = r0 - al[k] * sk;
-      stv<NT>(d.r + e, rk);
+      const double r0 = ldv<NT>(d.r + e), t = pick3(th, k);
+      const double rm = t != 0.0 ? ldv<NT>(d.s + e) : r0;
+      rk = (r0 + t * (r0 - rm)) - pick3(al, k) * ldv<NT>(d.w + e);
+      stv<NT>(d.s + e, rk);
     }
     if (!ext) {
       const double uk = di * rk;
@@ -235,35 +232,89 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
   write_partials<3>(d, sub, 6, rr);
 }
 
-// Partials (r, u) per sub-tile after an external preconditioner pass (IC(0)),
-// component selection as k_cg_vec's mode.
-// Pending x terms before a true-residual check: x += alpha p for the
-// components whose check is pending and whose last iteration (it - 1) was
-// even (see k_cg_vec); replicas without a pending check return at once.
-__global__ __launch_bounds__(SUB_THREADS) void k_cg_flush(DevPtrs d) {
+// The ring's pending terms u_0 .. u_{m-1} (slots cbase ..) of a component
+// into x and into the direction p that the later terms build on.  With
+// p_j = u_j + beta_j p_{j-1} and x += sum_j alpha_j p_j, the beta are ratios of
+// the gamma (beta_{j+1} = gamma_{j+1} / gamma_j), so
+//   x += sum_j c_j u_j + beta_0 c_0 p,  c_j = (sum_{k>=j} alpha_k gamma_k) / gamma_j,
+//   p  = sum_j d_j u_j + beta_0 d_0 p,  d_j = gamma_{m-1} / gamma_j
+// (every term positive), the sums by a suffix scan, one wave per component;
+// every u is read once.  forced = 1 (the ring is full): replicas that iterate,
+// every component with pending terms; forced = 0: before a check, the
+// components whose check is pending (p is not needed after it).  The
+// finisher that follows marks the terms as added.
+__global__ __launch_bounds__(SUB_THREADS) void k_cg_flush(DevPtrs d, int forced) {
   const int sub = sub_of_block(d);
   if (sub < 0) return;
-  const CgRep& cr = d.cg[d.blk_rep[sub / SUBS_PER_TILE]];
-  if (!cr.check) return;
-  bool on[3];
-  double al[3];
+  const int rid = d.blk_rep[sub / SUBS_PER_TILE];
+  const CgRep& cr = d.cg[rid];
+  if (forced ? !cr.run : !cr.check) return;
+  static_assert(U_RING <= 64 && SUB_THREADS >= 192, "one lane per term, one wave per component");
+  __shared__ double h[U_RING][3][2];       // c, d
+  __shared__ double hp[3][2];              // the factors of p
+  __shared__ int cnt[3], off[3];
+  const int t = threadIdx.x;
+  if (t < 192) {
+    const int k = t >> 6, j = t & 63;
+    const int m = cr.state[k] == 1 || (forced && cr.state[k] == 0) ? cr.pend[k] : 0;
+    int slot = cr.cbase[k] + j;
+    slot = slot >= d.ring ? slot - d.ring : slot;
+    const double* hs = d.hist + (((int64_t)rid * U_RING + slot) * 3 + k) * 3;
+    const double ga = j < m ? hs[2] : 1.0;
+    double s = j < m ? hs[0] * ga : 0.0;  // alpha_j gamma_j
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    on[k] = cr.state[k] == 1 && (cr.it[k] & 1) != 0;
-    al[k] = cr.alpha[k];
+    for (int o = 1; o < 64; o <<= 1) {
+      const double up = __shfl_down(s, o, 64);
+      s += j + o < 64 ? up : 0.0;
+    }
+    const double last = __shfl(ga, m > 0 ? m - 1 : 0, 64);
+    if (j < m) {
+      h[j][k][0] = s / ga;
+      h[j][k][1] = last / ga;
+    }
+    if (j == 0) {
+      cnt[k] = m;
+      off[k] = cr.cbase[k];
+      hp[k][0] = m > 0 ? hs[1] * (s / ga) : 0.0;
+      hp[k][1] = m > 0 ? hs[1] * (last / ga) : 0.0;
+    }
   }
-  if (!on[0] && !on[1] && !on[2]) return;
-  const int64_t base = (int64_t)sub * VEC_ELEMS;
+  __syncthreads();
+  const int64_t base = (int64_t)sub * VEC_ELEMS, ring = 3 * d.rows;
+  double ax[3] = {0.0, 0.0, 0.0}, ap[3] = {0.0, 0.0, 0.0};
+  const int m = max(cnt[0], max(cnt[1], cnt[2]));
+#pragma unroll 8
+  for (int j = 0; j < m; ++j) {  // independent loads: 24 in flight per lane
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int le = q * SUB_THREADS + t;
+      const int k = le % 3;
+      if (j >= cnt[k]) continue;
+      int slot = off[k] + j;
+      slot = slot >= d.ring ? slot - d.ring : slot;
+      const double uj = __builtin_nontemporal_load(d.u + slot * ring + base + le);
+      ax[q] += h[j][k][0] * uj;
+      ap[q] += h[j][k][1] * uj;
+    }
+  }
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const int le = q * SUB_THREADS + threadIdx.x;
+    const int le = q * SUB_THREADS + t;
     const int k = le % 3;
-    if (!on_k(on, k)) continue;
+    if (cnt[k] == 0) continue;
     const int64_t e = base + le;
-    d.x[e] += pick3(al, k) * d.p[e];
+    if (hp[k][1] != 0.0) {  // a direction from before the ring's first term
+      const double p0 = d.p[e];
+      ax[q] += hp[k][0] * p0;
+      ap[q] += hp[k][1] * p0;
+    }
+    d.x[e] += ax[q];
+    if (forced) d.p[e] = ap[q];
   }
 }
 
+// Partials (r, u) per sub-tile after an external preconditioner pass (IC(0)),
+// component selection as k_cg_vec's mode.
 __global__ __launch_bounds__(SUB_THREADS) void k_cg_dot_ru(DevPtrs d, int mode) {
   const int sub = sub_of_block(d);
   if (sub < 0) return;
@@ -578,86 +629,115 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_apply(DevPtrs d, int mode) {
 }
 
 // Advance the recurrences of one replica from its totals
-// tot = [gamma0..2, delta0..2, rr0..2].  mode 0: after a fresh start, 1: after
-// a restart, 2: after an iteration, 3: after a true-residual check, 4: after
-// the residual of a warm-start guess.
-__device__ void cg_advance(const DevPtrs& d, CgRep& c, int mode, const double (&tot)[9]) {
-  int finished = 0;
-  for (int k = 0; k < 3; ++k) {
+// tot = [gamma0..2, delta0..2, rr0..2] (in LDS), called by the first wave:
+// lane k < 3 takes component k.  mode 0: after a fresh start, 1: after a
+// restart, 2: after an iteration, 3: after a true-residual check, 4: after
+// the residual of a warm-start guess.  `slot` is the ring slot of the u just
+// multiplied, whose alpha, beta and gamma go to the history; `flushed`
+// (mode 2): the terms before the last one were added to x in this iteration.
+__device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, int mode,
+                                           const double* tot, int slot, int flushed) {
+  const int k = threadIdx.x;
+  int state = -1;
+  bool finished = false, broke = false, restarted = false;
+  if (k < 3) {
     const double gam = tot[k], del = tot[3 + k], rr = tot[6 + k];
-    if (mode == 0 || (mode == 1 && c.state[k] == 3)) {
+    double* hs = d.hist + (((int64_t)rid * U_RING + slot) * 3 + k) * 3;
+    const double bb = mode == 0 ? rr : c.bb[k], lim = c.tol2 * bb;
+    state = c.state[k];
+    if (mode == 0 || (mode == 1 && state == 3)) {
       if (mode == 0) c.bb[k] = rr;
       c.rr[k] = rr;
-      if (c.bb[k] == 0.0) {  // b = 0: x = 0 is exact
-        c.state[k] = 2;
-        ++finished;
-      } else if (rr <= c.tol2 * c.bb[k]) {
-        c.state[k] = 1;
+      if (bb == 0.0) {  // b = 0: x = 0 is exact
+        state = 2;
+        finished = true;
+      } else if (rr <= lim) {
+        state = 1;
       } else if (!(del > 0.0)) {
-        c.state[k] = 2;
-        c.breakdown = 1;
-        atomicOr(&d.ctrl->breakdown, 1);
-        ++finished;
+        state = 2;
+        broke = finished = true;
       } else {
-        c.state[k] = 0;
+        state = 0;
+        const double al = gam / del;
         c.gamma[k] = gam;
-        c.alpha[k] = gam / del;
-        c.alpha_prev[k] = 0.0;
-        c.beta[k] = 0.0;
+        c.alpha[k] = al;
+        c.theta[k] = 0.0;
+        c.pend[k] = 0;
+        c.cbase[k] = slot;
+        hs[0] = al;
+        hs[1] = 0.0;
+        hs[2] = gam;
       }
-    } else if (mode == 2 && c.state[k] == 0) {
-      c.it[k] += 1;
-      c.rr[k] = rr;
-      if (rr <= c.tol2 * c.bb[k]) {
-        c.state[k] = 1;
-      } else {
-        const double beta = gam / c.gamma[k];
-        const double den = del - beta * gam / c.alpha[k];
-        if (!(den > 0.0)) {
-          c.state[k] = 2;
-          c.breakdown = 1;
-        atomicOr(&d.ctrl->breakdown, 1);
-          ++finished;
+    } else if (mode == 2) {
+      int pend = c.pend[k];
+      if (flushed) {
+        pend = 0;
+        c.cbase[k] = slot > 0 ? slot - 1 : d.ring - 1;
+      }
+      if (state == 0) {
+        c.it[k] += 1;
+        pend += 1;
+        c.rr[k] = rr;
+        if (rr <= lim) {
+          state = 1;
         } else {
-          c.beta[k] = beta;
-          c.alpha_prev[k] = c.alpha[k];
-          c.alpha[k] = gam / den;
-          c.gamma[k] = gam;
+          const double beta = gam / c.gamma[k];
+          const double bal = beta / c.alpha[k];
+          const double den = del - bal * gam;
+          if (!(den > 0.0)) {
+            state = 2;
+            broke = finished = true;
+          } else {
+            const double al = gam / den;
+            c.theta[k] = al * bal;
+            c.alpha[k] = al;
+            c.gamma[k] = gam;
+            hs[0] = al;
+            hs[1] = beta;
+            hs[2] = gam;
+          }
         }
       }
-    } else if (mode == 4 && c.state[k] == 0) {
+      c.pend[k] = pend;
+    } else if (mode == 4 && state == 0) {
       // residual of the warm-start guess: done if it passes, else restart
       // from it (no restart is counted)
       c.rr[k] = rr;
-      c.state[k] = rr <= c.tol2 * c.bb[k] ? 1 : 3;
-    } else if (mode == 3 && c.state[k] == 1) {
+      state = rr <= lim ? 1 : 3;
+    } else if (mode == 3 && state == 1) {
       c.rr[k] = rr;
-      if (rr <= c.tol2 * c.bb[k]) {
-        c.state[k] = 2;
-        ++finished;
+      c.pend[k] = 0;  // added before the check
+      if (rr <= lim) {
+        state = 2;
+        finished = true;
       } else {
-        c.state[k] = 3;
-        c.restarts += 1;
+        state = 3;
+        restarted = true;
       }
     }
+    c.state[k] = state;
   }
-  int run = 0, pend = 0, rst = 0;
-  for (int k = 0; k < 3; ++k) {
-    run |= c.state[k] == 0;
-    pend |= c.state[k] == 1;
-    rst |= c.state[k] == 3;
+  const uint64_t run = __ballot(state == 0), pending = __ballot(state == 1);
+  const uint64_t rst = __ballot(state == 3), nf = __ballot(finished), nb = __ballot(broke);
+  const uint64_t nr = __ballot(restarted);
+  if (k == 0) {
+    c.run = run != 0;
+    c.check = run == 0 && pending != 0;
+    c.restart = rst != 0;
+    if (nr) c.restarts += __popcll(nr);
+    if (nb) {
+      c.breakdown = 1;
+      atomicOr(&d.ctrl->breakdown, 1);
+    }
+    if (nf) atomicSub(&d.ctrl->n_notdone, (int)__popcll(nf));
   }
-  c.run = run;
-  c.check = !run && pend;
-  c.restart = rst;
-  if (finished) atomicSub(&d.ctrl->n_notdone, finished);
 }
 
 // Sum `count` partial slots starting at `first` in a fixed order (thread t
 // takes slots t, t + blockDim, ...; then the wave and block trees).  Totals
-// valid in thread 0.
+// in tot (LDS), valid for every thread.
 __device__ __forceinline__ void sum_slots(const double* __restrict__ first, int count,
-                                          double (&tot)[9]) {
+                                          double* tot) {
   __shared__ double lds[FINISH_THREADS / 64][9];
   double acc[9];
 #pragma unroll
@@ -676,13 +756,13 @@ __device__ __forceinline__ void sum_slots(const double* __restrict__ first, int 
     for (int k = 0; k < 9; ++k) lds[wave][k] = acc[k];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 0; k < 9; ++k) {
-      double s = 0.0;
-      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += lds[w][k];
-      tot[k] = s;
-    }
+  if (threadIdx.x < 9) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < FINISH_THREADS / 64; ++w) s += lds[w][threadIdx.x];
+    tot[threadIdx.x] = s;
   }
+  __syncthreads();
 }
 
 // CSR product over the sub-tile's 256 rows.
@@ -773,28 +853,26 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_reduce1(DevPtrs d, int mo
   const int s0 = (b - R.l1_off) * L1_SUBS;
   const int nsub = SUBS_PER_TILE * R.nblk;
   const int cnt = nsub - s0 < L1_SUBS ? nsub - s0 : L1_SUBS;
-  double tot[9];
+  __shared__ double tot[9];
   sum_slots(d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off + s0) * NPART, cnt, tot);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) d.partial2[(int64_t)b * NPART + k] = tot[k];
-  }
+  if (threadIdx.x < 9) d.partial2[(int64_t)b * NPART + threadIdx.x] = tot[threadIdx.x];
 }
 
 // One block per replica: its sub-tile partials (or, for a large replica,
 // the first-level sums) in a fixed order, then the recurrences.
-__global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode) {
+__global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode, int slot,
+                                                              int flushed) {
   const int rid = blockIdx.x;
   const RepDev& R = d.rep[rid];
   CgRep& c = d.cg[rid];
   if (!finish_work(c, mode)) return;
-  double tot[9];
+  __shared__ double tot[9];
   if (R.l1_cnt > 0)
     sum_slots(d.partial2 + (int64_t)R.l1_off * NPART, R.l1_cnt, tot);
   else
     sum_slots(d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART, SUBS_PER_TILE * R.nblk,
               tot);
-  if (threadIdx.x == 0) cg_advance(d, c, mode, tot);
+  if (threadIdx.x < 64) cg_advance(d, rid, c, mode, tot, slot, flushed);
 }
 
 // ---------------------------------------------------------------------------
@@ -869,14 +947,16 @@ hipError_t launch_cg_warm(const DevPtrs& d, const int64_t* id_off, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_cg_flush(const DevPtrs& d, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_flush, dim3(xcd_grid(SUBS_PER_TILE * d.nblk)), dim3(SUB_THREADS), 0, s, d);
+// d.u: the first ring slot
+hipError_t launch_cg_flush(const DevPtrs& d, int forced, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_flush, dim3(xcd_grid(SUBS_PER_TILE * d.nblk)), dim3(SUB_THREADS), 0, s, d,
+                     forced);
   return hipGetLastError();
 }
 
-hipError_t launch_cg_finish(const DevPtrs& d, int mode, hipStream_t s) {
+hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s) {
   if (d.l1_total > 0)
     hipLaunchKernelGGL(k_cg_reduce1, dim3(d.l1_total), dim3(FINISH_THREADS), 0, s, d, mode);
-  hipLaunchKernelGGL(k_cg_finish, dim3(d.nrep), dim3(FINISH_THREADS), 0, s, d, mode);
+  hipLaunchKernelGGL(k_cg_finish, dim3(d.nrep), dim3(FINISH_THREADS), 0, s, d, mode, slot, flushed);
   return hipGetLastError();
 }

@@ -219,14 +219,22 @@ __device__ __forceinline__ void ic_group_sum(double& s0, double& s1, double& s2)
   }
 }
 
+// whether the solves run for the replica of row i (as k_cg_apply's mode): a
+// replica that waits for its check keeps the ring slots it has written
+__device__ __forceinline__ bool ic_runs(const DevPtrs& d, int64_t i, int mode) {
+  const CgRep& cr = d.cg[d.blk_rep[i / ROWS_PER_BLOCK]];
+  return mode == 0 || (mode == 1 ? cr.restart != 0 : cr.run != 0);
+}
+
 // Forward solve L y = r for the rows of one colour (y into u)
 __global__ __launch_bounds__(256) void k_ic_fwd(DevPtrs d, const int32_t* __restrict__ cells,
-                                                int count) {
+                                                int count, int mode) {
   const int g = (blockIdx.x * blockDim.x + threadIdx.x) / IC_LANES;
   const int lane = threadIdx.x & (IC_LANES - 1);
   if (g >= count || d.ctrl->overflow) return;  // whole groups: L was not built, or past the end
   int a, b;
   cell_rows(d, cells[g], a, b);
+  if (a >= b || !ic_runs(d, a, mode)) return;
   const int cap = (int)d.nnz_cap;
   for (int64_t i = a; i < b; ++i) {
     const int e0 = min(d.rowptr[i], cap);
@@ -250,12 +258,13 @@ __global__ __launch_bounds__(256) void k_ic_fwd(DevPtrs d, const int32_t* __rest
 
 // Backward solve L^T z = y for the rows of one colour, in place in u
 __global__ __launch_bounds__(256) void k_ic_bwd(DevPtrs d, const int32_t* __restrict__ cells,
-                                                int count) {
+                                                int count, int mode) {
   const int g = (blockIdx.x * blockDim.x + threadIdx.x) / IC_LANES;
   const int lane = threadIdx.x & (IC_LANES - 1);
   if (g >= count || d.ctrl->overflow) return;
   int a, b;
   cell_rows(d, cells[g], a, b);
+  if (a >= b || !ic_runs(d, a, mode)) return;
   const int cap = (int)d.nnz_cap;
   for (int64_t i = (int64_t)b - 1; i >= a; --i) {
     const int r0 = min(d.rowptr[i], cap), r1 = min(d.rowptr[i + 1], cap);
@@ -318,19 +327,19 @@ hipError_t launch_ic_factor(const DevPtrs& d, const int32_t* color_off, int ncol
   return hipGetLastError();
 }
 
-hipError_t launch_ic_apply(const DevPtrs& d, const int32_t* color_off, int ncolors,
+hipError_t launch_ic_apply(const DevPtrs& d, const int32_t* color_off, int ncolors, int mode,
                            hipStream_t s) {
   for (int c = 0; c < ncolors; ++c) {
     const int cnt = color_off[c + 1] - color_off[c];
     if (cnt == 0) continue;
     hipLaunchKernelGGL(k_ic_fwd, dim3(nb256((int64_t)IC_LANES * cnt)), dim3(256), 0, s, d,
-                       d.ic_cells + color_off[c], cnt);
+                       d.ic_cells + color_off[c], cnt, mode);
   }
   for (int c = ncolors - 1; c >= 0; --c) {
     const int cnt = color_off[c + 1] - color_off[c];
     if (cnt == 0) continue;
     hipLaunchKernelGGL(k_ic_bwd, dim3(nb256((int64_t)IC_LANES * cnt)), dim3(256), 0, s, d,
-                       d.ic_cells + color_off[c], cnt);
+                       d.ic_cells + color_off[c], cnt, mode);
   }
   return hipGetLastError();
 }

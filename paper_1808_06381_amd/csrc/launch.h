@@ -37,14 +37,15 @@ hipError_t launch_cg_vec(const DevPtrs& d, int mode, hipStream_t s, hipEvent_t e
                          hipEvent_t ev1 = nullptr);
 hipError_t launch_cg_spmv(const DevPtrs& d, int mode, int start_mode, hipStream_t s,
                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t launch_cg_finish(const DevPtrs& d, int mode, hipStream_t s);
-hipError_t launch_cg_flush(const DevPtrs& d, hipStream_t s);
+hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s);
+hipError_t launch_cg_flush(const DevPtrs& d, int forced, hipStream_t s);
 hipError_t launch_cg_warm(const DevPtrs& d, const int64_t* id_off, hipStream_t s);
 hipError_t launch_cg_apply(const DevPtrs& d, int mode, hipStream_t s, hipEvent_t ev0 = nullptr,
                            hipEvent_t ev1 = nullptr);
 hipError_t launch_cg_dot_ru(const DevPtrs& d, int mode, hipStream_t s);
 hipError_t launch_ic_factor(const DevPtrs& d, const int32_t* color_off, int ncolors, hipStream_t s);
-hipError_t launch_ic_apply(const DevPtrs& d, const int32_t* color_off, int ncolors, hipStream_t s);
+hipError_t launch_ic_apply(const DevPtrs& d, const int32_t* color_off, int ncolors, int mode,
+                           hipStream_t s);
 hipError_t launch_ic_export(const DevPtrs& d, const int64_t* id_off, int64_t* rows, int64_t* cols,
                             double* vals, double* diag, hipStream_t s);
 struct MpPtrs;

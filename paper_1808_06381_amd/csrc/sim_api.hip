@@ -103,6 +103,9 @@ struct sim_t {
   int32_t graph_K = 0;
   // IC(0) preconditioner
   bool ic0 = false;
+  // the scalar CG's rotating buffers: ring slot of the last u, which of the
+  // two residual buffers holds r, ring terms written since the last full flush
+  struct CgRing { int slot = 0, par = 0, used = 0; } ring;
   bool warm = false;         // step solves start from the previous velocities
   void* sq_scratch = nullptr;  // structure-factor scratch (grown on demand)
   size_t sq_bytes = 0;
@@ -458,13 +461,34 @@ static int cg_maxit(const sim_t* s) {
   return maxit;
 }
 
+// the device pointers with the CG's rotating buffers in place: r the current
+// residual, s the one before it, u the ring slot in use
+static DevPtrs cg_view(const sim_t* s) {
+  DevPtrs d = s->d;
+  if (s->ring.par) std::swap(d.r, d.s);
+  d.u += (int64_t)s->ring.slot * 3 * s->rows;
+  return d;
+}
+
+// the buffers move on by one iteration (k_cg_vec has written the new residual
+// over the older one and u into the next slot); true if the ring was full, so
+// that its terms had to be added to x first
+static bool ring_advance(sim_t::CgRing& g, int len) {
+  const bool full = g.used == len - 1;
+  g.used = full ? 1 : g.used + 1;
+  g.slot = g.slot + 1 == len ? 0 : g.slot + 1;
+  g.par ^= 1;
+  return full;
+}
+
 // u = M^-1 r by the learned product or the IC(0) triangular solves (with
 // the (r, u) partials), for the components selected by mode
 static int queue_apply(sim_t* s, int mode, hipEvent_t e0, hipEvent_t e1, int rev = 0) {
-  DevPtrs d = s->d;
+  DevPtrs d = cg_view(s);
   d.rev = rev;
   if (d.ic0) {
-    HIPCHK(launch_ic_apply(d, s->ic_color_off.data(), (int)s->ic_color_off.size() - 1, s->stream));
+    HIPCHK(launch_ic_apply(d, s->ic_color_off.data(), (int)s->ic_color_off.size() - 1, mode,
+                           s->stream));
     HIPCHK(launch_cg_dot_ru(d, mode, s->stream));
   } else {
     HIPCHK(launch_cg_apply(d, mode, s->stream, e0, e1));
@@ -499,7 +523,8 @@ static int prepare_precond(sim_t* s) {
 // x = v_prev, r = b - A x, done if r passes, else the restart path.
 static int cg_queue_start(sim_t* s, double tol, bool warm) {
   s->vv_valid = false;
-  const DevPtrs& d = s->d;
+  s->ring = sim_t::CgRing();
+  const DevPtrs d = cg_view(s);
   const bool ext = d.learned || d.ic0;
   HIPCHK(launch_cg_reset(d, tol, s->stream));
   HIPCHK(launch_cg_vec(d, 0, s->stream));
@@ -508,18 +533,18 @@ static int cg_queue_start(sim_t* s, double tol, bool warm) {
     if (rc) return rc;
   }
   HIPCHK(launch_cg_spmv(d, 0, 0, s->stream));
-  HIPCHK(launch_cg_finish(d, 0, s->stream));
+  HIPCHK(launch_cg_finish(d, 0, s->ring.slot, 0, s->stream));
   if (warm) {
     HIPCHK(launch_cg_warm(d, s->id_off_d, s->stream));
     HIPCHK(launch_cg_spmv(d, 2, 0, s->stream));
-    HIPCHK(launch_cg_finish(d, 4, s->stream));
+    HIPCHK(launch_cg_finish(d, 4, s->ring.slot, 0, s->stream));
     HIPCHK(launch_cg_vec(d, 1, s->stream));
     if (ext) {
       int rc = queue_apply(s, 1, nullptr, nullptr);
       if (rc) return rc;
     }
     HIPCHK(launch_cg_spmv(d, 0, 1, s->stream));
-    HIPCHK(launch_cg_finish(d, 1, s->stream));
+    HIPCHK(launch_cg_finish(d, 1, s->ring.slot, 0, s->stream));
   }
   return SIM_OK;
 }
@@ -528,7 +553,7 @@ static int cg_queue_start(sim_t* s, double tol, bool warm) {
 // which is off when probes is false), then the check round: true residuals
 // of replicas whose components all passed, restarts of those that failed
 static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
-  const DevPtrs& d = s->d;
+  const DevPtrs d = cg_view(s);  // for the configuration; the buffers rotate below
   hipStream_t stream = s->stream;
   const bool ext = d.learned || d.ic0;  // a separate preconditioner pass
   // iteration form of the probe: an event before iteration 0 of the first
@@ -549,10 +574,14 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
     // vector update, then (learned) u = M^-1 r, then w = A u; consecutive
     // streaming launches walk their sub-tiles in opposite directions
     const int order[3] = {0, 2, 1};
+    DevPtrs dk = cg_view(s);
+    const bool full = ring_advance(s->ring, s->d.ring);
+    if (full) HIPCHK(launch_cg_flush(s->d, 1, stream));
+    dk.u = cg_view(s).u;  // the vector pass reads the old r and s, writes the next u
     for (int oi = 0; oi < 3; ++oi) {
       const int kern = order[oi];
       if (kern == 2 && !ext) continue;
-      DevPtrs dk = d;
+      if (oi > 0) dk = cg_view(s);
       dk.rev = nstream++ & 1;
       hipEvent_t e0 = nullptr, e1 = nullptr;
       if (probe && !(kern == 2 && d.ic0)) {  // the IC(0) pass is many launches: not probed
@@ -568,19 +597,20 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
         if (rc) return rc;
       }
     }
-    HIPCHK(launch_cg_finish(d, 2, stream));
+    HIPCHK(launch_cg_finish(s->d, 2, s->ring.slot, full ? 1 : 0, stream));
     if (run_form) HIPCHK(hipEventRecord(s->prof_run_ev[k + 1], stream));
   }
-  HIPCHK(launch_cg_flush(d, stream));  // x complete where a check is pending
-  HIPCHK(launch_cg_spmv(d, 1, 0, stream));
-  HIPCHK(launch_cg_finish(d, 3, stream));
-  HIPCHK(launch_cg_vec(d, 1, stream));
+  HIPCHK(launch_cg_flush(s->d, 0, stream));  // x complete where a check is pending
+  const DevPtrs dc = cg_view(s);
+  HIPCHK(launch_cg_spmv(dc, 1, 0, stream));
+  HIPCHK(launch_cg_finish(dc, 3, s->ring.slot, 0, stream));
+  HIPCHK(launch_cg_vec(dc, 1, stream));
   if (ext) {
     int rc = queue_apply(s, 1, nullptr, nullptr);
     if (rc) return rc;
   }
-  HIPCHK(launch_cg_spmv(d, 0, 1, stream));
-  HIPCHK(launch_cg_finish(d, 1, stream));
+  HIPCHK(launch_cg_spmv(dc, 0, 1, stream));
+  HIPCHK(launch_cg_finish(dc, 1, s->ring.slot, 0, stream));
   return SIM_OK;
 }
 
@@ -654,10 +684,9 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
     const double rows = (double)s->rows, nnz = (double)s->ctrl_h->nnz;
     const double ntile = (double)(SUBS_PER_TILE * d.nblk);  // partial slots written
     const double per_launch[kProfKernels] = {
-        // vector kernel: r, p, w, s, x read (120 B/row), 1/diag (8), p, s, x, r, u written
-        // (120); with the learned preconditioner u is read instead of 1/diag and not written;
-        // x (48 of these bytes) only in odd iterations (see below)
-        (learned ? rows * 240.0 : rows * 248.0) + ntile * 6.0 * 8.0,
+        // vector kernel: the last two residuals and w read (72 B/row), the new residual
+        // written (24); with Jacobi 1/diag read (8) and u written (24) too
+        (learned ? rows * 96.0 : rows * 128.0) + ntile * 6.0 * 8.0,
         // product: row pointers (4), u (24), diag (8), w written (24), CSR col + value
         rows * 60.0 + 4.0 + nnz * (4.0 + (s->d.spmv_fp32 ? 4.0 : 8.0)) + ntile * 3.0 * 8.0,
         // learned apply: row pointers (4), r (24), M^-1 diagonal (8), u written (24),
@@ -695,9 +724,7 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
       if (smp.iter >= itmin - 1) continue;
       acc.launches += 1;
       acc.ms += ms;
-      // the vector kernel updates x every other iteration: in an even one
-      // (iteration number = every component's count here) x is not touched
-      acc.bytes += per_launch[smp.kernel] - (smp.kernel == 0 && smp.iter % 2 == 0 ? 48.0 * rows : 0.0);
+      acc.bytes += per_launch[smp.kernel];
     }
     s->prof_pending.clear();
     // the next solve samples the next residue, so that every position in a
@@ -1024,7 +1051,16 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   ALLOC(d.r, sizeof(double) * 3 * rows);
   ALLOC(d.s, sizeof(double) * 3 * rows);
   ALLOC(d.w, sizeof(double) * 3 * rows);
-  ALLOC(d.u, sizeof(double) * 3 * rows);
+  // slots of the ring of u: 64 (a whole solve of the usual length without an
+  // intermediate pass over x) while they take at most 2 GiB, else fewer, at
+  // least 16.  Step times with 16 / 32 / 64 slots: N = 1e3 (ten steps, Jacobi)
+  // 12.2 / 12.2 / 12.0 ms, N = 1e5 (two, learned) 2.52 / 2.51 / 2.47, N = 1e6
+  // 4.07 / 4.00 / 3.99; N = 8e6 29.2 with 16 and 32 (29.8 with 8, 31.0 with 4)
+  d.ring = s->block ? 1 : (int32_t)std::min<int64_t>(
+                              U_RING, std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
+  const size_t slots = d.ring;
+  ALLOC(d.u, sizeof(double) * 3 * rows * slots);
+  ALLOC(d.hist, sizeof(double) * 9 * U_RING * replicas);
   ALLOC(d.vel_orig, sizeof(double) * 3 * (size_t)n_total);
   ALLOC(s->io, sizeof(double) * 3 * (size_t)n_total);
   ALLOC(s->id_off_d, sizeof(int64_t) * replicas);
@@ -1122,8 +1158,8 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   // padding rows never receive a cell: keep their cell index a valid entry
   if ((e = hipMemset(d.cellidx, 0, sizeof(int32_t) * rows))) return fail(e, "clear cells");
   if ((e = hipMemset(d.cellidx_alt, 0, sizeof(int32_t) * rows))) return fail(e, "clear cells");
-  // padding rows keep u = 0 (the IC(0) and learned passes write real rows only)
-  if ((e = hipMemset(d.u, 0, sizeof(double) * 3 * rows))) return fail(e, "clear u");
+  // padding rows keep u = 0 (the IC(0) passes write real rows only)
+  if (s->ic0 && (e = hipMemset(d.u, 0, sizeof(double) * 3 * rows * slots))) return fail(e, "clear u");
   if (s->ic0) {
     if ((e = hipMemcpy((void*)d.cell_color, ccolor_h.data(), sizeof(int32_t) * ccolor_h.size(),
                        hipMemcpyHostToDevice)))
@@ -1575,7 +1611,9 @@ static int step_graph(sim_t* s, sim_stats* st) {
     g = &s->graphs.back();
     s->graph_captures += 1;
   } else {
-    // the host-side effects of build_system
+    // the host-side effects of build_system and of the queued iterations
+    s->ring = sim_t::CgRing();
+    for (int k = 0; k < K; ++k) (void)ring_advance(s->ring, s->d.ring);
     std::swap(s->d.pos, s->d.pos_alt);
     std::swap(s->d.cellidx, s->d.cellidx_alt);
   }

@@ -9,7 +9,9 @@
 //   rowptr   int32[rows+1]   CSR of the off-diagonal part of A, full rows
 //   col/val  int32/double    -alpha*w_ij per directed pair (valf: FP32 copy)
 //   diag     double[rows]    gamma0 + alpha*sum_j w_ij (dinv = 1/diag)
-//   b, x, p, r, s, w, u   double[3*rows]  right-hand sides and the CG vectors
+//   b, x, p, r, s, w      double[3*rows]  right-hand sides and the CG vectors
+//   u        double[U_RING][3*rows]  the last preconditioned residuals (the
+//                            scalar solve's ring; the block solve uses one)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -76,11 +78,12 @@ struct CgRep {
   double rr[3];     // ||r||^2 (recursive while iterating, true after a check)
   double gamma[3];  // (r, M^-1 r) of the current iterate
   double alpha[3];
-  double alpha_prev[3];  // the previous iteration's alpha (0 after a start or restart)
-  double beta[3];
+  double theta[3];  // alpha beta / alpha of the previous iteration (0 after a (re)start)
   double tol2;      // tolerance^2 of this solve
   int32_t state[3]; // 0 iterating, 1 check pending, 2 done, 3 restart pending
   int32_t it[3];
+  int32_t pend[3];  // ring terms u_j not yet added to x ...
+  int32_t cbase[3]; // ... and the slot of the first of them
   int32_t run;      // some component iterating
   int32_t check;    // none iterating and some check pending
   int32_t restart;  // some restart pending
@@ -88,6 +91,12 @@ struct CgRep {
   int32_t breakdown;
   int32_t pad;
 };
+static_assert(sizeof(CgRep) % 8 == 0, "CgRep is an array element");
+
+// Most slots of the ring of preconditioned residuals (see cg.hip; a handle
+// uses `ring` of them): x is brought up to date every ring - 1 iterations and
+// before a check.
+#define U_RING 64
 
 // Global control words (one per handle)
 struct Ctrl {
@@ -132,9 +141,10 @@ struct DevPtrs {
   double* x;
   double* p;
   double* r;
-  double* s;
+  double* s;                // scalar CG: the residual before r (the two alternate); block CG: A p
   double* w;
-  double* u;
+  double* u;                // scalar CG: the ring slot in use, of `ring`
+  double* hist;             // [replicas][U_RING][3][3] alpha, beta, gamma of the ring's terms
   double* vel_orig;         // velocities of the last step, original order
   float* er;                // r_ij / rc per CSR entry (learned preconditioner input)
   const double* mdiag;      // learned M^-1 diagonal, or null (Jacobi)
@@ -165,6 +175,8 @@ struct DevPtrs {
   int32_t l1_total;         // first-level reduction blocks over all replicas
   int32_t want_er;          // 1: the pair terms write er (the network's edge input)
   int32_t vec_nt;           // 1: the CG vector kernel streams with nontemporal accesses
+  int32_t ring;             // slots of the ring of u
+  int32_t pad0;
   int32_t rev;              // 1: each XCD walks its CG sub-tiles from the last
 };
 static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padding");
