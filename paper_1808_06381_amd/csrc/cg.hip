@@ -635,8 +635,11 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_apply(DevPtrs d, int mode) {
 // the residual of a warm-start guess.  `slot` is the ring slot of the u just
 // multiplied, whose alpha, beta and gamma go to the history; `flushed`
 // (mode 2): the terms before the last one were added to x in this iteration.
+// c may be a copy in LDS that several blocks advance alike; one of them,
+// `leader`, also writes the history and the control words.
 __device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, int mode,
-                                           const double* tot, int slot, int flushed) {
+                                           const double* tot, int slot, int flushed,
+                                           bool leader) {
   const int k = threadIdx.x;
   int state = -1;
   bool finished = false, broke = false, restarted = false;
@@ -664,9 +667,11 @@ __device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, 
         c.theta[k] = 0.0;
         c.pend[k] = 0;
         c.cbase[k] = slot;
-        hs[0] = al;
-        hs[1] = 0.0;
-        hs[2] = gam;
+        if (leader) {
+          hs[0] = al;
+          hs[1] = 0.0;
+          hs[2] = gam;
+        }
       }
     } else if (mode == 2) {
       int pend = c.pend[k];
@@ -692,9 +697,11 @@ __device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, 
             c.theta[k] = al * bal;
             c.alpha[k] = al;
             c.gamma[k] = gam;
-            hs[0] = al;
-            hs[1] = beta;
-            hs[2] = gam;
+            if (leader) {
+              hs[0] = al;
+              hs[1] = beta;
+              hs[2] = gam;
+            }
           }
         }
       }
@@ -727,9 +734,9 @@ __device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, 
     if (nr) c.restarts += __popcll(nr);
     if (nb) {
       c.breakdown = 1;
-      atomicOr(&d.ctrl->breakdown, 1);
+      if (leader) atomicOr(&d.ctrl->breakdown, 1);
     }
-    if (nf) atomicSub(&d.ctrl->n_notdone, (int)__popcll(nf));
+    if (nf && leader) atomicSub(&d.ctrl->n_notdone, (int)__popcll(nf));
   }
 }
 
@@ -858,13 +865,27 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_reduce1(DevPtrs d, int mo
   if (threadIdx.x < 9) d.partial2[(int64_t)b * NPART + threadIdx.x] = tot[threadIdx.x];
 }
 
+// words of the per-replica state, as copied between memory and LDS
+constexpr int CG_WORDS = sizeof(CgRep) / 8;
+__device__ __forceinline__ void copy_state(CgRep* dst, const CgRep* src) {
+  if (threadIdx.x < CG_WORDS)
+    reinterpret_cast<uint64_t*>(dst)[threadIdx.x] =
+        reinterpret_cast<const uint64_t*>(src)[threadIdx.x];
+}
+
 // One block per replica: its sub-tile partials (or, for a large replica,
-// the first-level sums) in a fixed order, then the recurrences.
+// the first-level sums) in a fixed order, then the recurrences.  `from`: the
+// state to advance into d.cg (d.cg itself, or the other copy after an odd
+// number of fused iterations).
 __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode, int slot,
-                                                              int flushed) {
+                                                              int flushed, const CgRep* from) {
   const int rid = blockIdx.x;
   const RepDev& R = d.rep[rid];
   CgRep& c = d.cg[rid];
+  if (from != d.cg) {
+    copy_state(&c, from + rid);
+    __syncthreads();
+  }
   if (!finish_work(c, mode)) return;
   __shared__ double tot[9];
   if (R.l1_cnt > 0)
@@ -872,7 +893,212 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mod
   else
     sum_slots(d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART, SUBS_PER_TILE * R.nblk,
               tot);
-  if (threadIdx.x < 64) cg_advance(d, rid, c, mode, tot, slot, flushed);
+  if (threadIdx.x < 64) cg_advance(d, rid, c, mode, tot, slot, flushed, true);
+}
+
+// ---------------------------------------------------------------------------
+// One launch for finisher, vector pass and the product that follows, for
+// handles whose iterations are a few microseconds of work each, where every
+// launch costs about as much again.  Each block forms the replica's new
+// scalars itself from the last launch's sub-tile partials (the same sums in
+// the same order in every block; the replica's first block stores them), and
+// takes the new residual of a gathered row j from the three vectors that
+// define it, r_j, s_j and w_j, instead of waiting for a pass that stores it:
+//   Jacobi:   u_j = (1/diag_j) r'_j, w' = A u        one launch per iteration
+//   learned:  u = M^-1 r'                            then k_cg_spmv: w = A u
+// What is read here by other blocks is not written here: the new residual
+// goes to a third buffer, w', the partials and the scalars to second ones.
+// Every sum has the operands and the order of the separate kernels (product
+// in entry order), so both forms give the same bits.  Three gathers per entry
+// in place of one: for large handles the separate passes are faster.
+// Bound by launch and memory latency (a sub-tile's chain is partials -> scalars
+// -> products -> row sums; entries and the rows they gather are loaded before
+// the scalars are known).  T threads for the 256 rows: with few tiles the
+// chip is filled by their entries (T at a time); rows and elements are the
+// first 256 threads' work.
+// The times and the limits are beside FUSED_ROWS.
+// ---------------------------------------------------------------------------
+template <int T, bool LEARNED, bool FP32>
+__global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
+  const int sub = sub_of_block(d);
+  if (sub < 0) return;
+  const int rid = d.blk_rep[sub / SUBS_PER_TILE];
+  const RepDev& R = d.rep[rid];
+  __shared__ CgRep c;
+  __shared__ double prod[3][T];
+  __shared__ double io[3 * SUB_ROWS];   // the source's own rows, then the results
+  __shared__ double lds[SUB_THREADS / 64][9];
+  __shared__ double tot[9];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const bool rowt = t < SUB_ROWS;       // this thread has a row (and three elements)
+  const int64_t base = (int64_t)sub * SUB_ROWS;
+  copy_state(&c, f.cg_in + rid);
+  // everything that does not depend on the scalars is loaded first
+  const int cap = (int)d.nnz_cap;       // clamped as in lane_tile
+  const int E0 = min(d.rowptr[base], cap);
+  const int ne = min(d.rowptr[base + SUB_ROWS], cap) - E0;
+  int r0 = 0, r1 = 0;
+  double dgi = 0.0, er[3], es[3], ew[3], ed[3];
+  if (rowt) {
+    r0 = min(d.rowptr[base + t], cap) - E0;
+    r1 = min(d.rowptr[base + t + 1], cap) - E0;
+    dgi = LEARNED ? d.mdiag[base + t] : d.diag[base + t];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int le = q * SUB_THREADS + t;
+      er[q] = d.r[3 * base + le];
+      es[q] = d.s[3 * base + le];
+      ew[q] = d.w[3 * base + le];
+      ed[q] = LEARNED || d.pc_none ? 1.0 : d.dinv[base + le / 3];
+    }
+  }
+  auto value = [&](int e) {
+    if constexpr (LEARNED) return d.moff[e];
+    else if constexpr (FP32) return d.valf[e];
+    else return d.val[e];
+  };
+  using VT = decltype(value(0));
+  VT m = VT(0);
+  double gr[3], gs[3], gw[3], gd = 1.0;
+  auto load = [&](int e) {   // entry e of the sub-tile and the rows it gathers
+    const int j = d.col[E0 + e];
+    m = value(E0 + e);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      gr[k] = d.r[3 * (int64_t)j + k];
+      gs[k] = d.s[3 * (int64_t)j + k];
+      gw[k] = d.w[3 * (int64_t)j + k];
+    }
+    if (!LEARNED && !d.pc_none) gd = d.dinv[j];
+  };
+  if (t < ne) load(t);
+  __syncthreads();
+  // the state is advanced unless the last launch left it advanced
+  if (!f.first && c.run) {
+    const int nsub = SUBS_PER_TILE * R.nblk;
+    const double* first = f.part_in + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART;
+    if (rowt) {
+      double acc[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) acc[k] = 0.0;
+      for (int q = t; q < nsub; q += FINISH_THREADS) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) acc[k] += first[(int64_t)q * NPART + k];
+      }
+#pragma unroll
+      for (int k = 0; k < 9; ++k) acc[k] = wave_sum(acc[k]);
+      if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) lds[wave][k] = acc[k];
+      }
+    }
+    __syncthreads();
+    if (t < 9) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < FINISH_THREADS / 64; ++w) s += lds[w][t];
+      tot[t] = s;
+    }
+    __syncthreads();
+    if (t < 64)
+      cg_advance(d, rid, c, 2, tot, f.slot, f.flushed, sub == SUBS_PER_TILE * R.blk_off);
+    __syncthreads();
+  }
+  if (sub == SUBS_PER_TILE * R.blk_off) copy_state(f.cg_out + rid, &c);
+  if (!c.run) return;
+  bool on[3];
+  double al[3], th[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    on[k] = c.state[k] == 0;
+    al[k] = c.alpha[k];
+    th[k] = c.theta[k];
+  }
+  // r' as k_cg_vec forms it
+  auto next = [](double r, double s, double w, double a, double tk) {
+    const double rm = tk != 0.0 ? s : r;
+    return (r + tk * (r - rm)) - a * w;
+  };
+  double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};  // (r,u), (w,u), (r,r)
+  if (rowt) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int le = q * SUB_THREADS + t, k = le % 3;
+      double src = 0.0;
+      if (on_k(on, k)) {
+        const double rk = next(er[q], es[q], ew[q], pick3(al, k), pick3(th, k));
+        f.rnew[3 * base + le] = rk;
+        src = rk;
+        if constexpr (!LEARNED) {
+          src = ed[q] * rk;
+          d.u[3 * base + le] = src;
+          v[k] += rk * src;
+        }
+        v[6 + k] += rk * rk;
+      }
+      io[le] = src;
+    }
+  }
+  double a[3] = {0.0, 0.0, 0.0};
+  for (int c0 = 0; c0 < ne; c0 += T) {
+    if (c0 + t < ne) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        double src = next(gr[k], gs[k], gw[k], al[k], th[k]);
+        if constexpr (!LEARNED) src = gd * src;
+        prod[k][t] = (double)m * src;
+      }
+      if (c0 + T + t < ne) load(c0 + T + t);
+    }
+    __syncthreads();
+    const int lo = r0 > c0 ? r0 : c0, hi = r1 < c0 + T ? r1 : c0 + T;
+    for (int e = lo; e < hi; ++e) {
+      a[0] += prod[0][e - c0];
+      a[1] += prod[1][e - c0];
+      a[2] += prod[2][e - c0];
+    }
+    __syncthreads();
+  }
+  if (ne == 0) __syncthreads();
+  double out[3] = {0.0, 0.0, 0.0};
+  if (rowt) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double sk = io[3 * t + k];
+      if (on_k(on, k)) {
+        out[k] = dgi * sk + a[k];
+        // learned: (r, u), u the result; Jacobi: (w, u), u the source
+        if constexpr (LEARNED) v[k] += sk * out[k];
+        else v[3 + k] += out[k] * sk;
+      }
+    }
+  }
+  __syncthreads();  // every own row read
+  if (rowt) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) io[3 * t + k] = out[k];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v[k] = wave_sum(v[k]);
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) lds[wave][k] = v[k];
+    }
+  }
+  __syncthreads();
+  if (rowt) {
+    double* __restrict__ dst = LEARNED ? d.u : f.wnew;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int le = q * SUB_THREADS + t;
+      if (on_k(on, le % 3)) dst[3 * base + le] = io[le];
+    }
+  }
+  if (t < 9 && !(LEARNED && t / 3 == 1)) {  // learned: k_cg_spmv writes (w, u)
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < SUB_THREADS / 64; ++w) s += lds[w][t];
+    d.partial[(int64_t)sub * NPART + t] = s;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -954,9 +1180,28 @@ hipError_t launch_cg_flush(const DevPtrs& d, int forced, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s) {
+template <int T>
+static void launch_fused_t(const DevPtrs& d, const CgFused& f, hipStream_t s) {
+  const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(T);
+  if (d.learned)
+    hipLaunchKernelGGL((k_cg_fused<T, true, false>), g, b, 0, s, d, f);
+  else if (d.spmv_fp32)
+    hipLaunchKernelGGL((k_cg_fused<T, false, true>), g, b, 0, s, d, f);
+  else
+    hipLaunchKernelGGL((k_cg_fused<T, false, false>), g, b, 0, s, d, f);
+}
+
+hipError_t launch_cg_fused(const DevPtrs& d, const CgFused& f, hipStream_t s) {
+  if (SUBS_PER_TILE * d.nblk <= FUSED_WIDE_SUBS) launch_fused_t<1024>(d, f, s);
+  else launch_fused_t<512>(d, f, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s,
+                            const CgRep* from) {
   if (d.l1_total > 0)
     hipLaunchKernelGGL(k_cg_reduce1, dim3(d.l1_total), dim3(FINISH_THREADS), 0, s, d, mode);
-  hipLaunchKernelGGL(k_cg_finish, dim3(d.nrep), dim3(FINISH_THREADS), 0, s, d, mode, slot, flushed);
+  hipLaunchKernelGGL(k_cg_finish, dim3(d.nrep), dim3(FINISH_THREADS), 0, s, d, mode, slot, flushed,
+                     from ? from : d.cg);
   return hipGetLastError();
 }

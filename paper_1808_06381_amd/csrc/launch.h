@@ -37,7 +37,21 @@ hipError_t launch_cg_vec(const DevPtrs& d, int mode, hipStream_t s, hipEvent_t e
                          hipEvent_t ev1 = nullptr);
 hipError_t launch_cg_spmv(const DevPtrs& d, int mode, int start_mode, hipStream_t s,
                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s);
+// from: the scalars to advance into d.cg (null: d.cg itself)
+hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s,
+                            const CgRep* from = nullptr);
+struct CgFused {           // buffers of a fused iteration besides DevPtrs' own
+  const CgRep* cg_in;      // scalars before ...
+  CgRep* cg_out;           // ... and after the advance at the launch's start
+  const double* part_in;   // sub-tile partials of the last iteration (d.partial: this one's)
+  double* rnew;            // the new residual
+  double* wnew;            // Jacobi: A u
+  int32_t slot;            // ring slot of the last iteration's u
+  int32_t flushed;         // the ring was emptied in the last iteration
+  int32_t first;           // 1: the scalars are advanced already
+  int32_t pad;
+};
+hipError_t launch_cg_fused(const DevPtrs& d, const CgFused& f, hipStream_t s);
 hipError_t launch_cg_flush(const DevPtrs& d, int forced, hipStream_t s);
 hipError_t launch_cg_warm(const DevPtrs& d, const int64_t* id_off, hipStream_t s);
 hipError_t launch_cg_apply(const DevPtrs& d, int mode, hipStream_t s, hipEvent_t ev0 = nullptr,

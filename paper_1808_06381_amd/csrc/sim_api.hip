@@ -103,9 +103,14 @@ struct sim_t {
   int32_t graph_K = 0;
   // IC(0) preconditioner
   bool ic0 = false;
-  // the scalar CG's rotating buffers: ring slot of the last u, which of the
-  // two residual buffers holds r, ring terms written since the last full flush
-  struct CgRing { int slot = 0, par = 0, used = 0; } ring;
+  // the scalar CG's rotating buffers: ring slot of the last u, ring terms
+  // written since the last full flush, the residual buffers that hold r, the
+  // residual before it and nothing, and which of the two w buffers holds w
+  struct CgRing { int slot = 0, used = 0, r = 0, s = 1, spare = 2, w = 0; } ring;
+  double* rbuf[3] = {};        // the third, and the second of the others, only
+  double* wbuf[2] = {};        // where the fused iterations may run
+  CgRep* cg2 = nullptr;
+  double* partial2nd = nullptr;
   bool warm = false;         // step solves start from the previous velocities
   void* sq_scratch = nullptr;  // structure-factor scratch (grown on demand)
   size_t sq_bytes = 0;
@@ -465,19 +470,34 @@ static int cg_maxit(const sim_t* s) {
 // residual, s the one before it, u the ring slot in use
 static DevPtrs cg_view(const sim_t* s) {
   DevPtrs d = s->d;
-  if (s->ring.par) std::swap(d.r, d.s);
+  d.r = s->rbuf[s->ring.r];
+  d.s = s->rbuf[s->ring.s];
+  d.w = s->wbuf[s->ring.w];
   d.u += (int64_t)s->ring.slot * 3 * s->rows;
   return d;
 }
 
-// the buffers move on by one iteration (k_cg_vec has written the new residual
-// over the older one and u into the next slot); true if the ring was full, so
-// that its terms had to be added to x first
-static bool ring_advance(sim_t::CgRing& g, int len) {
+// the fused iterations (see k_cg_fused) where the handle is small enough, has
+// their buffers, and its product is tuned to a form with their order of sums
+// (a row's products in entry order: variants of one lane or entry-parallel)
+static bool fused_ok(const sim_t* s) {
+  const int32_t var = s->d.learned ? s->d.apply_var : s->d.spmv_var;
+  return s->cg2 && !s->d.ic0 && (var == 0 || var >= CSR_VARIANT_DEFAULT);
+}
+
+// the buffers move on by one iteration: u into the next slot; the new residual
+// over the older one, or (fused) into the spare buffer, and with Jacobi w into
+// the other one; true if the ring was full, so that its terms had to be added
+// to x first
+static bool ring_advance(sim_t::CgRing& g, int len, bool fused, bool learned) {
   const bool full = g.used == len - 1;
   g.used = full ? 1 : g.used + 1;
   g.slot = g.slot + 1 == len ? 0 : g.slot + 1;
-  g.par ^= 1;
+  const int newest = fused ? g.spare : g.s;
+  if (fused) g.spare = g.s;
+  g.s = g.r;
+  g.r = newest;
+  if (fused && !learned) g.w ^= 1;
   return full;
 }
 
@@ -559,6 +579,7 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
   // iteration form of the probe: an event before iteration 0 of the first
   // chunk and one after each of its iterations; the poll keeps the longest
   // run of iterations that every component went through
+  const bool probes_on = probes && s->prof_every > 0;  // times the separate kernels
   const bool run_form = probes && s->prof_every > 0 && (s->prof_solves & 1) && first == 0 &&
                         n + 1 <= (int)s->prof_run_ev.size();
   if (run_form) {
@@ -566,7 +587,56 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
     HIPCHK(hipEventRecord(s->prof_run_ev[0], stream));
   }
   int nstream = 0;  // streaming CG launches queued so far in this chunk
-  for (int k = 0; k < n; ++k) {
+  // fused iterations: each launch first advances the scalars over the last
+  // one's partials, the scalars and partials alternating between two copies
+  const bool fused = !probes_on && fused_ok(s);
+  const CgRep* cur = s->d.cg;       // the scalars, advanced unless `open`
+  double* part = s->d.partial;      // the last iteration's partials
+  bool open = false, open_flushed = false;
+  for (int k = 0; fused && k < n; ++k) {
+    DevPtrs dk = cg_view(s);
+    const int slot = s->ring.slot;
+    const bool full = ring_advance(s->ring, d.ring, true, d.learned);
+    if (full) {
+      if (open) {
+        DevPtrs df = s->d;
+        df.partial = part;
+        HIPCHK(launch_cg_finish(df, 2, slot, open_flushed, stream, cur));
+        cur = s->d.cg;
+        open = false;
+      }
+      HIPCHK(launch_cg_flush(s->d, 1, stream));
+    }
+    const DevPtrs dn = cg_view(s);
+    CgFused f{};
+    f.cg_in = cur;
+    f.cg_out = cur == s->d.cg ? s->cg2 : s->d.cg;
+    f.part_in = part;
+    part = part == s->d.partial ? s->partial2nd : s->d.partial;
+    f.rnew = dn.r;
+    f.wnew = dn.w;
+    f.slot = slot;
+    f.flushed = open_flushed;
+    f.first = !open;
+    dk.u = dn.u;
+    dk.partial = part;
+    HIPCHK(launch_cg_fused(dk, f, stream));
+    if (d.learned) {
+      DevPtrs dp = dn;
+      dp.cg = f.cg_out;
+      dp.partial = part;
+      HIPCHK(launch_cg_spmv(dp, 0, 2, stream));
+    }
+    cur = f.cg_out;
+    open = true;
+    open_flushed = full;
+  }
+  if (open) {
+    DevPtrs df = s->d;
+    df.partial = part;
+    HIPCHK(launch_cg_finish(df, 2, s->ring.slot, open_flushed, stream, cur));
+  }
+  for (int k = 0; !fused && k < n; ++k) {
     const int g = first + k;
     const bool probe = probes && !(s->prof_solves & 1) && s->prof_every > 0 &&
                        g % s->prof_every == s->prof_phase &&
@@ -575,7 +645,7 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
     // streaming launches walk their sub-tiles in opposite directions
     const int order[3] = {0, 2, 1};
     DevPtrs dk = cg_view(s);
-    const bool full = ring_advance(s->ring, s->d.ring);
+    const bool full = ring_advance(s->ring, s->d.ring, false, d.learned);
     if (full) HIPCHK(launch_cg_flush(s->d, 1, stream));
     dk.u = cg_view(s).u;  // the vector pass reads the old r and s, writes the next u
     for (int oi = 0; oi < 3; ++oi) {
@@ -1060,6 +1130,15 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
                               U_RING, std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
   const size_t slots = d.ring;
   ALLOC(d.u, sizeof(double) * 3 * rows * slots);
+  if (!s->block && !s->ic0 && s->rows <= FUSED_ROWS) {
+    ALLOC(s->cg2, sizeof(CgRep) * replicas);
+    ALLOC(s->partial2nd, sizeof(double) * NPART * SUBS_PER_TILE * d.nblk);
+    ALLOC(s->rbuf[2], sizeof(double) * 3 * rows);
+    ALLOC(s->wbuf[1], sizeof(double) * 3 * rows);
+  }
+  s->rbuf[0] = d.r;
+  s->rbuf[1] = d.s;
+  s->wbuf[0] = d.w;
   ALLOC(d.hist, sizeof(double) * 9 * U_RING * replicas);
   ALLOC(d.vel_orig, sizeof(double) * 3 * (size_t)n_total);
   ALLOC(s->io, sizeof(double) * 3 * (size_t)n_total);
@@ -1613,7 +1692,8 @@ static int step_graph(sim_t* s, sim_stats* st) {
   } else {
     // the host-side effects of build_system and of the queued iterations
     s->ring = sim_t::CgRing();
-    for (int k = 0; k < K; ++k) (void)ring_advance(s->ring, s->d.ring);
+    for (int k = 0; k < K; ++k)
+      (void)ring_advance(s->ring, s->d.ring, fused_ok(s), s->d.learned);
     std::swap(s->d.pos, s->d.pos_alt);
     std::swap(s->d.cellidx, s->d.cellidx_alt);
   }

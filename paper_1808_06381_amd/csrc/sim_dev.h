@@ -202,6 +202,16 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 #define L1_SUBS 256
 #define L1_MIN_SUBS 2048
 
+// Handles of at most FUSED_ROWS rows run finisher, vector pass and product as
+// one launch (k_cg_fused).  Per step, separate kernels against fused with 256 /
+// 512 / 1024 threads per 256-row sub-tile: N = 1e3 (ten steps) 12.0 ms against
+// 10.3 / 8.8 / 8.4; 4 x 20060 rows of 15 entries (ten) 20.8 against 23.0 / 18.8 /
+// 21.2; N = 1e5 learned (two) 2.51 against 2.39 / 2.31 / 2.49; a solve at
+// N = 2.5e5 2.28 against 2.33 / 2.51 / 3.30.  So 1024 threads where the
+// sub-tiles leave half the chip's 256 units idle, else 512.
+#define FUSED_ROWS (128 * 1024)
+#define FUSED_WIDE_SUBS 128
+
 // ---------------------------------------------------------------------------
 // Block -> tile mapping: hardware dispatches workgroups round-robin over the
 // 8 XCDs; give each XCD a contiguous range of row blocks so that the CSR

@@ -1,0 +1,66 @@
+"""Small handles run the CG iterations in fused launches (finisher, vector
+pass and product in one).  They must give the bits of the separate kernels,
+which the timing probe selects: at the edges of tiles and sub-tiles (1 row,
+255..257, 1023..1025), both widths of the launch, the largest fused handle,
+rows longer than a pass, uneven batches, every preconditioner and value type
+that takes them, and rings that wrap.
+"""
+import os
+
+import numpy as np
+import pytest
+
+from paper_1808_06381_amd import inputs, precond
+from paper_1808_06381_amd import sim as S
+
+pytestmark = pytest.mark.gpu
+WEIGHTS = os.path.join(os.path.dirname(precond.__file__), "weights", "precond_n1e5.bin")
+
+
+def both(cfgs, steps=3, tol=1e-10, **kw):
+    pos = np.concatenate([inputs.uniform_positions(c["n"], c["box"], 50 + r)
+                          for r, c in enumerate(cfgs)])
+    out = []
+    for probe in (0, 1):
+        with S.Sim(cfgs, pos, tol=tol, **kw) as sim:
+            if kw.get("precond") == "learned":
+                sim.load_precond(WEIGHTS)
+            sim.profile_enable(probe)   # 1: every step by the separate kernels
+            its = [tuple(sim.step(1)["iters"]) for _ in range(steps)]
+            out.append(sim.state()[:2] + (its,))
+    assert out[0][2] == out[1][2], (out[0][2], out[1][2])
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    return out[0]
+
+
+@pytest.mark.parametrize("n", [9, 255, 256, 257, 1023, 1024, 1025, 32768, 40000])
+@pytest.mark.parametrize("kw", [dict(), dict(precond="none"), dict(spmv_fp32=1),
+                                dict(precond="learned")], ids=lambda k: str(k))
+def test_single_box(n, kw):
+    both([inputs.cube_params(n, 0.4, seed=n)], **kw)
+
+
+def test_one_particle():
+    c = inputs.base_params(n=1, box=(5.0, 5.0, 5.0), shear_rate=0.3)
+    both([c])
+
+
+def test_the_largest_fused_handle_and_one_more():
+    for n in (128 * 1024, 128 * 1024 + 1):
+        both([inputs.cube_params(n, 0.2, seed=3)], steps=2, tol=1e-8)
+
+
+def test_long_rows_and_uneven_replicas():
+    cfgs = [dict(inputs.cube_params(n, 0.2 * (r + 1), seed=r, density=dens), stream=r)
+            for r, (n, dens) in enumerate([(300, 1.0), (5000, 12.0), (70, 2.0), (1500, 4.0)])]
+    for kw in (dict(), dict(precond="learned")):
+        both(cfgs, **kw)
+
+
+def test_wrapping_ring():
+    c = dict(inputs.cube_params(1300, 0.3, seed=4, density=2.0), gamma0=1e-4, alpha=4.0)
+    _, _, its = both([c])
+    assert max(map(max, its)) > 128
+    out = both([dict(c, stream=0), dict(inputs.cube_params(400, 0.1, seed=6), gamma0=20.0,
+                                        stream=1)])
+    assert max(map(max, out[2])) > 128
