@@ -16,22 +16,29 @@
 // work is FP64 arithmetic, not memory traffic (a particle's 24 bytes feed
 // nx * ny complex products).
 //
-// Layout.  k_sq_partial: a block of eight waves takes one tile of 64 mx x W
-// my values (W = the grid's my count rounded up to 16, at most 160) and one
-// chunk of one replica's rows.  Per group of 16 particles it first forms each
-// particle's sheared fractional coordinates and its two unit steps
-// exp(-2 pi i sx), exp(-2 pi i sy) (two sincospi per particle), then writes
-// the A and B tables to LDS in runs of 8 entries (a sincospi for the run's
-// first entry, complex multiplication by the particle's step for the
-// others), then the contraction runs on the matrix cores: FP64 16 x 16 x 4
-// MFMA, wave w owning mx rows 16(w mod 4).. and the 16-wide my tiles of
-// parity w / 4, four particles per step, Re += Ar Br - Ai Bi and
-// Im += Ar Bi + Ai Br as four real products.  One block covers every my
-// value of its mx rows (up to 160), so a particle's A table is built once,
-// not once per my tile; my tiles entirely past the grid are skipped.  The
-// vector units only generate the tables.  k_sq_reduce: per replica and q,
-// the chunks' partial sums in chunk order, then |rho|^2 / C.  No
-// floating-point atomics: the result is deterministic.
+// With the mz phase on A, A_c(mx) = exp(-2 pi i (mx sx + mz sz)), B(-my) is the
+// conjugate of B(my), so four real sums over the particles give a wavevector
+// and its mirror:
+//   P1 = sum Ar Br, P2 = sum Ai Bi, P3 = sum Ar Bi, P4 = sum Ai Br,
+//   rho(mx, my) = (P1 - P2) + i (P3 + P4),  rho(mx, -my) = (P1 + P2) + i (P4 - P3),
+// and my = 0 is the sum of A itself.
+//
+// Layout.  k_sq_partial: a block of sixteen waves takes one tile of 64 mx x 64
+// values of my >= 1 and one chunk of one replica's rows.  Per group of 32
+// particles the A and B tables go to LDS in runs of 8 entries (a sincospi for
+// the run's first entry, complex multiplication by the particle's unit step
+// for the others), then the contraction runs on the matrix cores: FP64 16 x 16
+// x 4 MFMA, one 16 x 16 tile of (mx, my) and its four sums per wave, four
+// particles per step.  Two table buffers: while all waves contract one group,
+// the halves of the block take turns to build the next one's tables first, so
+// that vector and matrix units work at the same time; a fixed wave prepares
+// the particles (coordinates and unit steps) two groups ahead, their positions
+// loaded three ahead.  The waves of the first my rows also sum A (my = 0).
+// Bound by the FP64 matrix rate: at N = 1e6 and 64 x 129 wavevectors 0.64 ms
+// (51 TFLOP/s of the 71 a large FP64 matrix product reaches; 1.42 ms with all
+// 129 my values contracted, one table buffer and eight waves).
+// k_sq_reduce: per replica and q, the chunks' partial sums in a fixed order,
+// then |rho|^2 / C.  No floating-point atomics: the result is deterministic.
 // Operand layout of v_mfma_f64_16x16x4f64 (checked on the device): lane l
 // supplies A[l%16][l/16] and B[l/16][l%16] and receives D[4r + l/16][l%16]
 // in accumulator register r.
@@ -46,15 +53,15 @@
 
 namespace {
 
-constexpr int SQ_THREADS = 512;
+constexpr int SQ_THREADS = 1024;
 constexpr int SQ_TX = 64;        // mx per tile
-constexpr int SQ_TT = 10;        // 16-wide my tiles per block at most
-constexpr int SQ_TYMAX = 16 * SQ_TT;
-constexpr int SQ_P = 16;         // particles per LDS group (a multiple of 4)
+constexpr int SQ_TY = 64;        // my >= 1 per block
+constexpr int SQ_TYMAX = 160;    // my columns of a tile of partial sums at most
+constexpr int SQ_P = 32;         // particles per LDS group (a multiple of 4)
 constexpr int SQ_RUN = 8;        // table entries per sincospi (complex recurrence)
-static_assert(SQ_TX == 16 * 4 && SQ_THREADS == 8 * 64 && SQ_TT <= 10,
-              "16 mx rows and up to five my tiles per wave");
-static_assert(SQ_TX % SQ_RUN == 0 && 16 % SQ_RUN == 0, "runs inside a tile");
+static_assert(SQ_TX == 16 * 4 && SQ_TY == 16 * 4 && SQ_THREADS == 16 * 64,
+              "one 16 x 16 tile of (mx, my) per wave");
+static_assert(SQ_P * (SQ_TX + SQ_TY) / SQ_RUN == SQ_THREADS / 2, "a half builds a group in one go");
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -73,149 +80,196 @@ __host__ __device__ __forceinline__ int sq_tile_w(int ny) {
   return w < SQ_TYMAX ? w : SQ_TYMAX;
 }
 
+// LDS of a block: two buffers of both tables (rows padded by one entry: the
+// table writes, 16 particles of one run per 16 lanes, and the MFMA operand
+// reads fall on distinct banks), and the prepared particles
+struct SqLds {
+  double2 A[2][SQ_P][SQ_TX + 1];
+  double2 B[2][SQ_P][SQ_TY + 1];
+  double2 stA[2][SQ_P], stB[2][SQ_P];  // unit steps exp(-2 pi i sx), exp(-2 pi i sy)
+  double fs[2][3][SQ_P];               // sx, sy, mz sz
+};
+
 // partial[(chunk * ntile + tile) * SQ_TX * tile_w + o] = sum over the chunk's
-// particles of A(mx) B(my), o = (mx - mx0) * tile_w + (my - my0); complex as
-// double2 (re, im)
+// particles of A(mx) B(my), o = (mx - mx0) * tile_w + column, tile and column
+// of my + my_max in tiles of tile_w columns (tiles_y per mx tile); complex as
+// double2 (re, im).  blockIdx.x: mx tile * blocks_y + block of my values.
 __global__ __launch_bounds__(SQ_THREADS) void k_sq_partial(DevPtrs d, const SqChunk* __restrict__ chunks,
-                                                           int nx, int my_max, int mz, int tiles_y,
-                                                           int tile_w, double2* __restrict__ partial) {
-  // rows padded by one entry: the table writes (16 particles of one run per
-  // 16 lanes) and the MFMA operand reads fall on distinct banks
-  __shared__ double2 A[SQ_P][SQ_TX + 1];
-  __shared__ double2 B[SQ_P][SQ_TYMAX + 1];
-  __shared__ double2 stA[SQ_P], stB[SQ_P];  // unit steps exp(-2 pi i sx), exp(-2 pi i sy)
-  __shared__ double fs[3][SQ_P];            // sx, sy, sz
-  const int tile = blockIdx.x, ci = blockIdx.y;
+                                                           int nx, int my_max, int mz, int blocks_y,
+                                                           int tiles_y, int tile_w, int ntile,
+                                                           double2* __restrict__ partial) {
+  extern __shared__ __align__(16) char sq_lds[];
+  SqLds& L = *reinterpret_cast<SqLds*>(sq_lds);
+  const int by = blockIdx.x % blocks_y, ci = blockIdx.y;
   const SqChunk ch = chunks[ci];
   const RepDev& R = d.rep[ch.rep];
-  const int mx0 = (tile / tiles_y) * SQ_TX;
-  const int my0 = -my_max + (tile % tiles_y) * tile_w;
-  const int ntt = tile_w / 16;
+  const int xt = blockIdx.x / blocks_y, mx0 = xt * SQ_TX;
+  const int my0 = 1 + by * SQ_TY;
   const double delta = le_offset(R, *d.step_d);
   const double ilx = 1.0 / R.L[0], ily = 1.0 / R.L[1], ilz = 1.0 / R.L[2];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave & 3, wh = wave >> 2;   // mx rows 16 wm.., my tiles tt = 2u + wh
+  const int wm = wave & 3, wn = wave >> 2;   // mx rows mx0 + 16 wm.., my values my0 + 16 wn..
   const int li = lane & 15, lk = lane >> 4;  // operand row / column, particle of the step
-  f64x4 re[5], im[5];
+  // the waves of a SIMD (wave mod 4) share wm: with few my values every SIMD
+  // keeps one busy wave
+  const bool busy = mx0 + 16 * wm < nx && my0 + 16 * wn <= my_max;
+  f64x4 acc[4];
 #pragma unroll
-  for (int u = 0; u < 5; ++u) {
-    re[u] = f64x4{0.0, 0.0, 0.0, 0.0};
-    im[u] = f64x4{0.0, 0.0, 0.0, 0.0};
-  }
-  const int runs_a = SQ_TX / SQ_RUN, runs = runs_a + tile_w / SQ_RUN;
-  // the particle step of a group (coordinates and unit steps, threads
-  // t < SQ_P) runs while the previous group is contracted, its positions
-  // loaded one group earlier still
-  auto particles = [&](int64_t g, const double4& r) {
-    if (t < SQ_P && g + t < ch.rows) {
-      const double sx = r.x * ilx - delta * r.y * (ilx * ily);
-      const double sy = r.y * ily;
-      fs[0][t] = sx;
-      fs[1][t] = sy;
-      fs[2][t] = r.z * ilz;
-      double ss, cs;
-      sincospi(2.0 * sx, &ss, &cs);
-      stA[t] = make_double2(cs, -ss);
-      sincospi(2.0 * sy, &ss, &cs);
-      stB[t] = make_double2(cs, -ss);
+  for (int u = 0; u < 4; ++u) acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // table building: a half's thread tb takes run tb / SQ_P of particle tb % SQ_P
+  const int half = t / (SQ_THREADS / 2), tb = t % (SQ_THREADS / 2);
+  const int bp = tb % SQ_P, brun = tb / SQ_P;
+  const bool isA = brun < SQ_TX / SQ_RUN;
+  const int k0 = (isA ? brun : brun - SQ_TX / SQ_RUN) * SQ_RUN;
+  const bool used = isA ? mx0 + k0 < nx : my0 + k0 <= my_max;
+  // my = 0: the waves of the first my rows also sum their A operands
+  const bool sums = by == 0 && wn == 0 && mx0 + 16 * wm < nx;
+  double s0r = 0.0, s0i = 0.0;
+  const int groups = (int)((ch.rows + SQ_P - 1) / SQ_P);
+  const bool prep = wave == 15 && lane < SQ_P;
+  auto load_pos = [&](int g) {
+    const int64_t i = (int64_t)g * SQ_P + lane;
+    return prep && i < ch.rows ? d.pos[ch.row0 + i] : make_double4(0.0, 0.0, 0.0, 0.0);
+  };
+  auto particles = [&](int g, const double4& r) {
+    if (!prep || g >= groups) return;
+    const int q = g & 1;
+    const double sx = r.x * ilx - delta * r.y * (ilx * ily);
+    const double sy = r.y * ily;
+    L.fs[q][0][lane] = sx;
+    L.fs[q][1][lane] = sy;
+    L.fs[q][2][lane] = (double)mz * (r.z * ilz);
+    double ss, cs;
+    sincospi(2.0 * sx, &ss, &cs);
+    L.stA[q][lane] = make_double2(cs, -ss);
+    sincospi(2.0 * sy, &ss, &cs);
+    L.stB[q][lane] = make_double2(cs, -ss);
+  };
+  // tables of group g: A[p][mx - mx0], B[p][my - my0], in runs of SQ_RUN
+  // consecutive entries: the first by sincospi, the others by complex
+  // multiplication with the unit step (error <= 2 (SQ_RUN - 1) ulp, against
+  // one sincospi per entry); rows past the chunk's particles are exact zeros
+  auto build = [&](int g) {
+    const int q = g & 1;
+    double2* dst = isA ? &L.A[q][bp][k0] : &L.B[q][bp][k0];
+    if ((int64_t)g * SQ_P + bp >= ch.rows || !used) {
+#pragma unroll
+      for (int j = 0; j < SQ_RUN; ++j) dst[j] = make_double2(0.0, 0.0);
+      return;
     }
-  };
-  auto load_pos = [&](int64_t g) {
-    return t < SQ_P && g + t < ch.rows ? d.pos[ch.row0 + g + t] : make_double4(0.0, 0.0, 0.0, 0.0);
-  };
-  particles(0, load_pos(0));
-  double4 rnext = load_pos(SQ_P);
-  __syncthreads();
-  for (int64_t g = 0; g < ch.rows; g += SQ_P) {
-    const int np = (int)min<int64_t>(SQ_P, ch.rows - g);
-    // phase tables of this group: A[p][mx - mx0], B[p][my - my0], in runs
-    // of SQ_RUN consecutive entries: the first by sincospi, the others by
-    // complex multiplication with the unit step (error <= 2 (SQ_RUN - 1)
-    // ulp, against one sincospi per entry)
-    for (int w = t; w < SQ_P * runs; w += SQ_THREADS) {
-      const int p = w % SQ_P, run = w / SQ_P;
-      const bool isA = run < runs_a;
-      const int k0 = (isA ? run : run - runs_a) * SQ_RUN;
-      double2* dst = isA ? &A[p][k0] : &B[p][k0];
-      if (p >= np) {  // rows past the group's particles: exact zeros
+    double s0, c0;
+    sincospi(isA ? 2.0 * ((double)(mx0 + k0) * L.fs[q][0][bp] + L.fs[q][2][bp])
+                 : 2.0 * ((double)(my0 + k0) * L.fs[q][1][bp]),
+             &s0, &c0);
+    double zr = c0, zi = -s0;  // exp(-i phase); step u
+    const double2 st = isA ? L.stA[q][bp] : L.stB[q][bp];
 #pragma unroll
-        for (int j = 0; j < SQ_RUN; ++j) dst[j] = make_double2(0.0, 0.0);
-        continue;
-      }
-      double s0, c0;
-      if (isA) sincospi(2.0 * (double)(mx0 + k0) * fs[0][p], &s0, &c0);
-      else sincospi(2.0 * ((double)(my0 + k0) * fs[1][p] + (double)mz * fs[2][p]), &s0, &c0);
-      // z = exp(-i phase) = (c, -s); step u
-      double zr = c0, zi = -s0;
-      const double2 st = isA ? stA[p] : stB[p];
-      const double ur = st.x, ui = st.y;
-      dst[0] = make_double2(zr, zi);
-#pragma unroll
-      for (int j = 1; j < SQ_RUN; ++j) {
-        const double nr = fma(zr, ur, -zi * ui);
-        const double ni = fma(zr, ui, zi * ur);
+    for (int j = 0; j < SQ_RUN; ++j) {
+      if (j > 0) {
+        const double nr = fma(zr, st.x, -zi * st.y);
+        const double ni = fma(zr, st.y, zi * st.x);
         zr = nr;
         zi = ni;
-        dst[j] = make_double2(zr, zi);
+      }
+      dst[j] = make_double2(zr, zi);
+    }
+  };
+  particles(0, load_pos(0));
+  particles(1, load_pos(1));
+  double4 rnext = load_pos(2);
+  __syncthreads();
+  if (half == 0) build(0);
+  __syncthreads();
+  for (int g = 0; g < groups; ++g) {
+    const int q = g & 1;
+    // the step buffer of group g is free (its tables are built): group g + 2's
+    particles(g + 2, rnext);
+    rnext = load_pos(g + 3);
+    if (half == ((g + 1) & 1) && g + 1 < groups) build(g + 1);
+    if (sums) {
+#pragma unroll
+      for (int p0 = 0; p0 < SQ_P; p0 += 4) {
+        const double2 a = L.A[q][p0 + lk][16 * wm + li];
+        s0r += a.x;
+        s0i += a.y;
       }
     }
-    __syncthreads();
-    // the next group's particle step (the tables of this one are built)
-    if (g + SQ_P < ch.rows) {
-      particles(g + SQ_P, rnext);
-      rnext = load_pos(g + 2 * SQ_P);
-    }
-    // the contraction over this group's particles, four per MFMA step
-    for (int p0 = 0; p0 < np; p0 += 4) {
-      const double2 a = A[p0 + lk][16 * wm + li];
-#pragma unroll
-      for (int u = 0; u < 5; ++u) {
-        const int tt = 2 * u + wh;
-        if (tt < ntt) {
-          const double2 b = B[p0 + lk][16 * tt + li];
-          re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[u], 0, 0, 0);
-          re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re[u], 0, 0, 0);
-          im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[u], 0, 0, 0);
-          im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im[u], 0, 0, 0);
-        }
+    if (busy) {
+#pragma unroll 2
+      for (int p0 = 0; p0 < SQ_P; p0 += 4) {
+        const double2 a = L.A[q][p0 + lk][16 * wm + li];
+        const double2 b = L.B[q][p0 + lk][16 * wn + li];
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, acc[3], 0, 0, 0);
       }
     }
-    __syncthreads();  // the tables are rewritten for the next group, whose
-                      // particle step is now visible
+    __syncthreads();  // group g + 1's tables and group g + 2's steps are visible,
+                      // group g's buffers free
   }
-  const int64_t base = ((int64_t)ci * gridDim.x + tile) * ((int64_t)SQ_TX * tile_w);
+  // the partial sum of (mx0 + row, my)
+  auto at = [&](int row, int my) -> double2& {
+    const int col = my + my_max;
+    return partial[((int64_t)ci * ntile + xt * tiles_y + col / tile_w) * ((int64_t)SQ_TX * tile_w) +
+                   (int64_t)row * tile_w + col % tile_w];
+  };
+  if (busy) {
+    const int my = my0 + 16 * wn + li;
+    if (my <= my_max) {
 #pragma unroll
-  for (int u = 0; u < 5; ++u) {
-    const int tt = 2 * u + wh;
-    if (tt >= ntt) continue;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      partial[base + (16 * wm + 4 * r + lk) * tile_w + 16 * tt + li] =
-          make_double2(re[u][r], im[u][r]);
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * wm + 4 * r + lk;
+        at(row, my) = make_double2(acc[0][r] - acc[1][r], acc[2][r] + acc[3][r]);
+        at(row, -my) = make_double2(acc[0][r] + acc[1][r], acc[3][r] - acc[2][r]);
+      }
+    }
   }
-  (void)nx;
+  if (sums) {  // over the four particle slots of a step
+    s0r += __shfl_xor(s0r, 16, 64);
+    s0i += __shfl_xor(s0i, 16, 64);
+    s0r += __shfl_xor(s0r, 32, 64);
+    s0i += __shfl_xor(s0i, 32, 64);
+    if (lk == 0) at(16 * wm + li, 0) = make_double2(s0r, s0i);
+  }
 }
 
 // out[(rep * nx + mx) * ny + (my + my_max)] = |sum of the replica's chunk
-// partials in chunk order|^2 / C
+// partials|^2 / C: slice s of SQ_SLICES adds chunks s, s + SQ_SLICES, .. in
+// order, then the slices in order (one thread per output walking all chunks
+// of N = 1e6 took 73 us: 33 blocks of dependent loads)
+constexpr int SQ_SLICES = 8;
+constexpr int SQ_OUTS = 256 / SQ_SLICES;
 __global__ __launch_bounds__(256) void k_sq_reduce(DevPtrs d, const int32_t* __restrict__ rep_chunk0,
                                                    int nrep, int nx, int my_max, int tiles_y,
                                                    int tile_w, int ntile,
                                                    const double2* __restrict__ partial,
                                                    double* __restrict__ out) {
+  __shared__ double2 part[SQ_SLICES][SQ_OUTS];
   const int ny = 2 * my_max + 1;
-  const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= (int64_t)nrep * nx * ny) return;
-  const int rep = (int)(o / ((int64_t)nx * ny));
-  const int q = (int)(o % ((int64_t)nx * ny));
-  const int mx = q / ny, myi = q % ny;
-  const int tile = (mx / SQ_TX) * tiles_y + myi / tile_w;
-  const int off = (mx % SQ_TX) * tile_w + myi % tile_w;
+  const int oi = threadIdx.x % SQ_OUTS, sl = threadIdx.x / SQ_OUTS;
+  const int64_t o = (int64_t)blockIdx.x * SQ_OUTS + oi;
+  const bool ok = o < (int64_t)nrep * nx * ny;
+  const int rep = ok ? (int)(o / ((int64_t)nx * ny)) : 0;
   double re = 0.0, im = 0.0;
-  for (int c = rep_chunk0[rep]; c < rep_chunk0[rep + 1]; ++c) {
-    const double2 v = partial[((int64_t)c * ntile + tile) * ((int64_t)SQ_TX * tile_w) + off];
-    re += v.x;
-    im += v.y;
+  if (ok) {
+    const int q = (int)(o % ((int64_t)nx * ny));
+    const int mx = q / ny, myi = q % ny;
+    const int tile = (mx / SQ_TX) * tiles_y + myi / tile_w;
+    const int off = (mx % SQ_TX) * tile_w + myi % tile_w;
+#pragma unroll 4
+    for (int c = rep_chunk0[rep] + sl; c < rep_chunk0[rep + 1]; c += SQ_SLICES) {
+      const double2 v = partial[((int64_t)c * ntile + tile) * ((int64_t)SQ_TX * tile_w) + off];
+      re += v.x;
+      im += v.y;
+    }
+  }
+  part[sl][oi] = make_double2(re, im);
+  __syncthreads();
+  if (sl != 0 || !ok) return;
+  for (int k = 1; k < SQ_SLICES; ++k) {
+    re += part[k][oi].x;
+    im += part[k][oi].y;
   }
   const int n = d.rep[rep].n;
   out[o] = n > 0 ? (re * re + im * im) / (double)n : 0.0;
@@ -261,6 +315,16 @@ __global__ void k_sq_chunks(DevPtrs d, SqChunk* __restrict__ chunks, int32_t* __
 }
 
 namespace {
+// blocks of my >= 1 values (one where there are none: my = 0 is its)
+int sq_blocks_y(int my_max) { return std::max(1, (my_max + SQ_TY - 1) / SQ_TY); }
+unsigned sq_blocks(int nx, int my_max) {
+  return (unsigned)((nx + SQ_TX - 1) / SQ_TX * sq_blocks_y(my_max));
+}
+// the contraction's tables take more LDS than a kernel gets unasked
+hipError_t allow_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(k_sq_partial),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SqLds));
+}
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 }
 
@@ -290,11 +354,16 @@ hipError_t launch_sq_scratch(const DevPtrs& d, int64_t nchunk, int nx, int my_ma
   const int tile_w = sq_tile_w(ny);
   const int tiles_y = (ny + tile_w - 1) / tile_w;
   const int ntile = (int)sq_tile_count(nx, my_max);
-  if (nchunk > 0)
-    hipLaunchKernelGGL(k_sq_partial, dim3(ntile, (unsigned)nchunk), dim3(SQ_THREADS), 0, s, d,
-                       (const SqChunk*)chunks, nx, my_max, mz, tiles_y, tile_w, partial);
+  if (nchunk > 0) {
+    const hipError_t e = allow_lds();
+    if (e) return e;
+    const int blocks_y = sq_blocks_y(my_max);
+    hipLaunchKernelGGL(k_sq_partial, dim3(sq_blocks(nx, my_max), (unsigned)nchunk),
+                       dim3(SQ_THREADS), sizeof(SqLds), s, d, (const SqChunk*)chunks, nx, my_max,
+                       mz, blocks_y, tiles_y, tile_w, ntile, partial);
+  }
   const int64_t nout = (int64_t)d.nrep * nx * ny;
-  hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, s, d, c0,
+  hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)((nout + SQ_OUTS - 1) / SQ_OUTS)), dim3(256), 0, s, d, c0,
                      d.nrep, nx, my_max, tiles_y, tile_w, ntile, partial, out_d);
   return hipGetLastError();
 }
@@ -327,16 +396,19 @@ hipError_t launch_sq(const DevPtrs& d, const std::vector<int64_t>& rep_row0,
   const int tiles_y = (ny + tile_w - 1) / tile_w;
   const int ntile = (int)sq_tile_count(nx, my_max);
   if (!ch.empty()) {
-    const dim3 g(ntile, (unsigned)ch.size()), b(SQ_THREADS);
+    if ((e = allow_lds())) return e;
+    const int blocks_y = sq_blocks_y(my_max);
+    const dim3 g(sq_blocks(nx, my_max), (unsigned)ch.size()), b(SQ_THREADS);
     if (ev0 || ev1)
-      hipExtLaunchKernelGGL(k_sq_partial, g, b, 0, s, ev0, ev1, 0, d, (const SqChunk*)chunks_d,
-                            nx, my_max, mz, tiles_y, tile_w, partial_d);
+      hipExtLaunchKernelGGL(k_sq_partial, g, b, sizeof(SqLds), s, ev0, ev1, 0, d,
+                            (const SqChunk*)chunks_d, nx, my_max, mz, blocks_y, tiles_y, tile_w,
+                            ntile, partial_d);
     else
-      hipLaunchKernelGGL(k_sq_partial, g, b, 0, s, d, (const SqChunk*)chunks_d, nx, my_max, mz,
-                         tiles_y, tile_w, partial_d);
+      hipLaunchKernelGGL(k_sq_partial, g, b, sizeof(SqLds), s, d, (const SqChunk*)chunks_d, nx,
+                         my_max, mz, blocks_y, tiles_y, tile_w, ntile, partial_d);
   }
   const int64_t nout = (int64_t)rep_rows.size() * nx * ny;
-  hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, s, d,
+  hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)((nout + SQ_OUTS - 1) / SQ_OUTS)), dim3(256), 0, s, d,
                      rep_chunk0_d, (int)rep_rows.size(), nx, my_max, tiles_y, tile_w, ntile,
                      partial_d, out_d);
   // host tables must outlive the asynchronous copies
