@@ -11,6 +11,8 @@
 #define MP_THREADS 256 // threads per block (8 nodes x 32 features)
 #define MP_ROWS 64     // rows per block
 #define MP_MSG 0.125f  // message scale
+#define MP_BW_BLOCKS 4096 // blocks of a layer's backward kernels at most
+#define MP_GSLICES 32     // slices of the parameter gradient's sum over blocks
 #define MP_EPS_LAM 0.3 // default floor of the diagonal head lam
 
 #define MP_OFF_W0 0
@@ -48,6 +50,7 @@ struct MpPtrs {
   float* av;       // Adam second moment
   float* grad;     // gradient of the last training step
   float* gpart;    // [blocks][MP_NPARAMS_ALL] partial gradients
+  double* gsum;    // [MP_GSLICES][MP_NPARAMS_ALL] their sums over slices of the blocks
   float* x;        // [rows][3] node features
   float* ef;       // [nnz][3] edge features
   float* er;       // [nnz] r_ij / rc (written by the pair-terms kernel)

@@ -808,33 +808,90 @@ __device__ __forceinline__ void slot_reduce_store(float v, float* lds, float* ds
   __syncthreads();
 }
 
-// row-k accumulators acc[0..31] of a 32 x 32 matrix, summed over node slots
-__device__ __forceinline__ void slot_reduce_matrix(const float (&acc)[MP_H], float* lds, float* dst) {
-  const int slot = threadIdx.x / MP_H, k = threadIdx.x % MP_H;
-  for (int q = 0; q < MP_H; ++q) lds[(slot * MP_H + k) * MP_H + q] = acc[q];
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < MP_H * MP_H; idx += blockDim.x) {
-    float s = 0.0f;
-    for (int sl = 0; sl < NODES; ++sl) s += lds[sl * MP_H * MP_H + idx];
-    dst[idx] = s;
-  }
-  __syncthreads();
+// FP32 matrix products of the backward pass (32 x 32 x 2 MFMA, FP32 operands
+// and accumulation).  Operand layout: lane l supplies A[l%32][l/32] and
+// B[l/32][l%32] and receives D[8(r/4) + 4(l/32) + r%4][l%32] in register r.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int BW_S = MP_H + 1;   // row stride (float) of a [rows][H] tile in LDS
+
+__device__ __forceinline__ int bw_row(int r) {
+  return 8 * (r >> 2) + 4 * ((threadIdx.x & 63) >> 5) + (r & 3);
 }
 
-// heads: dL/dh^3 (into dh) and the head parameters v, v0, z, ze, z0
+// acc[k][q] += sum over the tile's MP_ROWS rows of x[row][k] z[row][q]
+__device__ __forceinline__ void bw_outer(const float* x, const float* z, f32x16& acc) {
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+#pragma unroll 8
+  for (int r = 0; r < MP_ROWS; r += 2)
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[(r + hi) * BW_S + lo], z[(r + hi) * BW_S + lo],
+                                               acc, 0, 0, 0);
+}
+
+// out[row][k] = sum_q x[row][q] W[q][k] for the 32 rows from `row0` (W row-major)
+__device__ __forceinline__ f32x16 bw_rows(const float* x, int row0, const float* W) {
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll 8
+  for (int q = 0; q < MP_H; q += 2)
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[(row0 + lo) * BW_S + q + hi],
+                                               W[(q + hi) * MP_H + lo], acc, 0, 0, 0);
+  return acc;
+}
+
+__device__ __forceinline__ void bw_store_matrix(const f32x16& acc, float* dst) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) dst[bw_row(r) * MP_H + (threadIdx.x & 31)] = acc[r];
+}
+
+// Blocks of the layers' backward kernels: each walks a share of the tiles of
+// one XCD's contiguous eighth (the gathered rows stay in that XCD's L2) and
+// leaves one set of partial sums.
+static inline unsigned bw_blocks(int64_t ntiles) {
+  const int64_t n8 = (ntiles + 7) / 8, per = (8 * n8 + MP_BW_BLOCKS - 1) / MP_BW_BLOCKS;
+  return (unsigned)(8 * ((n8 + per - 1) / per));
+}
+struct BwTiles {
+  int tile, end, step;
+  __device__ explicit BwTiles(int ntiles) {
+    const int n8 = (ntiles + 7) >> 3, x = blockIdx.x & 7;
+    tile = x * n8 + (blockIdx.x >> 3);
+    end = min((x + 1) * n8, ntiles);
+    step = gridDim.x >> 3;
+  }
+};
+
+// heads: dL/dh^3 (into dh) and the head parameters v, v0, z, ze, z0.  The
+// FP64 work of an entry (dL/dS of it and of its reverse) is done once, by one
+// thread, into LDS, HB_E entries at a time; then half a wave per row walks
+// its entries with a feature per lane (all 32 lanes forming the entry's FP64
+// terms took 190 us at 1e5 rows; 100 us now).
+constexpr int HB_E = 1024;
 __global__ __launch_bounds__(MP_THREADS) void k_mp_heads_bwd(DevPtrs d, MpPtrs m) {
   if (d.ctrl->overflow) return;  // row pointers may exceed the capacity
-  __shared__ float hv[MP_H + 1], hz[MP_H], hze[MP_FE + 1];
-  __shared__ float red[NODES * MP_H * MP_H];
+  __shared__ float hv[MP_H + 1], hz[MP_H];
+  __shared__ float red[NODES * MP_H];
+  __shared__ int rp[MP_ROWS + 1];
+  __shared__ uint8_t erow[HB_E];
+  __shared__ float2 dts[HB_E];   // dL/dS of the entry, and that plus the reverse's
+  __shared__ int scol[HB_E];     // its column
+  static_assert(MP_ROWS <= 256, "rows fit the table's bytes");
+  const int t = threadIdx.x, slot = t / MP_H, k = t % MP_H;
+  const int ntiles = (int)(m.rows / MP_ROWS);
+  const int tile = xcd_block(blockIdx.x, ntiles);   // XCD-contiguous tiles
+  if (tile >= ntiles) return;
+  const int64_t i0 = (int64_t)tile * MP_ROWS;
   load_w(m, hv, MP_OFF_HEAD + MP_H_V, MP_H + 1);
   load_w(m, hz, MP_OFF_HEAD + MP_H_Z, MP_H);
-  load_w(m, hze, MP_OFF_HEAD + MP_H_ZE, MP_FE + 1);
+  if (t <= MP_ROWS) rp[t] = d.rowptr[i0 + t];
   __syncthreads();
-  const int slot = threadIdx.x / MP_H, k = threadIdx.x % MP_H;
   const float* __restrict__ hf = m.h + (int64_t)MP_NL * m.rows * MP_H;
-  float g_v = 0.0f, g_v0 = 0.0f, g_z = 0.0f, g_z0 = 0.0f, g_ze[MP_FE] = {0.0f, 0.0f, 0.0f};
+  float g_v = 0.0f, g_v0 = 0.0f, g_z = 0.0f, g_e = 0.0f;  // g_e: lanes 0..2 ze, lane 3 z0
+  float dh[PASSES], hk[PASSES];
+#pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
-    const int64_t i = (int64_t)blockIdx.x * MP_ROWS + pass * NODES + slot;
+    const int64_t i = i0 + pass * NODES + slot;
     const double di = d.diag[i];
     double gd = 0.0;
 #pragma unroll
@@ -842,13 +899,23 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_heads_bwd(DevPtrs d, MpPtrs m
     const double gl = gd / di;  // dL/dlam_i (mdiag = lam / D)
     const float tau = m.tau[i];
     const float gt = (float)gl * sigmoidf_(tau);
-    const float hk = act_in(m, hf[i * MP_H + k]);
-    float dh = gt * hv[k];
-    g_v += gt * hk;
+    hk[pass] = act_in(m, hf[i * MP_H + k]);
+    dh[pass] = gt * hv[k];
+    g_v += gt * hk[pass];
     if (k == 0) g_v0 += gt;
-    for (int e = d.rowptr[i]; e < d.rowptr[i + 1]; ++e) {
-      const int64_t j = d.col[e];
-      const double sq = sqrt(di * d.diag[j]);
+  }
+  const int E0 = rp[0], E1 = rp[MP_ROWS];
+  for (int cb = E0; cb < E1; cb += HB_E) {
+    const int ce = min(E1, cb + HB_E);
+    {
+      const int n = t >> 2;   // four threads per row
+      for (int e = max(rp[n], cb) + (t & 3); e < min(rp[n + 1], ce); e += 4)
+        erow[e - cb] = (uint8_t)n;
+    }
+    __syncthreads();
+    for (int e = cb + t; e < ce; e += MP_THREADS) {
+      const int64_t i = i0 + erow[e - cb], j = d.col[e];
+      const double sq = sqrt(d.diag[i] * d.diag[j]);
       double gm = 0.0, gmr = 0.0;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -856,131 +923,196 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_heads_bwd(DevPtrs d, MpPtrs m
         gmr += m.G[3 * j + c] * d.b[3 * i + c];   // the reverse entry (j -> i)
       }
       // moff = S / sqrt(D_i D_j): dL/dS of this entry and of its reverse
-      const float dt_own = (float)(gm / sq);
-      const float dt_rev = (float)(gmr / sq);
-      const float hj = act_in(m, hf[j * MP_H + k]);
-      dh += (dt_own + dt_rev) * hz[k] * hj;
-      g_z += dt_own * (hk * hj);
-      if (k == 0) {
-        g_z0 += dt_own;
+      const float own = (float)(gm / sq), rev = (float)(gmr / sq);
+      dts[e - cb] = make_float2(own, own + rev);
+      scol[e - cb] = (int)j;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int f = 0; f < MP_FE; ++f) g_ze[f] += dt_own * act_in(m, m.ef[3 * (int64_t)e + f]);
+    for (int pass = 0; pass < PASSES; ++pass) {
+      const int r = pass * NODES + slot;
+      const int lo = max(rp[r], cb), hi = min(rp[r + 1], ce);
+#pragma unroll 4
+      for (int e = lo; e < hi; ++e) {
+        const float hj = act_in(m, hf[(int64_t)scol[e - cb] * MP_H + k]);
+        const float2 dt = dts[e - cb];
+        dh[pass] += dt.y * hz[k] * hj;
+        g_z += dt.x * (hk[pass] * hj);
+        if (k < MP_FE) g_e += dt.x * act_in(m, m.ef[3 * (int64_t)e + k]);
+        else if (k == MP_FE) g_e += dt.x;
       }
     }
-    m.dh[i * MP_H + k] = dh;
+    __syncthreads();
   }
-  float* dst = m.gpart + (int64_t)blockIdx.x * MP_NPARAMS_ALL + MP_OFF_HEAD;
+#pragma unroll
+  for (int pass = 0; pass < PASSES; ++pass)
+    m.dh[(i0 + pass * NODES + slot) * MP_H + k] = dh[pass];
+  float* dst = m.gpart + (int64_t)tile * MP_NPARAMS_ALL + MP_OFF_HEAD;
   slot_reduce_store(g_v, red, dst + MP_H_V);
   slot_reduce_store(g_z, red, dst + MP_H_Z);
-  // scalar terms live in lane 0 of each slot
-  float sc[2 + MP_FE] = {g_v0, g_z0, g_ze[0], g_ze[1], g_ze[2]};
-  for (int q = 0; q < 2 + MP_FE; ++q) {
-    red[threadIdx.x] = sc[q];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float s = 0.0f;
-      for (int sl = 0; sl < NODES; ++sl) s += red[sl * MP_H];
-      const int off = q == 0 ? MP_H_V0 : (q == 1 ? MP_H_Z0 : MP_H_ZE + (q - 2));
-      dst[off] = s;
-    }
-    __syncthreads();
+  red[t] = g_e;
+  __syncthreads();
+  if (t <= MP_FE) {
+    float s = 0.0f;
+    for (int sl = 0; sl < NODES; ++sl) s += red[sl * MP_H + t];
+    dst[t < MP_FE ? MP_H_ZE + t : MP_H_Z0] = s;
+  }
+  __syncthreads();
+  red[t] = g_v0;
+  __syncthreads();
+  if (t == 0) {
+    float s = 0.0f;
+    for (int sl = 0; sl < NODES; ++sl) s += red[sl * MP_H];
+    dst[MP_H_V0] = s;
   }
 }
 
 // layer l backward, part A (per node i): da = dh * [a > 0];
-// dU, dV, dd; dh_in = dh + U^T da; dm = V^T da
+// dU, dV, dd; dh_in = dh + U^T da; dm = V^T da.  A block walks its tiles of 64
+// rows: the tile's da, h and m go to LDS, then wave 0 adds da h^T to dU, wave 1
+// da m^T to dV, waves 2 and 3 form U^T da and V^T da, all as FP32 matrix
+// products; the accumulators stay in registers over the tiles.  (One lane per
+// feature walking 32 x 32 scalar products took 204 us at 1e5 rows; 50 us now)
 __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_a(DevPtrs d, MpPtrs m, int l) {
-  __shared__ float U[MP_H * MP_H], V[MP_H * MP_H];
-  __shared__ float sda[NODES][MP_H];
-  __shared__ float red[NODES * MP_H * MP_H];
+  __shared__ float UV[2][MP_H * MP_H];
+  __shared__ float sda[MP_ROWS * BW_S], shm[2][MP_ROWS * BW_S];
+  __shared__ float red[NODES * MP_H];
   const int base = MP_OFF_L0 + l * MP_L_SIZE;
-  load_w(m, U, base + MP_L_U, MP_H * MP_H);
-  load_w(m, V, base + MP_L_V, MP_H * MP_H);
-  __syncthreads();
-  const int slot = threadIdx.x / MP_H, k = threadIdx.x % MP_H;
+  load_w(m, UV[0], base + MP_L_U, MP_H * MP_H);
+  load_w(m, UV[1], base + MP_L_V, MP_H * MP_H);
+  const int slot = threadIdx.x / MP_H, k = threadIdx.x % MP_H, wave = threadIdx.x >> 6;
   const float* __restrict__ hin = m.h + (int64_t)l * m.rows * MP_H;
   const float* __restrict__ mm = m.m + (int64_t)l * m.rows * MP_H;
   const float* __restrict__ aa = m.a + (int64_t)l * m.rows * MP_H;
-  float accU[MP_H], accV[MP_H], accd = 0.0f;
+  f32x16 acc;
 #pragma unroll
-  for (int q = 0; q < MP_H; ++q) accU[q] = accV[q] = 0.0f;
-  for (int pass = 0; pass < PASSES; ++pass) {
-    const int64_t i = (int64_t)blockIdx.x * MP_ROWS + pass * NODES + slot;
-    const float dh = m.dh[i * MP_H + k];
-    const float da = aa[i * MP_H + k] > 0.0f ? dh : 0.0f;
-    accd += da;
-    for (int q = 0; q < MP_H; ++q) {
-      accU[q] += da * act_in(m, hin[i * MP_H + q]);
-      accV[q] += da * act_in(m, mm[i * MP_H + q]);
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  float accd = 0.0f;
+  for (BwTiles w((int)(m.rows / MP_ROWS)); w.tile < w.end; w.tile += w.step) {
+    const int64_t i0 = (int64_t)w.tile * MP_ROWS;
+#pragma unroll
+    for (int pass = 0; pass < PASSES; ++pass) {
+      const int row = pass * NODES + slot;
+      const int64_t o = (i0 + row) * MP_H + k;
+      const float da = aa[o] > 0.0f ? m.dh[o] : 0.0f;
+      accd += da;
+      sda[row * BW_S + k] = da;
+      shm[0][row * BW_S + k] = act_in(m, hin[o]);
+      shm[1][row * BW_S + k] = act_in(m, mm[o]);
     }
-    sda[slot][k] = da;
     __syncthreads();
-    float su = 0.0f, sv = 0.0f;
-#pragma unroll 8
-    for (int q = 0; q < MP_H; ++q) {
-      su += U[q * MP_H + k] * sda[slot][q];
-      sv += V[q * MP_H + k] * sda[slot][q];
+    if (wave < 2) {
+      bw_outer(sda, shm[wave], acc);
+    } else {
+#pragma unroll
+      for (int row0 = 0; row0 < MP_ROWS; row0 += 32) {
+        const f32x16 s = bw_rows(sda, row0, UV[wave - 2]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int64_t o = (i0 + row0 + bw_row(r)) * MP_H + k;
+          if (wave == 2) m.dh2[o] = m.dh[o] + s[r];
+          else m.dm[o] = s[r];
+        }
+      }
     }
-    m.dh2[i * MP_H + k] = dh + su;
-    m.dm[i * MP_H + k] = sv;
     __syncthreads();
   }
   float* dst = m.gpart + (int64_t)blockIdx.x * MP_NPARAMS_ALL + base;
-  slot_reduce_matrix(accU, red, dst + MP_L_U);
-  slot_reduce_matrix(accV, red, dst + MP_L_V);
+  if (wave == 0) bw_store_matrix(acc, dst + MP_L_U);
+  if (wave == 1) bw_store_matrix(acc, dst + MP_L_V);
   slot_reduce_store(accd, red, dst + MP_L_D);
 }
 
 // layer l backward, part B (per node j, pulling from its neighbours i):
-// dy_j = 1/8 sum_i dm_i [y_j + Q e_ij + c > 0]; dQ, dc, dP; dh_in_j += P^T dy_j
+// dy_j = 1/8 sum_i dm_i [y_j + Q e_ij + c > 0]; dQ, dc, dP; dh_in_j += P^T dy_j.
+// Half a wave per row walks its entries, a feature per lane, four gathers in
+// flight; the tile's dy and h go to LDS, then wave 0 adds dy h^T to dP and
+// waves 1 and 2 form P^T dy as FP32 matrix products (210 us at 1e5 rows with
+// scalar products, two barriers per eight rows and three dependent loads per
+// entry; 86 us now).
+constexpr int BB_E = 512;   // entries staged at a time
 __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_b(DevPtrs d, MpPtrs m, int l) {
   if (d.ctrl->overflow) return;  // row pointers may exceed the capacity
   __shared__ float P[MP_H * MP_H], Q[MP_H * MP_FE], c[MP_H];
-  __shared__ float sdy[NODES][MP_H];
-  __shared__ float red[NODES * MP_H * MP_H];
+  __shared__ float sdy[MP_ROWS * BW_S], sh[MP_ROWS * BW_S];
+  __shared__ float red[NODES * MP_H];
+  __shared__ int rp[MP_ROWS + 1];
+  __shared__ float4 sef[BB_E];   // an entry's features and its column
   const int base = MP_OFF_L0 + l * MP_L_SIZE;
   load_w(m, P, base + MP_L_P, MP_H * MP_H);
   load_w(m, Q, base + MP_L_Q, MP_H * MP_FE);
   load_w(m, c, base + MP_L_C, MP_H);
   __syncthreads();
-  const int slot = threadIdx.x / MP_H, k = threadIdx.x % MP_H;
+  const int slot = threadIdx.x / MP_H, k = threadIdx.x % MP_H, wave = threadIdx.x >> 6;
   const float* __restrict__ hin = m.h + (int64_t)l * m.rows * MP_H;
   const float* __restrict__ y = m.y + (int64_t)l * m.rows * MP_H;
-  float accP[MP_H], accQ[MP_FE] = {0.0f, 0.0f, 0.0f}, accc = 0.0f;
+  const float q0 = Q[k * MP_FE], q1 = Q[k * MP_FE + 1], q2 = Q[k * MP_FE + 2], ck = c[k];
+  f32x16 acc;
 #pragma unroll
-  for (int q = 0; q < MP_H; ++q) accP[q] = 0.0f;
-  for (int pass = 0; pass < PASSES; ++pass) {
-    const int64_t j = (int64_t)blockIdx.x * MP_ROWS + pass * NODES + slot;
-    const float yj = y[j * MP_H + k];
-    float dy = 0.0f;
-    for (int e = d.rowptr[j]; e < d.rowptr[j + 1]; ++e) {
-      const int64_t i = d.col[e];
-      float s = yj + c[k];
-      float ef[MP_FE];
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  float accQ[MP_FE] = {0.0f, 0.0f, 0.0f}, accc = 0.0f;
+  for (BwTiles w((int)(m.rows / MP_ROWS)); w.tile < w.end; w.tile += w.step) {
+    const int64_t i0 = (int64_t)w.tile * MP_ROWS;
+    if (threadIdx.x <= MP_ROWS) rp[threadIdx.x] = d.rowptr[i0 + threadIdx.x];
+    float dy[PASSES], yj[PASSES];
 #pragma unroll
-      for (int f = 0; f < MP_FE; ++f) {
-        ef[f] = act_in(m, m.ef[3 * (int64_t)e + f]);
-        s += Q[k * MP_FE + f] * ef[f];
+    for (int pass = 0; pass < PASSES; ++pass) {
+      dy[pass] = 0.0f;
+      yj[pass] = y[(i0 + pass * NODES + slot) * MP_H + k] + ck;
+    }
+    __syncthreads();
+    const int E0 = rp[0], E1 = rp[MP_ROWS];
+    for (int cb = E0; cb < E1; cb += BB_E) {
+      // the chunk's columns and features: one gather per entry is then the
+      // only load that a row's walk waits for
+      const int ce = min(E1, cb + BB_E);
+      for (int e = cb + threadIdx.x; e < ce; e += MP_THREADS) {
+        const float* efp = m.ef + 3 * (int64_t)e;
+        sef[e - cb] = make_float4(act_in(m, efp[0]), act_in(m, efp[1]), act_in(m, efp[2]),
+                                  __int_as_float(d.col[e]));
       }
-      if (s > 0.0f) {
-        const float ds = MP_MSG * m.dm[i * MP_H + k];
-        dy += ds;
-        accc += ds;
+      __syncthreads();
 #pragma unroll
-        for (int f = 0; f < MP_FE; ++f) accQ[f] += ds * ef[f];
+      for (int pass = 0; pass < PASSES; ++pass) {
+        const int row = pass * NODES + slot;
+        const int lo = max(rp[row], cb), hi = min(rp[row + 1], ce);
+#pragma unroll 4
+        for (int e = lo; e < hi; ++e) {
+          const float4 f = sef[e - cb];
+          const float s = ((yj[pass] + q0 * f.x) + q1 * f.y) + q2 * f.z;
+          const float dmi = m.dm[(int64_t)__float_as_int(f.w) * MP_H + k];
+          const float ds = s > 0.0f ? MP_MSG * dmi : 0.0f;
+          dy[pass] += ds;
+          accc += ds;
+          accQ[0] += ds * f.x;
+          accQ[1] += ds * f.y;
+          accQ[2] += ds * f.z;
+        }
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int pass = 0; pass < PASSES; ++pass) {
+      const int row = pass * NODES + slot;
+      sdy[row * BW_S + k] = dy[pass];
+      sh[row * BW_S + k] = act_in(m, hin[(i0 + row) * MP_H + k]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      bw_outer(sdy, sh, acc);
+    } else if (wave <= MP_ROWS / 32) {
+      const int row0 = 32 * (wave - 1);
+      const f32x16 s = bw_rows(sdy, row0, P);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t o = (i0 + row0 + bw_row(r)) * MP_H + k;
+        m.dh[o] = m.dh2[o] + s[r];  // dL/dh^l for the next part A
       }
     }
-    for (int q = 0; q < MP_H; ++q) accP[q] += dy * act_in(m, hin[j * MP_H + q]);
-    sdy[slot][k] = dy;
-    __syncthreads();
-    float sp = 0.0f;
-#pragma unroll 8
-    for (int q = 0; q < MP_H; ++q) sp += P[q * MP_H + k] * sdy[slot][q];
-    m.dh[j * MP_H + k] = m.dh2[j * MP_H + k] + sp;  // dL/dh^l for the next part A
     __syncthreads();
   }
   float* dst = m.gpart + (int64_t)blockIdx.x * MP_NPARAMS_ALL + base;
-  slot_reduce_matrix(accP, red, dst + MP_L_P);
+  if (wave == 0) bw_store_matrix(acc, dst + MP_L_P);
   slot_reduce_store(accc, red, dst + MP_L_C);
   for (int f = 0; f < MP_FE; ++f) {
     red[threadIdx.x] = accQ[f];
@@ -1033,9 +1165,23 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_encode_bwd(DevPtrs d, MpPtrs 
   }
 }
 
-// grad[p] = (1/den) sum_b gpart[b][p], blocks in order (zero beyond the
-// parameters this handle trains)
-__global__ __launch_bounds__(256) void k_mp_grad_reduce(MpPtrs m, int nblk) {
+// gsum[g][p] = sum of gpart[b][p] over the blocks b = g, g + MP_GSLICES, ..
+// that hold parameter p (`layers` blocks for the layers' parameters, `tiles`
+// for the others), in order
+__global__ __launch_bounds__(256) void k_mp_grad_part(MpPtrs m, int tiles, int layers) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= m.nparams) return;
+  const int nblk = p >= MP_OFF_L0 && p < MP_OFF_HEAD ? layers : tiles;
+  double s = 0.0;
+#pragma unroll 4
+  for (int b = blockIdx.y; b < nblk; b += MP_GSLICES) s += m.gpart[(int64_t)b * MP_NPARAMS_ALL + p];
+  m.gsum[(int64_t)blockIdx.y * MP_NPARAMS_ALL + p] = s;
+}
+
+// grad[p] = (1/den) sum_g gsum[g][p], in order (zero beyond the parameters
+// this handle trains).  One thread per parameter walking every block's
+// partial took 604 us at 1600 blocks; both kernels take under 20 us.
+__global__ __launch_bounds__(256) void k_mp_grad_reduce(MpPtrs m) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= MP_NPARAMS_ALL) return;
   if (p >= m.nparams) {
@@ -1043,7 +1189,8 @@ __global__ __launch_bounds__(256) void k_mp_grad_reduce(MpPtrs m, int nblk) {
     return;
   }
   double s = 0.0;
-  for (int b = 0; b < nblk; ++b) s += m.gpart[(int64_t)b * MP_NPARAMS_ALL + p];
+#pragma unroll
+  for (int g = 0; g < MP_GSLICES; ++g) s += m.gsum[(int64_t)g * MP_NPARAMS_ALL + p];
   m.grad[p] = (float)(s * m.loss[1]);
 }
 
@@ -1610,19 +1757,22 @@ hipError_t launch_mp_loss(const DevPtrs& d, const MpPtrs& m, hipStream_t s) {
 // parameter gradient
 static hipError_t launch_mp_trunk_backward(const DevPtrs& d, const MpPtrs& m, hipStream_t s) {
   const unsigned blocks = (unsigned)(d.rows / MP_ROWS);
+  const unsigned lb = bw_blocks(blocks);
   for (int l = MP_NL - 1; l >= 0; --l) {
-    hipLaunchKernelGGL(k_mp_layer_bwd_a, dim3(blocks), dim3(MP_THREADS), 0, s, d, m, l);
-    hipLaunchKernelGGL(k_mp_layer_bwd_b, dim3(blocks), dim3(MP_THREADS), 0, s, d, m, l);
+    hipLaunchKernelGGL(k_mp_layer_bwd_a, dim3(lb), dim3(MP_THREADS), 0, s, d, m, l);
+    hipLaunchKernelGGL(k_mp_layer_bwd_b, dim3(lb), dim3(MP_THREADS), 0, s, d, m, l);
   }
   hipLaunchKernelGGL(k_mp_encode_bwd, dim3(blocks), dim3(MP_THREADS), 0, s, d, m);
-  hipLaunchKernelGGL(k_mp_grad_reduce, dim3(nb(MP_NPARAMS_ALL, 256)), dim3(256), 0, s, m,
-                     (int)blocks);
+  hipLaunchKernelGGL(k_mp_grad_part, dim3(nb(MP_NPARAMS_ALL, 256), MP_GSLICES), dim3(256), 0, s, m,
+                     (int)blocks, (int)lb);
+  hipLaunchKernelGGL(k_mp_grad_reduce, dim3(nb(MP_NPARAMS_ALL, 256)), dim3(256), 0, s, m);
   return hipGetLastError();
 }
 
 hipError_t launch_mp_backward(const DevPtrs& d, const MpPtrs& m, hipStream_t s) {
   const unsigned blocks = (unsigned)(d.rows / MP_ROWS);
-  hipLaunchKernelGGL(k_mp_heads_bwd, dim3(blocks), dim3(MP_THREADS), 0, s, d, m);
+  hipLaunchKernelGGL(k_mp_heads_bwd, dim3((unsigned)xcd_grid((int)blocks)), dim3(MP_THREADS), 0, s, d,
+                     m);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_mp_trunk_backward(d, m, s);

@@ -380,6 +380,7 @@ static int ensure_mp(sim_t* s, bool training) {
     MPALLOC(m.dh2, sizeof(float) * rows * H);
     MPALLOC(m.dm, sizeof(float) * rows * H);
     MPALLOC(m.gpart, sizeof(float) * (rows / MP_ROWS) * MP_NPARAMS_ALL);
+    MPALLOC(m.gsum, sizeof(double) * MP_GSLICES * MP_NPARAMS_ALL);
     MPALLOC(m.pz, sizeof(double) * 3 * rows);
     MPALLOC(m.pb, sizeof(double) * 3 * rows);
     if (s->block) {  // R G, A_ii^-1 G, R b, A_ii^-1 b
