@@ -2236,7 +2236,7 @@ int sim_velocity_correlation(sim_t* s, double r_max, int32_t nbins, int32_t flow
   const size_t nch = chunks.size();
   const size_t o_blk = take2(sizeof(VvBlock) * blk.size());
   const size_t o_psum = take2(sizeof(long long) * blk.size() * nbins);
-  const size_t o_pcnt = take2(sizeof(unsigned long long) * blk.size() * nbins);
+  const size_t o_pcnt = take2(sizeof(unsigned int) * blk.size() * nbins);
   const size_t o_ch = take2(sizeof(int2) * nch);
   const size_t o_flo = take2(sizeof(unsigned long long) * nch * nbins);
   const size_t o_fhi = take2(sizeof(long long) * nch * nbins);
@@ -2260,7 +2260,7 @@ int sim_velocity_correlation(sim_t* s, double r_max, int32_t nbins, int32_t flow
     HIPCHK(hipEventCreateWithFlags(&e1, hipEventDisableSystemFence));
   }
   long long* psum_d = (long long*)(base2 + o_psum);
-  unsigned long long* pcnt_d = (unsigned long long*)(base2 + o_pcnt);
+  unsigned int* pcnt_d = (unsigned int*)(base2 + o_pcnt);
   hipError_t err = launch_vv_pairs(s->d, vr_d, blk_d, (int)blk.size(), cstart_d, spos_d, su_d,
                                    umax_d, nbins, psum_d, pcnt_d, st, e0, e1);
   if (!err)

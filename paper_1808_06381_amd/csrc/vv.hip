@@ -54,18 +54,24 @@ constexpr int VV_HOME = 64;       // home particles (threads, one wave) per bloc
 constexpr int VV_STAGE = 64;      // candidates staged in LDS at a time (4 KB: a one-wave
                                   // block with 256 staged, 16 KB, left two waves per SIMD)
 constexpr int VV_THREADS = 1024;  // threads of the binning kernels
-constexpr int VV_FOLD = 256;      // table blocks folded per first-stage reduce block
+constexpr int VV_FOLD = 64;       // table blocks folded per first-stage reduce block
 
 }  // namespace
 
 // bin of t >= 0: the largest k with k^2 <= t, capped at nb - 1
-// (t < nb^2 (1 + eps) <= 2^20 (1 + eps) for an accepted pair, so the
-// single-precision root is within one of the answer: one correction each way)
+// (t < nb^2 (1 + eps) <= 2^20 (1 + eps) for an accepted pair: the rounding of t
+// to single precision and the hardware root's one ulp leave at most 1.9e-4 of
+// error, so only a root within 2^-11 of an integer needs the exact comparison;
+// k^2 and (k + 1)^2 are exact in FP64)
 __device__ __forceinline__ int vv_bin(double t, int nb) {
-  int k = (int)sqrtf((float)t);
-  k += ((double)(k + 1) * (double)(k + 1) <= t) ? 1 : 0;
-  k -= ((double)k * (double)k > t) ? 1 : 0;
-  return k < nb - 1 ? k : nb - 1;
+  const float f = __builtin_amdgcn_sqrtf((float)t);
+  int k = (int)f;
+  if (fabsf(__builtin_amdgcn_fractf(f) - 0.5f) > 0.5f - 0x1p-11f) {
+    k += ((double)(k + 1) * (double)(k + 1) <= t) ? 1 : 0;
+    k -= ((double)k * (double)k > t) ? 1 : 0;
+    k = k < nb - 1 ? k : nb - 1;  // f can reach nb only within the rounding
+  }
+  return k;
 }
 
 // fixed-point scale exponent of a replica: 61 - log2p - E with |u|^2 < 2^E
@@ -157,16 +163,29 @@ __global__ __launch_bounds__(VV_THREADS) void k_vv_scatter(DevPtrs d, int flow,
   }
 }
 
+// The product in fixed point, rint(p * scale) (scale a power of two).  ADD:
+// |p * scale| < 2^50 (a replica of 32 or more particles), and the sum with
+// 1.5 * 2^52 rounds to that integer in its low bits; the FP64 bits themselves
+// are added up (mod 2^64), and the constant's, once per pair, are taken off
+// the block's totals at the end.  (The conversion to a 64-bit integer is a
+// dozen instructions.)
+constexpr double VV_MAGIC = 6755399441055744.0;
+template <bool ADD>
+__device__ __forceinline__ unsigned long long vv_fixed(double p, double scale) {
+  if constexpr (ADD) return (unsigned long long)__double_as_longlong(__fma_rn(p, scale, VV_MAGIC));
+  else return (unsigned long long)(long long)rint(p * scale);
+}
+
 // one accepted pair: its bin, and the fixed-point product added to the
 // block's histogram (integer LDS atomics: order-independent)
+template <bool ADD>
 __device__ __forceinline__ void vv_accept(double r2, const double4& hu, const double4& w,
                                           double cscale, double scale, int nb,
                                           unsigned long long* hs, unsigned int* hc) {
   const int k = vv_bin(__dmul_rn(r2, cscale), nb);
   const double p = __dadd_rn(__dadd_rn(__dmul_rn(hu.x, w.x), __dmul_rn(hu.y, w.y)),
                              __dmul_rn(hu.z, w.z));
-  const long long qv = (long long)rint(p * scale);
-  atomicAdd(&hs[k], (unsigned long long)qv);
+  atomicAdd(&hs[k], vv_fixed<ADD>(p, scale));
   atomicAdd(&hc[k], 1u);
 }
 
@@ -179,30 +198,16 @@ __device__ __forceinline__ void vv_accept(double r2, const double4& hu, const do
 // where the two disagree -- |d| exactly L/2 -- only the sign differs), and
 // r^2 is the same bits.  Rows across the y boundary and one-cell axes use
 // the full per-pair separation.
-__global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __restrict__ vr,
-                                                      const VvBlock* __restrict__ blocks, int nblk,
-                                                      const int32_t* __restrict__ cstart,
-                                                      const double4* __restrict__ spos,
-                                                      const double4* __restrict__ su,
-                                                      const unsigned long long* __restrict__ umax,
-                                                      int nb, long long* __restrict__ psum,
-                                                      unsigned long long* __restrict__ pcnt) {
-  extern __shared__ unsigned long long vv_hist[];  // [nb] sums, then [nb] 32-bit counts
-  __shared__ double4 cp[VV_STAGE], cu[VV_STAGE];
-  const int b = xcd_block(blockIdx.x, nblk);
-  if (b >= nblk) return;
-  const VvBlock B = blocks[b];
+template <bool ADD>
+__device__ __forceinline__ void vv_pairs_block(const DevPtrs& d, const VvRep& V, const VvBlock& B,
+                                               const int32_t* __restrict__ cstart,
+                                               const double4* __restrict__ spos,
+                                               const double4* __restrict__ su, double scale,
+                                               int nb, unsigned long long* hs, unsigned int* hc,
+                                               double4* cp, double4* cu) {
   const RepDev& R = d.rep[B.rep];
-  const VvRep& V = vr[B.rep];
   const int t = threadIdx.x;
-  unsigned long long* hs = vv_hist;
-  unsigned int* hc = (unsigned int*)(vv_hist + nb);
-  for (int k = t; k < nb; k += VV_HOME) {
-    hs[k] = 0ull;
-    hc[k] = 0u;
-  }
   const double delta = le_offset(R, *d.step_d - 1);
-  const double scale = ldexp(1.0, vv_scale_exp(umax[B.rep], V.log2p));
   const double rmax2 = V.rmax2, cscale = V.cscale;
   // lanes: G = 64 / P groups of P = the home count lanes share the wave (the
   // lanes past the last whole group idle), group g testing candidates g,
@@ -223,7 +228,6 @@ __global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __
   const int M = V.M;
   const int zr = ncz == 1 ? 0 : M, yr = ncy == 1 ? 0 : M;
   const bool split = ncx > 1 && ncy > 1 && ncz > 1;
-  __syncthreads();
   for (int dz = -zr; dz <= zr; ++dz) {
     const double gz = fmax((double)(abs(dz) - 1) * V.len[2] - V.margin, 0.0);
     const int czu = cz + dz;
@@ -274,7 +278,17 @@ __global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __
             cu[q] = su[c0 + q];
           }
           __syncthreads();
-          if (home && fast) {
+          // candidates after the home particle: jj > thr
+          const int thr = (int)min<int64_t>(self - c0, VV_STAGE);
+          if (home && fast && (kx | kz) == 0) {
+            for (int jj = g; jj < m; jj += G) {
+              const double4 q = cp[jj];
+              const double r2 = dist2(__dsub_rn(hp.x, q.x), __dsub_rn(hp.y, q.y),
+                                      __dsub_rn(hp.z, q.z));
+              if (r2 < rmax2 && jj > thr)
+                vv_accept<ADD>(r2, hu, cu[jj], cscale, scale, nb, hs, hc);
+            }
+          } else if (home && fast) {
             for (int jj = g; jj < m; jj += G) {
               const double4 q = cp[jj];
               double dx = __dsub_rn(hp.x, q.x);
@@ -285,8 +299,8 @@ __global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __
               if (kz < 0) dzz = __dadd_rn(dzz, R.L[2]);
               else if (kz > 0) dzz = __dsub_rn(dzz, R.L[2]);
               const double r2 = dist2(dx, dyy, dzz);
-              if (r2 < rmax2 && (int64_t)(c0 + jj) > self)
-                vv_accept(r2, hu, cu[jj], cscale, scale, nb, hs, hc);
+              if (r2 < rmax2 && jj > thr)
+                vv_accept<ADD>(r2, hu, cu[jj], cscale, scale, nb, hs, hc);
             }
           } else if (home) {
             for (int jj = g; jj < m; jj += G) {
@@ -294,8 +308,8 @@ __global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __
               double dx, dyy, dzz;
               le_sep(R, delta, hp.x, hp.y, hp.z, q.x, q.y, q.z, dx, dyy, dzz);
               const double r2 = dist2(dx, dyy, dzz);
-              if (r2 < rmax2 && (int64_t)(c0 + jj) > self)
-                vv_accept(r2, hu, cu[jj], cscale, scale, nb, hs, hc);
+              if (r2 < rmax2 && jj > thr)
+                vv_accept<ADD>(r2, hu, cu[jj], cscale, scale, nb, hs, hc);
             }
           }
           __syncthreads();
@@ -305,9 +319,43 @@ __global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __
       }
     }
   }
-  __syncthreads();
+}
+
+// One wave per block of the table: the block's pairs into an LDS histogram
+// and from there to its partial sums.  Bound by the FP64 and integer work of
+// an accepted pair and its two LDS atomics (vector units busy 79 % of the cycles,
+// LDS 64 %): at N = 1e6, r_max = 10 10.9 -> 8.2 ms with the fixed-point addition
+// and the single-precision bin.
+__global__ __launch_bounds__(VV_HOME) void k_vv_pairs(DevPtrs d, const VvRep* __restrict__ vr,
+                                                      const VvBlock* __restrict__ blocks, int nblk,
+                                                      const int32_t* __restrict__ cstart,
+                                                      const double4* __restrict__ spos,
+                                                      const double4* __restrict__ su,
+                                                      const unsigned long long* __restrict__ umax,
+                                                      int nb, long long* __restrict__ psum,
+                                                      unsigned int* __restrict__ pcnt) {
+  extern __shared__ unsigned long long vv_hist[];  // [nb] sums, then [nb] 32-bit counts
+  __shared__ double4 cp[VV_STAGE], cu[VV_STAGE];
+  const int b = xcd_block(blockIdx.x, nblk);
+  if (b >= nblk) return;
+  const VvBlock B = blocks[b];
+  const VvRep& V = vr[B.rep];
+  const int t = threadIdx.x;
+  unsigned long long* hs = vv_hist;
+  unsigned int* hc = (unsigned int*)(vv_hist + nb);
   for (int k = t; k < nb; k += VV_HOME) {
-    psum[(int64_t)b * nb + k] = (long long)hs[k];
+    hs[k] = 0ull;
+    hc[k] = 0u;
+  }
+  __syncthreads();
+  const double scale = ldexp(1.0, vv_scale_exp(umax[B.rep], V.log2p));
+  const bool add = V.log2p >= 11;   // |p * scale| < 2^(61 - log2p) = 2^50
+  if (add) vv_pairs_block<true>(d, V, B, cstart, spos, su, scale, nb, hs, hc, cp, cu);
+  else vv_pairs_block<false>(d, V, B, cstart, spos, su, scale, nb, hs, hc, cp, cu);
+  __syncthreads();
+  const unsigned long long off = add ? (unsigned long long)__double_as_longlong(VV_MAGIC) : 0ull;
+  for (int k = t; k < nb; k += VV_HOME) {
+    psum[(int64_t)b * nb + k] = (long long)(hs[k] - off * hc[k]);
     pcnt[(int64_t)b * nb + k] = hc[k];
   }
 }
@@ -323,7 +371,7 @@ __device__ __forceinline__ void add128(unsigned long long& lo, long long& hi,
 
 __global__ __launch_bounds__(256) void k_vv_fold(const int2* __restrict__ chunks, int nb,
                                                  const long long* __restrict__ psum,
-                                                 const unsigned long long* __restrict__ pcnt,
+                                                 const unsigned int* __restrict__ pcnt,
                                                  unsigned long long* __restrict__ f_lo,
                                                  long long* __restrict__ f_hi,
                                                  unsigned long long* __restrict__ f_cnt) {
@@ -343,30 +391,39 @@ __global__ __launch_bounds__(256) void k_vv_fold(const int2* __restrict__ chunks
   }
 }
 
-// second stage, per replica and bin: the chunks' 128-bit integers added
-// exactly (chunk order), halved (each pair was counted from both ends) and
-// scaled back; per replica the blocks' |u|^2 sums in block order
-__global__ __launch_bounds__(256) void k_vv_reduce(DevPtrs d, const VvRep* __restrict__ vr,
-                                                   const int32_t* __restrict__ rep_chunk0,
-                                                   int nrep, int nb,
-                                                   const unsigned long long* __restrict__ f_lo,
-                                                   const long long* __restrict__ f_hi,
-                                                   const unsigned long long* __restrict__ f_cnt,
-                                                   const unsigned long long* __restrict__ umax,
-                                                   const double* __restrict__ u2_part,
-                                                   double* __restrict__ out_sum,
-                                                   long long* __restrict__ out_cnt,
-                                                   double* __restrict__ out_u2) {
-  const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// second stage, one wave per replica and bin: the chunks' 128-bit integers
+// added exactly (the order does not matter) and scaled back; one more wave
+// per replica adds the blocks' |u|^2 sums (a fixed tree).  (One thread per
+// bin walking every chunk took 228 us at N = 1e6.)
+__global__ __launch_bounds__(64) void k_vv_reduce(DevPtrs d, const VvRep* __restrict__ vr,
+                                                  const int32_t* __restrict__ rep_chunk0,
+                                                  int nrep, int nb,
+                                                  const unsigned long long* __restrict__ f_lo,
+                                                  const long long* __restrict__ f_hi,
+                                                  const unsigned long long* __restrict__ f_cnt,
+                                                  const unsigned long long* __restrict__ umax,
+                                                  const double* __restrict__ u2_part,
+                                                  double* __restrict__ out_sum,
+                                                  long long* __restrict__ out_cnt,
+                                                  double* __restrict__ out_u2) {
+  const int lane = threadIdx.x;
+  const int64_t o = blockIdx.x;
   if (o < (int64_t)nrep * nb) {
     const int rep = (int)(o / nb), k = (int)(o % nb);
     unsigned long long lo = 0ull, c = 0ull;
     long long hi = 0;
-    for (int ch = rep_chunk0[rep]; ch < rep_chunk0[rep + 1]; ++ch) {
+    for (int ch = rep_chunk0[rep] + lane; ch < rep_chunk0[rep + 1]; ch += 64) {
       const int64_t q = (int64_t)ch * nb + k;
       add128(lo, hi, f_lo[q], f_hi[q]);
       c += f_cnt[q];
     }
+    for (int s = 32; s > 0; s >>= 1) {
+      const unsigned long long plo = __shfl_xor(lo, s, 64), pc = __shfl_xor(c, s, 64);
+      const long long phi = __shfl_xor(hi, s, 64);
+      add128(lo, hi, plo, phi);
+      c += pc;
+    }
+    if (lane != 0) return;
     // to FP64 through the magnitude (a small negative total has hi = -1 and
     // lo near 2^64: converting those parts separately would cancel)
     const bool neg = hi < 0;
@@ -380,12 +437,13 @@ __global__ __launch_bounds__(256) void k_vv_reduce(DevPtrs d, const VvRep* __res
     const int S = vv_scale_exp(umax[rep], vr[rep].log2p);
     out_sum[o] = ldexp(val, -S);
     out_cnt[o] = (long long)c;
-  }
-  if (o < nrep) {
-    const RepDev& R = d.rep[o];
+  } else {
+    const int rep = (int)(o - (int64_t)nrep * nb);
+    const RepDev& R = d.rep[rep];
     double s = 0.0;
-    for (int bb = 0; bb < R.nblk; ++bb) s += u2_part[R.blk_off + bb];
-    out_u2[o] = s;
+    for (int bb = lane; bb < R.nblk; bb += 64) s += u2_part[R.blk_off + bb];
+    s = wave_sum(s);
+    if (lane == 0) out_u2[rep] = s;
   }
 }
 
@@ -413,7 +471,7 @@ hipError_t launch_vv_scatter(const DevPtrs& d, int flow, const int32_t* cstart,
 hipError_t launch_vv_pairs(const DevPtrs& d, const VvRep* vr, const VvBlock* blocks, int nblk,
                            const int32_t* cstart, const double4* spos, const double4* su,
                            const unsigned long long* umax, int nb, long long* psum,
-                           unsigned long long* pcnt, hipStream_t s, hipEvent_t ev0,
+                           unsigned int* pcnt, hipStream_t s, hipEvent_t ev0,
                            hipEvent_t ev1) {
   if (nblk <= 0) return hipSuccess;
   const dim3 g(xcd_grid(nblk)), bl(VV_HOME);
@@ -431,15 +489,14 @@ int vv_fold() { return VV_FOLD; }
 
 hipError_t launch_vv_reduce(const DevPtrs& d, const VvRep* vr, const int2* chunks, int nchunk,
                             const int32_t* rep_chunk0, int nrep, int nb, const long long* psum,
-                            const unsigned long long* pcnt, unsigned long long* f_lo,
+                            const unsigned int* pcnt, unsigned long long* f_lo,
                             long long* f_hi, unsigned long long* f_cnt,
                             const unsigned long long* umax, const double* u2_part,
                             double* out_sum, long long* out_cnt, double* out_u2, hipStream_t s) {
   if (nchunk > 0)
     hipLaunchKernelGGL(k_vv_fold, dim3((unsigned)nchunk), dim3(256), 0, s, chunks, nb, psum, pcnt,
                        f_lo, f_hi, f_cnt);
-  const int64_t n = std::max<int64_t>((int64_t)nrep * nb, nrep);
-  hipLaunchKernelGGL(k_vv_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d, vr,
+  hipLaunchKernelGGL(k_vv_reduce, dim3((unsigned)(nrep * (nb + 1))), dim3(64), 0, s, d, vr,
                      rep_chunk0, nrep, nb, f_lo, f_hi, f_cnt, umax, u2_part, out_sum, out_cnt,
                      out_u2);
   return hipGetLastError();
