@@ -213,38 +213,60 @@ __global__ void k_cell_sort(DevPtrs d) {
 // ===========================================================================
 // Neighbour count.  The first NBR_SLOTS accepted candidates of each row are
 // also kept, slot-major (slots[k * rows + i]), so that the list pass copies
-// them instead of searching the stencil again.
-__global__ __launch_bounds__(BLOCK_THREADS) void k_nbr_count(DevPtrs d, int32_t* __restrict__ slots) {
-  const int blk = xcd_block(blockIdx.x, d.nblk);  // neighbour rows in this XCD's L2
-  if (blk >= d.nblk) return;
+// them instead of searching the stencil again.  Bound by vector instructions
+// (89 % of its cycles at N = 1e6), so a wave whose particles all lie away from
+// the faces tests plain differences (three subtractions in place of the image
+// rule's twenty compares and selects), and cell keys shift instead of dividing:
+// 227 -> 172 us at N = 1e6, 1643 -> 1247 at 8e6.  Blocks of 256 threads: 1024
+// left most of the chip idle on small handles (N = 1e3: one unit).
+constexpr int NBR_THREADS = 256;
+constexpr int NBR_TILES = ROWS_PER_BLOCK / NBR_THREADS;
+__global__ __launch_bounds__(NBR_THREADS) void k_nbr_count(DevPtrs d, int32_t* __restrict__ slots) {
+  const int tile = xcd_block(blockIdx.x, NBR_TILES * d.nblk);  // neighbour rows in this XCD's L2
+  if (tile >= NBR_TILES * d.nblk) return;
   // a copy: the box constants stay in registers across the candidate loop
   // (through the reference they were reloaded after every slot store: 1619
   // -> 1580 us at N = 8e6)
-  const RepDev R = d.rep[d.blk_rep[blk]];
+  const RepDev R = d.rep[d.blk_rep[tile / NBR_TILES]];
   const int64_t step = *d.step_d;
   const double delta = le_offset(R, step);
-  int mx = 0;
-  for (int u = 0; u < ROWS_PER_BLOCK / BLOCK_THREADS; ++u) {
-    const int64_t i = (int64_t)blk * ROWS_PER_BLOCK + u * BLOCK_THREADS + threadIdx.x;
-    int cnt = 0;
-    if (i - R.row_off < R.n) {
-      const double4 pi = d.pos[i];
-      for_candidates(R, d.cell_row, delta, pi.x, pi.y, pi.z, i, [&](int j) {
-        const double4 pj = d.pos[j];
-        double dx, dy, dz;
-        le_sep(R, delta, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-        if (dist2(dx, dy, dz) < R.rc2) {
-          if (cnt < NBR_SLOTS) slots[(int64_t)cnt * d.rows + i] = j;
-          ++cnt;
-        }
-      });
-    }
-    d.rowlen[i] = cnt;
-    mx = cnt > mx ? cnt : mx;
+  const int64_t i = (int64_t)tile * NBR_THREADS + threadIdx.x;
+  const bool real = i - R.row_off < R.n;
+  int cnt = 0;
+  double4 pi = make_double4(0.0, 0.0, 0.0, -1.0);
+  int cx = 1, cy = 1, cz = 1;
+  if (real) {
+    pi = d.pos[i];
+    cx = cell_axis(pi.x, R, 0);
+    cy = cell_axis(pi.y, R, 1);
+    cz = cell_axis(pi.z, R, 2);
   }
-  // longest row: one atomic per block (atomics on one address serialise
-  // across the chip)
-  __shared__ int wmax[BLOCK_THREADS / 64];
+  auto take = [&](int j, double r2) {
+    if (r2 < R.rc2) {
+      if (cnt < NBR_SLOTS) slots[(int64_t)cnt * d.rows + i] = j;
+      ++cnt;
+    }
+  };
+  if (__all(!real || cell_inside(R, cx, cy, cz))) {
+    if (real)
+      for_candidates_inside(R, d.cell_row, cx, cy, cz, i, [&](int j) {
+        const double4 pj = d.pos[j];
+        take(j, dist2(__dsub_rn(pi.x, pj.x), __dsub_rn(pi.y, pj.y), __dsub_rn(pi.z, pj.z)));
+      });
+  } else if (real) {
+    for_candidates(R, d.cell_row, delta, pi.x, pi.y, pi.z, i, [&](int j) {
+      const double4 pj = d.pos[j];
+      double dx, dy, dz;
+      le_sep(R, delta, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
+      take(j, dist2(dx, dy, dz));
+    });
+  }
+  d.rowlen[i] = cnt;
+  int mx = cnt;
+  // longest row: at most one atomic per block, and none where the maximum is
+  // no longer than what is there (atomics on one address serialise across the
+  // chip; a stale value read here is only lower)
+  __shared__ int wmax[NBR_THREADS / 64];
   for (int o = 32; o > 0; o >>= 1) {
     const int t = __shfl_xor(mx, o, 64);
     mx = t > mx ? t : mx;
@@ -252,8 +274,9 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_nbr_count(DevPtrs d, int32_t*
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < BLOCK_THREADS / 64; ++w) mx = wmax[w] > mx ? wmax[w] : mx;
-    if (mx > 0) atomicMax(&d.ctrl->max_row, mx);
+    for (int w = 1; w < NBR_THREADS / 64; ++w) mx = wmax[w] > mx ? wmax[w] : mx;
+    if (mx > __hip_atomic_load(&d.ctrl->max_row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&d.ctrl->max_row, mx);
   }
 }
 
@@ -271,40 +294,39 @@ __device__ __forceinline__ double force_coef(const RepDev& R, double r2, double 
 
 // Neighbour list: each passing candidate's sorted row index goes to
 // col[rowptr[i] + k], in k_nbr_count's candidate order: copied from the
-// count pass's slots, or searched again for a row longer than NBR_SLOTS.
-__global__ __launch_bounds__(BLOCK_THREADS) void k_nbr_list(DevPtrs d,
-                                                            const int32_t* __restrict__ slots) {
-  const int blk = xcd_block(blockIdx.x, d.nblk);  // neighbour rows in this XCD's L2
-  if (blk >= d.nblk) return;
-  const RepDev& R = d.rep[d.blk_rep[blk]];
-  const int64_t step = *d.step_d;
-  const double delta = le_offset(R, step);
-  for (int u = 0; u < ROWS_PER_BLOCK / BLOCK_THREADS; ++u) {
-    const int64_t i = (int64_t)blk * ROWS_PER_BLOCK + u * BLOCK_THREADS + threadIdx.x;
-    if (i - R.row_off >= R.n) continue;
-    if (d.ctrl->too_many) {  // offsets wrapped: nothing is written, the fill fails
-      atomicOr(&d.ctrl->overflow, 1);
-      continue;
-    }
-    const int64_t e1 = d.rowptr[i + 1];
-    if (e1 > d.nnz_cap) {
-      atomicOr(&d.ctrl->overflow, 1);
-      continue;
-    }
-    int64_t e = d.rowptr[i];
-    if (e1 - e <= NBR_SLOTS) {
-      for (int k = 0; e < e1; ++k, ++e) d.col[e] = slots[(int64_t)k * d.rows + i];
-      continue;
-    }
-    const double4 pi = d.pos[i];
-    for_candidates(R, d.cell_row, delta, pi.x, pi.y, pi.z, i, [&](int j) {
-      const double4 pj = d.pos[j];
-      double dx, dy, dz;
-      le_sep(R, delta, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-      if (dist2(dx, dy, dz) < R.rc2) d.col[e++] = j;
-    });
-  }
+// count pass's slots, or searched again for a row longer than NBR_SLOTS
+// (with 16 slots the paper's box, 15 entries per row, searched in every wave:
+// 160 -> 42 us per step of 4 x 20060).
+__global__ __launch_bounds__(NBR_THREADS) void k_nbr_list(DevPtrs d,
+                                                          const int32_t* __restrict__ slots) {
+  const int tile = xcd_block(blockIdx.x, NBR_TILES * d.nblk);  // neighbour rows in this XCD's L2
+  if (tile >= NBR_TILES * d.nblk) return;
+  const RepDev& R = d.rep[d.blk_rep[tile / NBR_TILES]];
   if (blockIdx.x == 0 && threadIdx.x == 0 && !d.ctrl->too_many) d.ctrl->nnz = d.rowptr[d.rows];
+  const int64_t i = (int64_t)tile * NBR_THREADS + threadIdx.x;
+  if (i - R.row_off >= R.n) return;
+  if (d.ctrl->too_many) {  // offsets wrapped: nothing is written, the fill fails
+    atomicOr(&d.ctrl->overflow, 1);
+    return;
+  }
+  const int64_t e1 = d.rowptr[i + 1];
+  if (e1 > d.nnz_cap) {
+    atomicOr(&d.ctrl->overflow, 1);
+    return;
+  }
+  int64_t e = d.rowptr[i];
+  if (e1 - e <= NBR_SLOTS) {
+    for (int k = 0; e < e1; ++k, ++e) d.col[e] = slots[(int64_t)k * d.rows + i];
+    return;
+  }
+  const double delta = le_offset(R, *d.step_d);
+  const double4 pi = d.pos[i];
+  for_candidates(R, d.cell_row, delta, pi.x, pi.y, pi.z, i, [&](int j) {
+    const double4 pj = d.pos[j];
+    double dx, dy, dz;
+    le_sep(R, delta, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
+    if (dist2(dx, dy, dz) < R.rc2) d.col[e++] = j;
+  });
 }
 
 // Pair terms and assembly: -alpha*w_ij into val, diag = gamma0 + alpha*sum w,
@@ -620,11 +642,13 @@ hipError_t launch_cell_sort(const DevPtrs& d, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_nbr_count(const DevPtrs& d, int32_t* slots, hipStream_t s) {
-  hipLaunchKernelGGL(k_nbr_count, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, slots);
+  hipLaunchKernelGGL(k_nbr_count, dim3(xcd_grid(NBR_TILES * d.nblk)), dim3(NBR_THREADS), 0, s, d,
+                     slots);
   return hipGetLastError();
 }
 hipError_t launch_nbr_list(const DevPtrs& d, const int32_t* slots, hipStream_t s) {
-  hipLaunchKernelGGL(k_nbr_list, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, slots);
+  hipLaunchKernelGGL(k_nbr_list, dim3(xcd_grid(NBR_TILES * d.nblk)), dim3(NBR_THREADS), 0, s, d,
+                     slots);
   return hipGetLastError();
 }
 hipError_t launch_pair_terms(const DevPtrs& d, hipStream_t s) {

@@ -16,7 +16,7 @@ hipError_t launch_cell_sort(const DevPtrs& d, hipStream_t s);
 hipError_t launch_ctrl_zero(const DevPtrs& d, hipStream_t s);
 // the count pass keeps the first NBR_SLOTS neighbours of every row in
 // slots[NBR_SLOTS][rows] (slot-major) for the list pass
-#define NBR_SLOTS 16
+#define NBR_SLOTS 32
 hipError_t launch_nbr_count(const DevPtrs& d, int32_t* slots, hipStream_t s);
 hipError_t launch_nbr_list(const DevPtrs& d, const int32_t* slots, hipStream_t s);
 hipError_t launch_pair_terms(const DevPtrs& d, hipStream_t s);

@@ -239,7 +239,11 @@ static RepDev make_rep(const sim_params& p) {
   }
   // bricks of 8^3 cells for boxes of 32 or more cells per axis (the IC(0)
   // form keeps the z-major order its colour lists are built in)
-  if (p.precond != SIM_PC_IC0 && R.nc[0] >= 32 && R.nc[1] >= 32 && R.nc[2] >= 32) R.brick = 8;
+  R.bshift = 31;  // one brick
+  if (p.precond != SIM_PC_IC0 && R.nc[0] >= 32 && R.nc[1] >= 32 && R.nc[2] >= 32) {
+    R.brick = 8;
+    R.bshift = 3;
+  }
   R.n = (int32_t)p.n;
   R.kT = p.kT;
   R.gamma0 = p.gamma0;

@@ -51,7 +51,7 @@ struct RepDev {
   int32_t brick;              // brick edge of the cell order, in cells (>= every nc: z-major)
   int32_t l1_cnt;             // first-level reduction blocks of the CG partials (0: none)
   int32_t l1_off;             // the first of them
-  int32_t pad0;
+  int32_t bshift;             // log2 of the brick edge (31: one brick)
   uint64_t seed, stream;
 };
 
@@ -63,7 +63,7 @@ struct RepDev {
 // brick >= nc on every axis gives the plain z-major order.
 __host__ __device__ __forceinline__ int cell_key(const RepDev& R, int cx, int cy, int cz) {
   const int B = R.brick, nx = R.nc[0], ny = R.nc[1], nz = R.nc[2];
-  const int bx = cx / B, by = cy / B, bz = cz / B;
+  const int bx = cx >> R.bshift, by = cy >> R.bshift, bz = cz >> R.bshift;
   const int wx = cx - bx * B, wy = cy - by * B, wz = cz - bz * B;
   const int sx = nx - bx * B < B ? nx - bx * B : B;
   const int sy = ny - by * B < B ? ny - by * B : B;
@@ -326,7 +326,8 @@ __device__ __forceinline__ void for_candidates(const RepDev& R, const int32_t* c
   const int ylo = ncy == 1 ? 0 : -1, yhi = ncy == 1 ? 0 : 1;
   const double eps = 1e-9 * R.cell_len[0];
   for (int dz = zlo; dz <= zhi; ++dz) {
-    const int cz2 = imod(cz + dz, ncz);
+    const int czr = cz + dz;
+    const int cz2 = czr < 0 ? czr + ncz : (czr >= ncz ? czr - ncz : czr);
     for (int dyc = ylo; dyc <= yhi; ++dyc) {
       const int cyr = cy + dyc;
       int cy2, lo, hi;
@@ -352,7 +353,7 @@ __device__ __forceinline__ void for_candidates(const RepDev& R, const int32_t* c
       int len = hi - lo + 1;
       while (len > 0) {
         int run = (a + len <= ncx) ? len : (ncx - a);
-        const int bend = (a / R.brick + 1) * R.brick - a;
+        const int bend = ((a >> R.bshift) + 1) * R.brick - a;
         run = run < bend ? run : bend;
         const int c0 = R.seg_off + cell_key(R, a, cy2, cz2);
         const int j0 = cell_row[c0], j1 = cell_row[c0 + run];
@@ -363,6 +364,37 @@ __device__ __forceinline__ void for_candidates(const RepDev& R, const int32_t* c
       }
     }
   }
+}
+
+// The same candidates in the same order for a particle of cell (cx, cy, cz)
+// with no box face among its neighbour cells (at least three cells per axis,
+// none of the nine rows crosses a face): no image, no periodic wrap.  The
+// separation is then the plain difference: where the general form would wrap
+// one (only cells of L/3 allow |d| > L/2) the pair is no closer than a cell
+// either way.
+__device__ __forceinline__ bool cell_inside(const RepDev& R, int cx, int cy, int cz) {
+  return cx >= 1 && cx + 2 <= R.nc[0] && cy >= 1 && cy + 2 <= R.nc[1] && cz >= 1 &&
+         cz + 2 <= R.nc[2];
+}
+template <typename F>
+__device__ __forceinline__ void for_candidates_inside(const RepDev& R, const int32_t* cell_row,
+                                                      int cx, int cy, int cz, int64_t self, F&& f) {
+  const int first = ((((cx - 1) >> R.bshift) + 1) << R.bshift) - (cx - 1);  // cells to the brick's end
+  const int run = R.bshift < 31 && first < 3 ? first : 3;
+  for (int dz = -1; dz <= 1; ++dz)
+    for (int dy = -1; dy <= 1; ++dy) {
+      int c0 = R.seg_off + cell_key(R, cx - 1, cy + dy, cz + dz);
+      int j = cell_row[c0], j1 = cell_row[c0 + run];
+      for (; j < j1; ++j)
+        if (j != self) f(j);
+      if (run < 3) {
+        c0 = R.seg_off + cell_key(R, cx - 1 + run, cy + dy, cz + dz);
+        j = cell_row[c0];
+        j1 = cell_row[c0 + 3 - run];
+        for (; j < j1; ++j)
+          if (j != self) f(j);
+      }
+    }
 }
 
 // ---------------------------------------------------------------------------
