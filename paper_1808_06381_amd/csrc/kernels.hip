@@ -22,7 +22,10 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int32_t v, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// exclusive scan of int32 (3 passes: block sums, scan of block sums, down)
+// exclusive scan of int32 (two passes: block sums; then each block adds the
+// sums before it and scans its own tile, with 16-byte accesses and wave scans:
+// 4.4 + 5.0 us at 1e6 rows, against 4.5 + 4.4 + 10.7 us in three passes).  One
+// launch where there is one block.
 // ---------------------------------------------------------------------------
 #define SCAN_ITEMS 8
 #define SCAN_TILE (BLOCK_THREADS * SCAN_ITEMS)
@@ -33,6 +36,7 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_reduce(const int32_t* __
   __shared__ int32_t lds[BLOCK_THREADS / 64];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
   int32_t s = 0;
+#pragma unroll
   for (int k = 0; k < SCAN_ITEMS; ++k) {
     const int64_t i = base + (int64_t)k * BLOCK_THREADS + threadIdx.x;
     if (i < m) s += in[i];
@@ -47,71 +51,71 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_reduce(const int32_t* __
   }
 }
 
-// inclusive scan of one value per thread over the block (Hillis-Steele in LDS)
-__device__ __forceinline__ int32_t block_incl_scan(int32_t v, int32_t* lds) {
-  lds[threadIdx.x] = v;
-  __syncthreads();
-  for (int o = 1; o < (int)blockDim.x; o <<= 1) {
-    const int32_t add = threadIdx.x >= (unsigned)o ? lds[threadIdx.x - o] : 0;
-    __syncthreads();
-    lds[threadIdx.x] += add;
-    __syncthreads();
-  }
-  return lds[threadIdx.x];
-}
-
-// The block sums are scanned in 64 bits: if the total passes INT32_MAX the
-// 32-bit offsets below would wrap, so *too_many (optional) is raised and the
+// The sums before a block are added in 64 bits: if the total passes INT32_MAX
+// the 32-bit offsets would wrap, so *too_many (optional) is raised and the
 // consumers of the offsets (the neighbour list) write nothing.
-__device__ __forceinline__ int64_t block_incl_scan64(int64_t v, int64_t* lds) {
-  lds[threadIdx.x] = v;
-  __syncthreads();
-  for (int o = 1; o < (int)blockDim.x; o <<= 1) {
-    const int64_t add = threadIdx.x >= (unsigned)o ? lds[threadIdx.x - o] : 0;
-    __syncthreads();
-    lds[threadIdx.x] += add;
-    __syncthreads();
-  }
-  return lds[threadIdx.x];
-}
-
-__global__ __launch_bounds__(1024) void k_scan_top(int32_t* __restrict__ bsum, int64_t nb,
-                                                   int32_t* __restrict__ too_many) {
-  __shared__ int64_t lds[1024];
-  __shared__ int64_t carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int64_t base = 0; base < nb; base += 1024) {
-    const int64_t i = base + threadIdx.x;
-    const int64_t v = i < nb ? bsum[i] : 0;
-    const int64_t inc = block_incl_scan64(v, lds);
-    const int64_t c = carry;
-    if (i < nb) bsum[i] = (int32_t)(c + inc - v);
-    __syncthreads();
-    if (threadIdx.x == 1023) carry = c + inc;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0 && too_many && carry > (int64_t)INT32_MAX) *too_many = 1;
-}
-
 __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_down(const int32_t* __restrict__ in,
                                                              int64_t m,
                                                              const int32_t* __restrict__ bsum,
-                                                             int32_t* __restrict__ out) {
-  __shared__ int32_t lds[BLOCK_THREADS];
-  const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
+                                                             int32_t* __restrict__ out,
+                                                             int32_t* __restrict__ too_many) {
+  constexpr int WAVES = BLOCK_THREADS / 64;
+  __shared__ int32_t wsum[WAVES];
+  __shared__ int64_t wbase[WAVES];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)t * SCAN_ITEMS;
+  static_assert(SCAN_ITEMS == 8, "two 16-byte loads per thread");
   int32_t v[SCAN_ITEMS];
   int32_t tot = 0;
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    v[k] = base + k < m ? in[base + k] : 0;
-    tot += v[k];
+  // in and out are whole allocations, so base (a multiple of 8) is aligned
+  const bool whole = base + SCAN_ITEMS <= m;
+  if (whole) {
+    const int4 a = reinterpret_cast<const int4*>(in + base)[0];
+    const int4 b = reinterpret_cast<const int4*>(in + base)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k) v[k] = base + k < m ? in[base + k] : 0;
   }
-  const int32_t inc = block_incl_scan(tot, lds);
-  int32_t run = bsum[blockIdx.x] + inc - tot;
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    if (base + k < m) out[base + k] = run;
-    run += v[k];
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) tot += v[k];
+  int64_t before = 0;
+  for (int b = t; b < (int)blockIdx.x; b += BLOCK_THREADS) before += bsum[b];
+  int32_t inc = tot;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t up = __shfl_up(inc, o, 64);
+    inc += lane >= o ? up : 0;
+    before += __shfl_xor(before, o, 64);
   }
+  if (lane == 63) wsum[wave] = inc;
+  if (lane == 0) wbase[wave] = before;
+  __syncthreads();
+  int64_t run64 = 0;
+  int64_t all = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    run64 += wbase[w] + (w < wave ? wsum[w] : 0);
+    all += wsum[w];
+  }
+  int32_t run = (int32_t)run64 + inc - tot;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    const int32_t next = run + v[k];
+    v[k] = run;
+    run = next;
+  }
+  if (whole) {
+    reinterpret_cast<int4*>(out + base)[0] = make_int4(v[0], v[1], v[2], v[3]);
+    reinterpret_cast<int4*>(out + base)[1] = make_int4(v[4], v[5], v[6], v[7]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k)
+      if (base + k < m) out[base + k] = v[k];
+  }
+  if (too_many && t == 0 && blockIdx.x + 1 == gridDim.x && run64 + all > (int64_t)INT32_MAX)
+    *too_many = 1;
 }
 
 // ===========================================================================
@@ -292,6 +296,91 @@ __device__ __forceinline__ double force_coef(const RepDev& R, double r2, double 
   return 0.0;
 }
 
+// The count for small handles: sixteen lanes per particle, nine of them taking
+// one row of cells each, so that a particle waits for one row's dependent
+// loads instead of nine rows' (the chip is mostly idle at these sizes).  A
+// lane keeps its accepted candidates in LDS; a scan over the lanes gives each
+// row of cells its place, so the columns come in the candidate order of
+// k_nbr_count.  A particle with a lane of more than NBR_LANE_KEEP accepted
+// candidates is searched again by its first lane.  N = 1e3: 58 -> 12 us, N = 1e5:
+// 58 -> 37.
+constexpr int NBR_LANES = 16;
+constexpr int NBR_LANE_KEEP = 12;
+constexpr int NBR_WIDE_ROWS = NBR_THREADS / NBR_LANES;  // particles per block
+__global__ __launch_bounds__(NBR_THREADS) void k_nbr_count_wide(DevPtrs d,
+                                                                int32_t* __restrict__ slots) {
+  const int ntile = ROWS_PER_BLOCK / NBR_WIDE_ROWS * d.nblk;
+  const int tile = xcd_block(blockIdx.x, ntile);
+  if (tile >= ntile) return;
+  __shared__ int32_t keep[NBR_LANE_KEEP][NBR_THREADS];
+  __shared__ int wmax[NBR_THREADS / 64];
+  const RepDev R = d.rep[d.blk_rep[tile / (ROWS_PER_BLOCK / NBR_WIDE_ROWS)]];
+  const int64_t step = *d.step_d;
+  const double delta = le_offset(R, step);
+  const int t = threadIdx.x, lane = t % NBR_LANES;
+  const int64_t i = (int64_t)tile * NBR_WIDE_ROWS + t / NBR_LANES;
+  const bool real = i - R.row_off < R.n;
+  const int dz = lane / 3 - 1, dy = lane % 3 - 1;
+  const bool mine = real && lane < 9 && (dz == 0 || R.nc[2] > 1) && (dy == 0 || R.nc[1] > 1);
+  double4 pi = make_double4(0.0, 0.0, 0.0, -1.0);
+  if (real) pi = d.pos[i];
+  int cnt = 0;
+  const int cx = cell_axis(pi.x, R, 0), cy = cell_axis(pi.y, R, 1), cz = cell_axis(pi.z, R, 2);
+  auto take = [&](int j, double r2) {
+    if (r2 < R.rc2) {
+      if (cnt < NBR_LANE_KEEP) keep[cnt][t] = j;
+      ++cnt;
+    }
+  };
+  if (__all(!mine || cell_inside(R, cx, cy, cz))) {
+    if (mine)
+      for_candidates_row(R, d.cell_row, delta, pi.x, cx, cy, cz, dz, dy, i, [&](int j) {
+        const double4 pj = d.pos[j];
+        take(j, dist2(__dsub_rn(pi.x, pj.x), __dsub_rn(pi.y, pj.y), __dsub_rn(pi.z, pj.z)));
+      });
+  } else if (mine) {
+    for_candidates_row(R, d.cell_row, delta, pi.x, cx, cy, cz, dz, dy, i, [&](int j) {
+      const double4 pj = d.pos[j];
+      double dx, dyy, dzz;
+      le_sep(R, delta, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dyy, dzz);
+      take(j, dist2(dx, dyy, dzz));
+    });
+  }
+  int inc = cnt, most = cnt;   // over the particle's sixteen lanes
+#pragma unroll
+  for (int o = 1; o < NBR_LANES; o <<= 1) {
+    const int up = __shfl_up(inc, o, NBR_LANES);
+    inc += lane >= o ? up : 0;
+    most = max(most, __shfl_xor(most, o, NBR_LANES));
+  }
+  const int total = __shfl(inc, NBR_LANES - 1, NBR_LANES);
+  if (most <= NBR_LANE_KEEP) {
+    for (int k = 0, at = inc - cnt; k < cnt && at < NBR_SLOTS; ++k, ++at)
+      slots[(int64_t)at * d.rows + i] = keep[k][t];
+  } else if (lane == 0) {
+    int at = 0;
+    for_candidates(R, d.cell_row, delta, pi.x, pi.y, pi.z, i, [&](int j) {
+      const double4 pj = d.pos[j];
+      double dx, dyy, dzz;
+      le_sep(R, delta, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dyy, dzz);
+      if (dist2(dx, dyy, dzz) < R.rc2) {
+        if (at < NBR_SLOTS) slots[(int64_t)at * d.rows + i] = j;
+        ++at;
+      }
+    });
+  }
+  if (lane == 0) d.rowlen[i] = total;
+  int mx = total;
+  for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+  if ((t & 63) == 0) wmax[t >> 6] = mx;
+  __syncthreads();
+  if (t == 0) {
+    for (int w = 1; w < NBR_THREADS / 64; ++w) mx = max(mx, wmax[w]);
+    if (mx > __hip_atomic_load(&d.ctrl->max_row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&d.ctrl->max_row, mx);
+  }
+}
+
 // Neighbour list: each passing candidate's sorted row index goes to
 // col[rowptr[i] + k], in k_nbr_count's candidate order: copied from the
 // count pass's slots, or searched again for a row longer than NBR_SLOTS
@@ -332,27 +421,30 @@ __global__ __launch_bounds__(NBR_THREADS) void k_nbr_list(DevPtrs d,
 // Pair terms and assembly: -alpha*w_ij into val, diag = gamma0 + alpha*sum w,
 // 1/diag, and the three right-hand sides: Couette drive (Eq. 6c),
 // conservative force (Eq. 6b), boundary velocity term of Eq. 8, thermal
-// force.  A block owns a tile of PAIR_THREADS rows (a quarter of a row
-// block, so that the grid holds enough waves to hide the gathers) and walks
+// force.  A block owns a tile of ROWS rows (256, a quarter of a row block, so
+// that the grid holds enough waves to hide the gathers; 64 on small handles,
+// which 256 leave with a few blocks of many passes: N = 1e3 28 -> 14 us, 4 x
+// 20060 rows of 15 entries 54 -> 37) and walks
 // the tile's CSR entries (contiguous) in chunks of PAIR_THREADS, one entry
 // per lane, so every lane has an entry to work on whatever the row lengths;
 // each entry leaves its five row contributions (w, w s, and the three force
 // components with the pair noise) in LDS, and each thread then adds those of
 // its row in entry order.  The node noise and the assembly run once per row.
 #define PAIR_THREADS 256
-#define PAIR_TILES (ROWS_PER_BLOCK / PAIR_THREADS)   // tiles per row block
+template <int ROWS>
 __global__ __launch_bounds__(PAIR_THREADS) void k_pair_terms(DevPtrs d) {
-  const int tile = xcd_block(blockIdx.x, PAIR_TILES * d.nblk);  // rows in this XCD's L2
-  if (tile >= PAIR_TILES * d.nblk) return;
-  const int blk = tile / PAIR_TILES;
+  constexpr int TILES = ROWS_PER_BLOCK / ROWS;                  // tiles per row block
+  const int tile = xcd_block(blockIdx.x, TILES * d.nblk);       // rows in this XCD's L2
+  if (tile >= TILES * d.nblk) return;
+  const int blk = tile / TILES;
   const RepDev R = d.rep[d.blk_rep[blk]];  // a copy: no reloads after the entry stores
   if (d.ctrl->overflow) return;
-  __shared__ int rp[PAIR_THREADS + 1];        // row pointers of the tile
+  __shared__ int rp[ROWS + 1];                // row pointers of the tile
   __shared__ int16_t erow[PAIR_THREADS];      // tile row of each entry of the chunk
   __shared__ double contrib[5][PAIR_THREADS]; // w, w s, fx, fy, fz of each entry
   const int t = threadIdx.x;
-  const int64_t row0 = (int64_t)blk * ROWS_PER_BLOCK + (tile % PAIR_TILES) * PAIR_THREADS;
-  for (int r = t; r <= PAIR_THREADS; r += PAIR_THREADS) rp[r] = d.rowptr[row0 + r];
+  const int64_t row0 = (int64_t)blk * ROWS_PER_BLOCK + (tile % TILES) * ROWS;
+  for (int r = t; r <= ROWS; r += PAIR_THREADS) rp[r] = d.rowptr[row0 + r];
   __syncthreads();
   const int64_t step = *d.step_d;
   const double delta = le_offset(R, step);
@@ -361,10 +453,11 @@ __global__ __launch_bounds__(PAIR_THREADS) void k_pair_terms(DevPtrs d) {
   double acc[5];
 #pragma unroll
   for (int k = 0; k < 5; ++k) acc[k] = 0.0;
-  const int E0 = rp[0], E1 = rp[PAIR_THREADS];
+  const int E0 = rp[0], E1 = rp[ROWS];
+  const bool rowt = ROWS == PAIR_THREADS || t < ROWS;
   for (int cb = E0; cb < E1; cb += PAIR_THREADS) {
     // the tile row of each entry of this chunk
-    {
+    if (rowt) {
       const int lo = max(rp[t], cb), hi = min(rp[t + 1], cb + PAIR_THREADS);
       for (int e = lo; e < hi; ++e) erow[e - cb] = (int16_t)t;
     }
@@ -408,7 +501,7 @@ __global__ __launch_bounds__(PAIR_THREADS) void k_pair_terms(DevPtrs d) {
       contrib[4][t] = fz;
     }
     __syncthreads();
-    {
+    if (rowt) {
       const int lo = max(rp[t], cb), hi = min(rp[t + 1], cb + PAIR_THREADS);
       for (int e2 = lo; e2 < hi; ++e2)
 #pragma unroll
@@ -417,7 +510,7 @@ __global__ __launch_bounds__(PAIR_THREADS) void k_pair_terms(DevPtrs d) {
     __syncthreads();  // erow and contrib are rewritten for the next chunk
   }
   const double drag_unit = R.alpha * (R.shear * R.L[1]);
-  {
+  if (rowt) {
     const int64_t i = row0 + t;
     if (i - R.row_off >= R.n) {  // padding row: identity, no right-hand side
       d.diag[i] = 1.0;
@@ -617,9 +710,10 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
 hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t m, int32_t* bsum, hipStream_t s,
                        int32_t* too_many) {
   const int64_t nb = (m + SCAN_TILE - 1) / SCAN_TILE;
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(BLOCK_THREADS), 0, s, in, m, bsum);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, nb, too_many);
-  hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(BLOCK_THREADS), 0, s, in, m, bsum, out);
+  if (nb > 1)
+    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(BLOCK_THREADS), 0, s, in, m, bsum);
+  hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(BLOCK_THREADS), 0, s, in, m, bsum, out,
+                     too_many);
   return hipGetLastError();
 }
 
@@ -642,6 +736,13 @@ hipError_t launch_cell_sort(const DevPtrs& d, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_nbr_count(const DevPtrs& d, int32_t* slots, hipStream_t s) {
+  // few particles per cell only: with 4.2 (the paper's box) a row of cells is a
+  // long walk for one lane, 126 against 97 us
+  if (d.rows <= SMALL_ROWS && d.rows <= 2.5 * d.ncell_entries) {
+    hipLaunchKernelGGL(k_nbr_count_wide, dim3(xcd_grid(ROWS_PER_BLOCK / NBR_WIDE_ROWS * d.nblk)),
+                       dim3(NBR_THREADS), 0, s, d, slots);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_nbr_count, dim3(xcd_grid(NBR_TILES * d.nblk)), dim3(NBR_THREADS), 0, s, d,
                      slots);
   return hipGetLastError();
@@ -652,8 +753,12 @@ hipError_t launch_nbr_list(const DevPtrs& d, const int32_t* slots, hipStream_t s
   return hipGetLastError();
 }
 hipError_t launch_pair_terms(const DevPtrs& d, hipStream_t s) {
-  hipLaunchKernelGGL(k_pair_terms, dim3(xcd_grid(PAIR_TILES * d.nblk)), dim3(PAIR_THREADS), 0, s,
-                     d);
+  if (d.rows <= SMALL_ROWS)
+    hipLaunchKernelGGL(k_pair_terms<64>, dim3(xcd_grid(ROWS_PER_BLOCK / 64 * d.nblk)),
+                       dim3(PAIR_THREADS), 0, s, d);
+  else
+    hipLaunchKernelGGL(k_pair_terms<256>, dim3(xcd_grid(ROWS_PER_BLOCK / 256 * d.nblk)),
+                       dim3(PAIR_THREADS), 0, s, d);
   return hipGetLastError();
 }
 hipError_t launch_ctrl_zero(const DevPtrs& d, hipStream_t s) {

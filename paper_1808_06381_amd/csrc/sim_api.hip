@@ -546,6 +546,7 @@ static int prepare_precond(sim_t* s) {
 // Fresh start from x = 0 (which also takes ||b||^2); with `warm`, the
 // iterating components then restart from the previous step's velocities:
 // x = v_prev, r = b - A x, done if r passes, else the restart path.
+static int cg_queue_restart(sim_t* s);
 static int cg_queue_start(sim_t* s, double tol, bool warm) {
   s->vv_valid = false;
   s->ring = sim_t::CgRing();
@@ -563,20 +564,16 @@ static int cg_queue_start(sim_t* s, double tol, bool warm) {
     HIPCHK(launch_cg_warm(d, s->id_off_d, s->stream));
     HIPCHK(launch_cg_spmv(d, 2, 0, s->stream));
     HIPCHK(launch_cg_finish(d, 4, s->ring.slot, 0, s->stream));
-    HIPCHK(launch_cg_vec(d, 1, s->stream));
-    if (ext) {
-      int rc = queue_apply(s, 1, nullptr, nullptr);
-      if (rc) return rc;
-    }
-    HIPCHK(launch_cg_spmv(d, 0, 1, s->stream));
-    HIPCHK(launch_cg_finish(d, 1, s->ring.slot, 0, s->stream));
+    int rc = cg_queue_restart(s);
+    if (rc) return rc;
   }
   return SIM_OK;
 }
 
 // n iterations (iteration numbers first..first+n-1 for the timing probe,
 // which is off when probes is false), then the check round: true residuals
-// of replicas whose components all passed, restarts of those that failed
+// of replicas whose components all passed (those that fail restart before the
+// next chunk, which the host queues)
 static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
   const DevPtrs d = cg_view(s);  // for the configuration; the buffers rotate below
   hipStream_t stream = s->stream;
@@ -679,13 +676,19 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
   const DevPtrs dc = cg_view(s);
   HIPCHK(launch_cg_spmv(dc, 1, 0, stream));
   HIPCHK(launch_cg_finish(dc, 3, s->ring.slot, 0, stream));
-  HIPCHK(launch_cg_vec(dc, 1, stream));
-  if (ext) {
+  return SIM_OK;
+}
+
+// the components whose true residual failed the check start over from it
+static int cg_queue_restart(sim_t* s) {
+  const DevPtrs d = cg_view(s);
+  HIPCHK(launch_cg_vec(d, 1, s->stream));
+  if (d.learned || d.ic0) {
     int rc = queue_apply(s, 1, nullptr, nullptr);
     if (rc) return rc;
   }
-  HIPCHK(launch_cg_spmv(dc, 0, 1, stream));
-  HIPCHK(launch_cg_finish(dc, 1, s->ring.slot, 0, stream));
+  HIPCHK(launch_cg_spmv(d, 0, 1, s->stream));
+  HIPCHK(launch_cg_finish(d, 1, s->ring.slot, 0, s->stream));
   return SIM_OK;
 }
 
@@ -727,6 +730,9 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
       }
     }
     const int n = std::max(1, std::min(2, maxit + 1 - launched));
+    bool restart = false;
+    for (int r = 0; r < s->R; ++r) restart = restart || s->cg_h[r].restart != 0;
+    if (restart && (rc = cg_queue_restart(s))) return rc;
     if ((rc = cg_queue_chunk(s, n, launched, true))) return rc;
     launched += n;
   }

@@ -210,6 +210,9 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 // N = 2.5e5 2.28 against 2.33 / 2.51 / 3.30.  So 1024 threads where the
 // sub-tiles leave half the chip's 256 units idle, else 512.
 #define FUSED_ROWS (128 * 1024)
+// ... and build their system with kernels that spread a particle's search and
+// a row's entries over more lanes (k_nbr_count_wide, k_pair_terms<64>)
+#define SMALL_ROWS 131072
 #define FUSED_WIDE_SUBS 128
 
 // ---------------------------------------------------------------------------
@@ -316,54 +319,58 @@ __device__ __forceinline__ int imod(int a, int m) {
 // Consecutive x cells of one brick are contiguous in the sorted order, so
 // each run is a few row ranges.  f(j) is called for every candidate j != i
 // in a fixed order.
+// One row (dz, dyc) of them:
+template <typename F>
+__device__ __forceinline__ void for_candidates_row(const RepDev& R, const int32_t* cell_row,
+                                                   double delta, double xi, int cx, int cy, int cz,
+                                                   int dz, int dyc, int64_t self, F&& f) {
+  const int ncx = R.nc[0], ncy = R.nc[1], ncz = R.nc[2];
+  const double eps = 1e-9 * R.cell_len[0];
+  const int czr = cz + dz;
+  const int cz2 = czr < 0 ? czr + ncz : (czr >= ncz ? czr - ncz : czr);
+  const int cyr = cy + dyc;
+  int cy2, lo, hi;
+  if (ncy == 1) {
+    cy2 = 0; lo = 0; hi = ncx - 1;
+  } else if (cyr >= 0 && cyr < ncy) {
+    cy2 = cyr;
+    if (ncx == 1) { lo = 0; hi = 0; }
+    else { lo = cx - 1; hi = cx + 1; }
+  } else {
+    // across the y boundary: j's image is shifted by s*delta in x, with
+    // s = +1 going up (j in row 0) and -1 going down (j in the top row)
+    const double sd = cyr >= ncy ? delta : -delta;
+    cy2 = cyr >= ncy ? 0 : ncy - 1;
+    const double c0 = xi - sd;
+    lo = (int)floor((c0 - R.rc - eps) * R.inv_cell[0]);
+    hi = (int)floor((c0 + R.rc + eps) * R.inv_cell[0]);
+    if (hi - lo + 1 >= ncx) { lo = 0; hi = ncx - 1; }
+  }
+  // split [lo, hi] at the periodic x edge and at brick edges into runs
+  // of consecutive cells (consecutive keys)
+  int a = imod(lo, ncx);
+  int len = hi - lo + 1;
+  while (len > 0) {
+    int run = (a + len <= ncx) ? len : (ncx - a);
+    const int bend = ((a >> R.bshift) + 1) * R.brick - a;
+    run = run < bend ? run : bend;
+    const int c0 = R.seg_off + cell_key(R, a, cy2, cz2);
+    const int j0 = cell_row[c0], j1 = cell_row[c0 + run];
+    for (int j = j0; j < j1; ++j)
+      if (j != self) f(j);
+    len -= run;
+    a = a + run == ncx ? 0 : a + run;
+  }
+}
 template <typename F>
 __device__ __forceinline__ void for_candidates(const RepDev& R, const int32_t* cell_row,
                                                double delta, double xi, double yi, double zi,
                                                int64_t self, F&& f) {
   const int cx = cell_axis(xi, R, 0), cy = cell_axis(yi, R, 1), cz = cell_axis(zi, R, 2);
-  const int ncx = R.nc[0], ncy = R.nc[1], ncz = R.nc[2];
-  const int zlo = ncz == 1 ? 0 : -1, zhi = ncz == 1 ? 0 : 1;
-  const int ylo = ncy == 1 ? 0 : -1, yhi = ncy == 1 ? 0 : 1;
-  const double eps = 1e-9 * R.cell_len[0];
-  for (int dz = zlo; dz <= zhi; ++dz) {
-    const int czr = cz + dz;
-    const int cz2 = czr < 0 ? czr + ncz : (czr >= ncz ? czr - ncz : czr);
-    for (int dyc = ylo; dyc <= yhi; ++dyc) {
-      const int cyr = cy + dyc;
-      int cy2, lo, hi;
-      if (ncy == 1) {
-        cy2 = 0; lo = 0; hi = ncx - 1;
-      } else if (cyr >= 0 && cyr < ncy) {
-        cy2 = cyr;
-        if (ncx == 1) { lo = 0; hi = 0; }
-        else { lo = cx - 1; hi = cx + 1; }
-      } else {
-        // across the y boundary: j's image is shifted by s*delta in x, with
-        // s = +1 going up (j in row 0) and -1 going down (j in the top row)
-        const double sd = cyr >= ncy ? delta : -delta;
-        cy2 = cyr >= ncy ? 0 : ncy - 1;
-        const double c0 = xi - sd;
-        lo = (int)floor((c0 - R.rc - eps) * R.inv_cell[0]);
-        hi = (int)floor((c0 + R.rc + eps) * R.inv_cell[0]);
-        if (hi - lo + 1 >= ncx) { lo = 0; hi = ncx - 1; }
-      }
-      // split [lo, hi] at the periodic x edge and at brick edges into runs
-      // of consecutive cells (consecutive keys)
-      int a = imod(lo, ncx);
-      int len = hi - lo + 1;
-      while (len > 0) {
-        int run = (a + len <= ncx) ? len : (ncx - a);
-        const int bend = ((a >> R.bshift) + 1) * R.brick - a;
-        run = run < bend ? run : bend;
-        const int c0 = R.seg_off + cell_key(R, a, cy2, cz2);
-        const int j0 = cell_row[c0], j1 = cell_row[c0 + run];
-        for (int j = j0; j < j1; ++j)
-          if (j != self) f(j);
-        len -= run;
-        a = a + run == ncx ? 0 : a + run;
-      }
-    }
-  }
+  const int zr = R.nc[2] == 1 ? 0 : 1, yr = R.nc[1] == 1 ? 0 : 1;
+  for (int dz = -zr; dz <= zr; ++dz)
+    for (int dyc = -yr; dyc <= yr; ++dyc)
+      for_candidates_row(R, cell_row, delta, xi, cx, cy, cz, dz, dyc, self, f);
 }
 
 // The same candidates in the same order for a particle of cell (cx, cy, cz)
