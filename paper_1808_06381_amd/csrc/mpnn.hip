@@ -46,10 +46,7 @@ __device__ __forceinline__ float bf16_round(float f) {
 }
 
 __device__ __forceinline__ uint16_t bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);   // v_cvt_pk_bf16_f32: the same rounding
 }
 
 __device__ __forceinline__ float act_in(const MpPtrs& m, float v) {
@@ -231,15 +228,10 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_heads(DevPtrs d, MpPtrs m) {
 
 // ---------------------------------------------------------------------------
 // forward with bf16 activations on the matrix cores.  A block owns MP_ROWS
-// consecutive rows; their CSR entries form one contiguous range that is
-// walked in chunks of MX_EC entries, four threads per entry (eight features
-// each).  Every product consumes h rounded to bf16, so each layer gathers the
-// 64-byte bf16 row of h_j per entry (one 16-byte load per thread) and forms
-// y_j = P h_j of the chunk on the matrix cores, rather than gathering a stored
-// FP32 y_j (twice the bytes); the product is the one that writes y for the
-// backward pass, operand for operand, so both give the same bits.  The dense
-// node products (32 x 64 and 32 x 32 per node) run as 16 x 16 x 16 bf16 MFMA
-// tiles, FP32 accumulate: wave w owns rows 16w..16w+15 of a tile.
+// consecutive rows; their CSR entries form one contiguous range.  Every product
+// consumes h rounded to bf16, so each layer gathers the 64-byte bf16 row of h_j
+// per entry and forms y_j = P h_j on the matrix cores, rather than gathering a
+// stored FP32 y_j (twice the bytes).
 // Operand layout of v_mfma_f32_16x16x16_bf16: lane l supplies
 // A[l%16][4(l/16)+i] and B[4(l/16)+i][l%16], i < 4, and receives
 // D[4(l/16)+r][l%16] in accumulator register r.
@@ -428,14 +420,205 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_encode_mx(DevPtrs d, MpPtrs m
   if (m.store_train) mx_store_py(m.w16, MP_OFF_L0 + MP_L_P, xh, MX_HS, m.y, i0);
 }
 
-// one message-passing layer l (bf16 activations): m, a and y^{l+1} (training),
-// h^{l+1} in FP32 and bf16
-// (seven waves per SIMD: P is read from LDS rather than held in registers,
-// which leaves room for seven without spills; measured at N = 8e6 against
-// six: 1184 against 1201 us.  Neither more entries per chunk (128, four
-// waves: 1722 us) nor a gather two chunks ahead (1276-1318 us) was faster.)
+// one message-passing layer l (bf16 activations): h^{l+1} in bf16, the next
+// layer's residual and product input and the heads' input
+//
+// A block owns 64 rows.  Their entries are taken in slots padded to groups of
+// four per row, sixteen slots per wave and product: lane l gathers 16 bytes of
+// the bf16 row of entry l % 16, which is the A operand of a 16 x 16 x 32 MFMA
+// as it stands, so the gathered rows never pass through LDS.  A second product
+// over (e_0, e_1, e_2, 1, zeros) and (Q, c) completes y_j + Q e_ij + c (the same
+// instruction on purpose: a 16 x 16 x 16 product accumulating straight onto
+// the result of a 16 x 16 x 32 one gave wrong sums), and since
+// register r of a lane holds entry 4 (l / 16) + r of one feature, the four
+// messages of a group are clamped and added in the lane: what goes to LDS is one
+// partial sum per group, a quarter of the messages.  The lane that will supply
+// row n's message as the next product's A operand adds n's groups, so h + relu(d
+// + U h + V m) follows from registers too (h itself by a product with the
+// identity, exact).  Two barriers per 128 groups (most tiles).
+// The earlier form (gather and messages through LDS, Q e and c on the vector
+// units) kept LDS busy 75 % and the vector units 82 % of the cycles: N = 1e6
+// 153 -> 103 us per layer, N = 8e6 1222 -> 982.  The gather of one product and the
+// columns of the next in flight (four products at a time: 126 us at N = 1e6, five
+// waves per SIMD; a row gathered by four adjacent lanes and turned through LDS: 128).
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+union MxQ {   // eight bf16
+  uint4 u;
+  bf16x8 v;
+};
+// max(y, 0) in one instruction (the median of y, 0 and infinity)
+__device__ __forceinline__ float relu(float y) {
+  return __builtin_amdgcn_fmed3f(y, 0.0f, __builtin_inff());
+}
+__device__ __forceinline__ f32x4 mx_mma32(const MxQ& a, const MxQ& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+// operand of 32 inputs: lane l holds inputs 8 (l / 16) .. + 7 of row / column
+// l % 16; W is row-major 32 x 32, output 16 nt + l % 16
+__device__ __forceinline__ MxQ mx_bw32(const uint16_t* __restrict__ w16, int off, int nt) {
+  const int lane = threadIdx.x & 63;
+  MxQ b;
+  b.u = *reinterpret_cast<const uint4*>(w16 + off + (16 * nt + (lane & 15)) * MP_H +
+                                        8 * (lane >> 4));
+  return b;
+}
+static_assert(MP_OFF_L0 % 8 == 0 && MP_L_SIZE % 8 == 0 && MP_L_U % 8 == 0 && MP_L_V % 8 == 0,
+              "16-byte aligned weight rows");
+
+constexpr int MXG = 128;            // groups of four slots per pass
+__global__ __launch_bounds__(MP_THREADS) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_mp_layer_mx(DevPtrs d, MpPtrs m, int l) {
+  if (d.ctrl->overflow) return;  // row pointers may exceed the capacity
+  __shared__ int rp[MP_ROWS + 1], gp[MP_ROWS + 1];   // first entry and group of each row
+  __shared__ uint8_t grow[MXG];                      // row of each group of the pass
+  __shared__ __align__(16) float msg[MXG * MX_FS];   // partial messages; then the output tile
+  static_assert(MP_ROWS == 64 && MP_THREADS == 256, "one wave scans the rows");
+  static_assert(MP_ROWS * MX_HS * sizeof(uint16_t) <= sizeof(float) * MXG * MX_FS, "aliased");
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int lo16 = lane & 15, hi4 = lane >> 4;
+  // tiles in XCD-contiguous ranges: the gathered h_j rows of neighbouring
+  // tiles stay in one XCD's L2
+  const int ntiles = (int)(m.rows / MP_ROWS);
+  const int tile = xcd_block(blockIdx.x, ntiles);
+  if (tile >= ntiles) return;
+  const int base = MP_OFF_L0 + l * MP_L_SIZE;
+  const int64_t i0 = (int64_t)tile * MP_ROWS;
+  if (w == 0) {
+    const int r0 = d.rowptr[i0 + lane], r1 = d.rowptr[i0 + lane + 1];
+    const int g = (r1 - r0 + 3) >> 2;
+    int inc = g;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(inc, o, 64);
+      inc += lane >= o ? up : 0;
+    }
+    rp[lane] = r0;
+    gp[lane] = inc - g;
+    if (lane == 63) {
+      rp[64] = r1;
+      gp[64] = inc;
+    }
+  }
+  const uint16_t* __restrict__ hbl = mx_hb(m, l);
+  const MxQ p0 = mx_bw32(m.w16, base + MP_L_P, 0), p1 = mx_bw32(m.w16, base + MP_L_P, 1);
+  // (Q, c) of the features: inputs 0..3, the other 28 zero
+  auto qc = [&](int k) {
+    MxQ q;
+    q.u = make_uint4(0u, 0u, 0u, 0u);
+    if (hi4 == 0) {
+      const uint16_t* qk = m.w16 + base + MP_L_Q + k * MP_FE;
+      q.u.x = (uint32_t)qk[0] | ((uint32_t)qk[1] << 16);
+      q.u.y = (uint32_t)qk[2] | ((uint32_t)m.w16[base + MP_L_C + k] << 16);
+    }
+    return q;
+  };
+  const MxQ q0 = qc(lo16), q1 = qc(16 + lo16);
+  __syncthreads();
+  const int G = gp[64];
+  const int nr = 16 * w + lo16;   // this lane's row, features 8 hi4 .. + 7
+  float acc[8];
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) acc[kk] = 0.0f;
+  for (int g0 = 0; g0 < G; g0 += MXG) {
+    if (t < MP_ROWS) {
+      const int ge = min(gp[t + 1], g0 + MXG);
+#pragma clang loop vectorize(disable) unroll(disable)
+      for (int g = max(gp[t], g0); g < ge; ++g) grow[g - g0] = (uint8_t)t;
+    }
+    __syncthreads();
+    const int ng = min(MXG, G - g0);
+    // the entry of this lane's slot of wave product c, or -1
+    auto entry = [&](int c) {
+      const int g = 4 * c + (lo16 >> 2);
+      if (g >= ng) return -1;
+      const int row = grow[g];
+      const int en = rp[row] + 4 * (g0 + g - gp[row]) + (lo16 & 3);
+      return en < rp[row + 1] ? en : -1;
+    };
+    int e = entry(w);
+    int j = e >= 0 ? d.col[e] : 0;
+    for (int c = w; 4 * c < ng; c += 4) {
+      MxQ hq, eq;
+      hq.u = make_uint4(0u, 0u, 0u, 0u);
+      eq.u = make_uint4(0u, 0u, 0u, 0u);
+      if (e >= 0) {
+        hq.u = *reinterpret_cast<const uint4*>(hbl + (int64_t)j * MP_H + 8 * hi4);
+        if (hi4 == 0) {
+          const uint2 ef = *reinterpret_cast<const uint2*>(m.efh + 4 * (int64_t)e);
+          eq.u.x = ef.x;
+          eq.u.y = (ef.y & 0xffffu) | 0x3f800000u;   // 1: the input that c multiplies
+        }
+      }
+      e = entry(c + 4);   // the next product's columns, while this one's rows arrive
+      j = e >= 0 ? d.col[e] : 0;
+      f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+      y0 = mx_mma32(hq, p0, y0);
+      y1 = mx_mma32(hq, p1, y1);
+      y0 = mx_mma32(eq, q0, y0);
+      y1 = mx_mma32(eq, q1, y1);
+      float* out = msg + (4 * c + hi4) * MX_FS + lo16;
+      out[0] = ((relu(y0[0]) + relu(y0[1])) + relu(y0[2])) + relu(y0[3]);
+      out[16] = ((relu(y1[0]) + relu(y1[1])) + relu(y1[2])) + relu(y1[3]);
+    }
+    __syncthreads();
+    const int hi = min(gp[nr + 1], g0 + MXG);
+    for (int g = max(gp[nr], g0); g < hi; ++g) {
+      const float4* mp = reinterpret_cast<const float4*>(msg + (g - g0) * MX_FS + 8 * hi4);
+      const float4 m0 = mp[0], m1 = mp[1];
+      acc[0] += m0.x; acc[1] += m0.y; acc[2] += m0.z; acc[3] += m0.w;
+      acc[4] += m1.x; acc[5] += m1.y; acc[6] += m1.z; acc[7] += m1.w;
+    }
+    __syncthreads();   // grow and msg are rewritten
+  }
+  MxQ hown, mo;
+  hown.u = *reinterpret_cast<const uint4*>(hbl + (i0 + nr) * MP_H + 8 * hi4);
+  uint32_t mw[4];
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) acc[kk] *= MP_MSG;
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    mw[kk] = (uint32_t)bf16_bits(acc[2 * kk]) | ((uint32_t)bf16_bits(acc[2 * kk + 1]) << 16);
+  mo.u = make_uint4(mw[0], mw[1], mw[2], mw[3]);
+  uint16_t* const xo = reinterpret_cast<uint16_t*>(msg);
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int k = 16 * nt + lo16;
+    // a = d + U h + V m, and h in the result's layout
+    const float bias = bf16_value(m.w16[base + MP_L_D + k]);
+    f32x4 av = {bias, bias, bias, bias}, hv = {0.f, 0.f, 0.f, 0.f};
+    av = mx_mma32(hown, mx_bw32(m.w16, base + MP_L_U, nt), av);
+    av = mx_mma32(mo, mx_bw32(m.w16, base + MP_L_V, nt), av);
+    MxQ id;   // column k of the identity: input k
+    uint32_t iw[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const int in = 8 * hi4 + 2 * kk;
+      iw[kk] = in == k ? 0x3f80u : (in + 1 == k ? 0x3f800000u : 0u);
+    }
+    id.u = make_uint4(iw[0], iw[1], iw[2], iw[3]);
+    hv = mx_mma32(hown, id, hv);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * w + 4 * hi4 + r;
+      const float a = av[r];
+      const float hn = hv[r] + (a > 0.0f ? a : 0.0f);
+      xo[row * MX_HS + k] = bf16_bits(hn);
+    }
+  }
+  __syncthreads();
+  // bf16 h^{l+1}: gathered by the next layer, read by the heads after the last
+  const int n = t >> 2, q = t & 3;
+  *reinterpret_cast<uint4*>(mx_hb(m, l + 1) + (i0 + n) * MP_H + 8 * q) =
+      *reinterpret_cast<const uint4*>(xo + n * MX_HS + 8 * q);
+}
+
+// The same layer for training, which also stores m, a and y^{l+1}: the messages
+// are formed as the backward pass forms them again from the stored y (the same
+// operations in the same order, so a message is clamped in both or in neither)
+// and summed in entry order.  The next chunk's gather is in flight while one is
+// processed.  (Seven waves per SIMD: P is read from LDS rather than held in
+// registers, which leaves room for seven without spills.)
 __global__ __launch_bounds__(MP_THREADS) __attribute__((amdgpu_waves_per_eu(7, 8)))
-void k_mp_layer_mx(DevPtrs d, MpPtrs m, int l) {
+void k_mp_layer_train(DevPtrs d, MpPtrs m, int l) {
   if (d.ctrl->overflow) return;  // row pointers may exceed the capacity
   __shared__ float Q[MP_H * MP_FE], c[MP_H], dd[MP_H];
   __shared__ __align__(16) uint16_t ps[MP_H * MX_PS];
@@ -545,11 +728,9 @@ void k_mp_layer_mx(DevPtrs d, MpPtrs m, int l) {
       xa[n * MX_AS + k] = hb16;
       xa[n * MX_AS + MP_H + k] = bf16_bits(acc[kk]);
     }
-    if (m.store_train) {
-      float4* mo = reinterpret_cast<float4*>(m.m + ((int64_t)l * rows + i) * MP_H + 8 * q);
-      mo[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-      mo[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    }
+    float4* mo = reinterpret_cast<float4*>(m.m + ((int64_t)l * rows + i) * MP_H + 8 * q);
+    mo[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    mo[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
   }
   __syncthreads();
   // a = d + U h + V m
@@ -578,15 +759,15 @@ void k_mp_layer_mx(DevPtrs d, MpPtrs m, int l) {
       // h^{l+1} is stored rounded to bf16 (the next layer's residual and
       // product input, the heads' input); its FP32 copy, the same value, is
       // for the backward pass only
-      if (m.store_train) hout[(i0 + row) * MP_H + k] = bf16_value(hnb);
-      if (m.store_train) m.a[((int64_t)l * rows + i0 + row) * MP_H + k] = a;
+      hout[(i0 + row) * MP_H + k] = bf16_value(hnb);
+      m.a[((int64_t)l * rows + i0 + row) * MP_H + k] = a;
       xa[row * MX_AS + k] = hnb;
     }
   __syncthreads();
   // bf16 h^{l+1}: gathered by the next layer, read by the heads after the last
   *reinterpret_cast<uint4*>(mx_hb(m, l + 1) + (i0 + n) * MP_H + 8 * q) =
       *reinterpret_cast<const uint4*>(xa + n * MX_AS + 8 * q);
-  if (l + 1 < MP_NL && m.store_train)
+  if (l + 1 < MP_NL)
     mx_store_py(m.w16, base + MP_L_SIZE + MP_L_P, xa, MX_AS,
                 m.y + (int64_t)(l + 1) * rows * MP_H, i0);
 }
@@ -1723,7 +1904,10 @@ hipError_t launch_mp_trunk(const DevPtrs& d, const MpPtrs& m, hipStream_t s) {
     const dim3 g((unsigned)xcd_grid((int)blocks));
     hipLaunchKernelGGL(k_mp_encode_mx, g, dim3(MP_THREADS), 0, s, d, m);
     for (int l = 0; l < MP_NL; ++l)
-      hipLaunchKernelGGL(k_mp_layer_mx, g, dim3(MP_THREADS), 0, s, d, m, l);
+      if (m.store_train)
+        hipLaunchKernelGGL(k_mp_layer_train, g, dim3(MP_THREADS), 0, s, d, m, l);
+      else
+        hipLaunchKernelGGL(k_mp_layer_mx, g, dim3(MP_THREADS), 0, s, d, m, l);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_mp_features, dim3(nb(d.rows, 256)), dim3(256), 0, s, d, m);
