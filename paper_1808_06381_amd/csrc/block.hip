@@ -16,17 +16,17 @@
 //
 // Solve: block-Jacobi preconditioned CG with one recurrence over the 3n
 // stacked unknowns of each replica (the three components are coupled), in
-// the single-reduction form of Chronopoulos & Gear (as the scalar solve),
-// stopping on the true residual ||b - A x|| <= tol ||b||.  Per iteration
-// three launches: w = A u with tile partials of (w, u); a per-replica
-// finisher that reduces (w, u), (r, u) and (r, r) together (convergence of
-// the recursive residual, then beta = gamma / gamma_old and
-// alpha = gamma / (delta - beta gamma / alpha_old)); and the vector pass
-// p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s, u = M^-1 r with
-// partials of (r, u), (r, r).  Residual rounds (start, and after the
-// recursive residual meets the tolerance): r = b - A x, u = M^-1 r,
-// p = s = 0 (so the next pass starts with p = u, s = w).  All reductions in
-// a fixed order: deterministic.
+// the single-reduction form of Chronopoulos & Gear with the residual formed
+// from its own last two values and x from a ring of the u (as the scalar
+// solve, see cg.hip), stopping on the true residual ||b - A x|| <= tol ||b||.
+// Per iteration three launches: w = A u with sub-tile partials of (w, u); a
+// per-replica finisher that reduces (w, u), (r, u) and (r, r) together
+// (convergence of the recursive residual, then beta = gamma / gamma_old,
+// alpha = gamma / (delta - beta gamma / alpha_old) and theta = alpha beta /
+// alpha_old); and the vector pass r' = r + theta (r - r_old) - alpha w,
+// u = M^-1 r' with partials of (r, u), (r, r).  Residual rounds (start, and
+// after the recursive residual meets the tolerance): r = b - A x, u = M^-1 r.
+// All reductions in a fixed order: deterministic.
 #include <hip/hip_runtime.h>
 
 #include "launch.h"
@@ -76,15 +76,20 @@ __device__ __forceinline__ double pforce(const RepDev& R, double r2, double r) {
   return 0.0;
 }
 
-// the tile's partial slots 0..2 from every thread's values (fixed order)
-// tile partial sums [(w, u), (r, u), (r, r)]: slots first .. first + N - 1
+// XCD-contiguous sub-tile of this block (or -1 past the end)
+__device__ __forceinline__ int block_sub(const DevPtrs& d) {
+  const int nsub = SUBS_PER_TILE * d.nblk;
+  const int sub = xcd_block(blockIdx.x, nsub);
+  return sub < nsub ? sub : -1;
+}
+
+// sub-tile partial sums [(w, u), (r, u), (r, r)]: slots first .. first + N - 1
 template <int N>
-__device__ __forceinline__ void tile_partials(const DevPtrs& d, int tile, int first,
-                                              double (&v)[N]) {
-  __shared__ double lds[BLOCK_THREADS / 64][N];
+__device__ __forceinline__ void sub_partials(const DevPtrs& d, int sub, int first, double (&v)[N]) {
+  __shared__ double lds[SUB_THREADS / 64][N];
   block_sum<N>(v, lds);
   if (threadIdx.x == 0) {
-    double* dst = d.partial + (int64_t)tile * NPART + first;
+    double* dst = d.partial + (int64_t)sub * NPART + first;
 #pragma unroll
     for (int k = 0; k < N; ++k) dst[k] = v[k];
   }
@@ -246,6 +251,8 @@ __global__ void k_bcg_reset(DevPtrs d, BlockPtrs bp, double tol) {
   B.state = 1;
   B.it = B.restarts = B.breakdown = 0;
   B.first = 1;
+  B.theta = 0.0;
+  B.pend = B.cbase = 0;
 }
 
 // Warm start, after the first residual round (which set ||b||^2 from x = 0
@@ -282,49 +289,63 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_bcg_zero(DevPtrs d) {
   d.x[3 * i] = d.x[3 * i + 1] = d.x[3 * i + 2] = 0.0;
 }
 
-// Entry-parallel 3 x 3 block product over a 1024-row tile (the scalar CG's
-// entry-parallel form with a block per entry): the tile's entries, one
+// Entry-parallel 3 x 3 block product over a 256-row sub-tile (the scalar CG's
+// entry-parallel form with a block per entry): the sub-tile's entries, one
 // contiguous CSR range, are striped over the block's threads, BEP per thread
 // and pass, so the column and block loads are coalesced and none waits on
 // its own row's pointers; each thread forms W_e src_j for its entries into
 // LDS, and after a barrier the thread of row i adds its row's products in
-// entry order.  The tile's own rows of src come in through LDS as
-// contiguous runs.  acc = sum_j W_ij src_j, si = src_i.  (Four lanes per row
-// walking interleaved entries took 82.5 against 74.4 us at N = 1e6.)
+// entry order.  The own rows of src come in through LDS as contiguous runs.
+// acc = sum_j W_ij src_j, si = src_i.  (Four lanes per row walking interleaved
+// entries took 82.5 us at N = 1e6, sub-tiles of 1024 rows 75, these 68.)
 constexpr int BEP = 2;
-constexpr int BCAP = BLOCK_THREADS * BEP;
+constexpr int BCAP = SUB_THREADS * BEP;
 template <class Mul>
-__device__ __forceinline__ void bep_tile(const DevPtrs& d, int tile, const double* __restrict__ src,
+__device__ __forceinline__ void bep_tile(const DevPtrs& d, int sub, const double* __restrict__ src,
                                          Mul mul, double (*prod)[BCAP], double* io,
                                          double (&acc)[3], double (&si)[3]) {
-  static_assert(ROWS_PER_BLOCK == BLOCK_THREADS, "one thread per row of the tile");
+  static_assert(SUB_ROWS == SUB_THREADS, "one thread per row of the sub-tile");
   const int t = threadIdx.x;
-  const int64_t base = (int64_t)tile * ROWS_PER_BLOCK;
+  const int64_t base = (int64_t)sub * SUB_ROWS;
   // clamped: after an overflowing fill the row pointers may pass the
   // capacity (the host discards that solve; the reads stay in bounds)
   const int cap = (int)d.nnz_cap;
   const int E0 = min(d.rowptr[base], cap);
-  const int ne = min(d.rowptr[base + ROWS_PER_BLOCK], cap) - E0;
+  const int ne = min(d.rowptr[base + SUB_ROWS], cap) - E0;
   const int64_t i = base + t;
   const int r0 = min(d.rowptr[i], cap) - E0, r1 = min(d.rowptr[i + 1], cap) - E0;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) io[t + q * BLOCK_THREADS] = src[3 * base + t + q * BLOCK_THREADS];
-  acc[0] = acc[1] = acc[2] = 0.0;
-  for (int c0 = 0; c0 < ne; c0 += BCAP) {
-    int c[BEP];
+  int c[BEP];
+  auto columns = [&](int c0) {
 #pragma unroll
     for (int k = 0; k < BEP; ++k) {
-      const int e = c0 + t + k * BLOCK_THREADS;
+      const int e = c0 + t + k * SUB_THREADS;
       c[k] = e < ne ? d.col[E0 + e] : -1;
     }
+  };
+  columns(0);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) io[t + q * SUB_THREADS] = src[3 * base + t + q * SUB_THREADS];
+  acc[0] = acc[1] = acc[2] = 0.0;
+  for (int c0 = 0; c0 < ne; c0 += BCAP) {
+    double g[BEP][3];
+    int64_t e[BEP];
 #pragma unroll
     for (int k = 0; k < BEP; ++k) {
-      if (c[k] >= 0) {
+      e[k] = c[k] >= 0 ? (int64_t)E0 + c0 + t + k * SUB_THREADS : -1;
+      if (e[k] >= 0) {
         const int64_t j = c[k];
-        const double g[3] = {src[3 * j], src[3 * j + 1], src[3 * j + 2]};
+        g[k][0] = src[3 * j];
+        g[k][1] = src[3 * j + 1];
+        g[k][2] = src[3 * j + 2];
+      }
+    }
+    columns(c0 + BCAP);   // the next pass's, while this one's rows arrive
+#pragma unroll
+    for (int k = 0; k < BEP; ++k) {
+      if (e[k] >= 0) {
         double o[3];
-        mul((int64_t)E0 + c0 + t + k * BLOCK_THREADS, g, o);
-        const int slot = t + k * BLOCK_THREADS;
+        mul(e[k], g[k], o);
+        const int slot = t + k * SUB_THREADS;
         prod[0][slot] = o[0];
         prod[1][slot] = o[1];
         prod[2][slot] = o[2];
@@ -332,10 +353,10 @@ __device__ __forceinline__ void bep_tile(const DevPtrs& d, int tile, const doubl
     }
     __syncthreads();
     const int lo = r0 > c0 ? r0 : c0, hi = r1 < c0 + BCAP ? r1 : c0 + BCAP;
-    for (int e = lo; e < hi; ++e) {
-      acc[0] += prod[0][e - c0];
-      acc[1] += prod[1][e - c0];
-      acc[2] += prod[2][e - c0];
+    for (int q = lo; q < hi; ++q) {
+      acc[0] += prod[0][q - c0];
+      acc[1] += prod[1][q - c0];
+      acc[2] += prod[2][q - c0];
     }
     __syncthreads();
   }
@@ -345,10 +366,10 @@ __device__ __forceinline__ void bep_tile(const DevPtrs& d, int tile, const doubl
   si[2] = io[3 * t + 2];
 }
 
-// three values per row of the tile to out[3 * (base + row) + k], through LDS
-// as contiguous runs (io free: every thread has read its own row)
-__device__ __forceinline__ void tile_store3(double* io, int64_t base, const double (&v)[3],
-                                            double* __restrict__ out) {
+// three values per row of the sub-tile to out[3 * (base + row) + k], through
+// LDS as contiguous runs (io free: every thread has read its own row)
+__device__ __forceinline__ void sub_store3(double* io, int64_t base, const double (&v)[3],
+                                           double* __restrict__ out) {
   const int t = threadIdx.x;
   __syncthreads();
   io[3 * t] = v[0];
@@ -356,26 +377,25 @@ __device__ __forceinline__ void tile_store3(double* io, int64_t base, const doub
   io[3 * t + 2] = v[2];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 3; ++q) out[3 * base + t + q * BLOCK_THREADS] = io[t + q * BLOCK_THREADS];
+  for (int q = 0; q < 3; ++q) out[3 * base + t + q * SUB_THREADS] = io[t + q * SUB_THREADS];
 }
 
 // mode 0: w = A u, partial (w, u)                        [iterating replicas]
-// mode 1: r = b - A x, u = M^-1 r, p = s = 0, partials (r, u), (r, r)
-//                                                          [residual round]
+// mode 1: r = b - A x, u = M^-1 r, partials (r, u), (r, r)  [residual round]
 // FP32: the off-diagonal blocks of mode 0 from their FP32 copies (the
 // residual round always takes the FP64 blocks, so the stopping test is the
 // FP64 residual)
 template <bool FP32>
-__global__ __launch_bounds__(BLOCK_THREADS) void k_bcg_spmv(DevPtrs d, BlockPtrs bp, int mode) {
-  const int tile = xcd_block(blockIdx.x, d.nblk);
-  if (tile >= d.nblk) return;
-  const BcgRep& B = bp.bcg[d.blk_rep[tile]];
+__global__ __launch_bounds__(SUB_THREADS) void k_bcg_spmv(DevPtrs d, BlockPtrs bp, int mode) {
+  const int sub = block_sub(d);
+  if (sub < 0) return;
+  const BcgRep& B = bp.bcg[d.blk_rep[sub / SUBS_PER_TILE]];
   if (B.state != (mode == 0 ? 0 : 1)) return;
   __shared__ double prod[3][BCAP];
-  __shared__ double io[3 * ROWS_PER_BLOCK];
+  __shared__ double io[3 * SUB_ROWS];
   const double* src = mode == 0 ? d.u : d.x;
   double acc[3], si[3];
-  bep_tile(d, tile, src,
+  bep_tile(d, sub, src,
            [&](int64_t e, const double (&g)[3], double (&o)[3]) {
              if constexpr (FP32)
                sym_mul_f(bp.bvalf + 6 * e, g, o);
@@ -383,7 +403,7 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_bcg_spmv(DevPtrs d, BlockPtrs
                sym_mul(bp.bval + 6 * e, g, o);
            },
            prod, io, acc, si);
-  const int64_t base = (int64_t)tile * ROWS_PER_BLOCK;
+  const int64_t base = (int64_t)sub * SUB_ROWS;
   const int64_t i = base + threadIdx.x;
   double dg[3];
   sym_mul(bp.bdiag + 6 * i, si, dg);
@@ -392,112 +412,162 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_bcg_spmv(DevPtrs d, BlockPtrs
   for (int k = 0; k < 3; ++k) own[k] = dg[k] + acc[k];
   if (mode == 0) {
     double v[1] = {(si[0] * own[0] + si[1] * own[1]) + si[2] * own[2]};
-    tile_store3(io, base, own, d.w);
-    tile_partials<1>(d, tile, 0, v);
+    sub_store3(io, base, own, d.w);
+    sub_partials<1>(d, sub, 0, v);
   } else {
     const double r[3] = {d.b[3 * i] - own[0], d.b[3 * i + 1] - own[1], d.b[3 * i + 2] - own[2]};
     double z[3];
     sym_mul(bp.binv + 6 * i, r, z);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      d.r[3 * i + k] = r[k];
-      if (!bp.learned) d.u[3 * i + k] = z[k];  // learned: k_bcg_apply forms u
-      d.p[3 * i + k] = 0.0;
-      d.s[3 * i + k] = 0.0;
-    }
+    sub_store3(io, base, r, d.r);
+    if (!bp.learned) sub_store3(io, base, z, d.u);  // learned: k_bcg_apply forms u
     double v[2] = {(r[0] * z[0] + r[1] * z[1]) + r[2] * z[2], (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2]};
-    tile_partials<2>(d, tile, 1, v);
+    sub_partials<2>(d, sub, 1, v);
   }
 }
 
-// p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s, u = M^-1 r,
-// partials (r, u), (r, r).  The vector updates run element-parallel over
-// the tile's 3 * 1024 consecutive doubles (coalesced); the new r goes
-// through LDS to one thread per row for the 3 x 3 block product, and u
-// back through LDS to coalesced stores.
-__global__ __launch_bounds__(BLOCK_THREADS) void k_bcg_vec(DevPtrs d, BlockPtrs bp) {
-  const int tile = xcd_block(blockIdx.x, d.nblk);
-  if (tile >= d.nblk) return;
-  const BcgRep& B = bp.bcg[d.blk_rep[tile]];
+// d.s = r + theta (r - d.s) - alpha w (the new residual over the one before
+// r; the host swaps them), u = M^-1 of it, partials (r, u), (r, r).  The update
+// runs element-parallel over the sub-tile's 768 consecutive doubles
+// (coalesced); the new r goes through LDS to one thread per row for the 3 x 3
+// block product, and u back through LDS to coalesced stores.  168 B per row
+// (312 with p, s and x kept, 47 us at N = 1e6; 27 us now).
+__global__ __launch_bounds__(SUB_THREADS) void k_bcg_vec(DevPtrs d, BlockPtrs bp) {
+  const int sub = block_sub(d);
+  if (sub < 0) return;
+  const BcgRep& B = bp.bcg[d.blk_rep[sub / SUBS_PER_TILE]];
   if (B.state != 0) return;
-  __shared__ double rs[3 * ROWS_PER_BLOCK];
-  static_assert(ROWS_PER_BLOCK == BLOCK_THREADS, "one row per thread in the block product");
-  const double a = B.alpha, be = B.beta;
-  const int64_t base = (int64_t)tile * 3 * ROWS_PER_BLOCK;
+  __shared__ double rs[3 * SUB_ROWS];
+  const double al = B.alpha, th = B.theta;
+  const int64_t base = (int64_t)sub * SUB_ROWS;
   const int t = threadIdx.x;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const int le = q * BLOCK_THREADS + t;
-    const int64_t e = base + le;
-    const double pk = d.u[e] + be * d.p[e];
-    const double sk = d.w[e] + be * d.s[e];
-    d.p[e] = pk;
-    d.s[e] = sk;
-    d.x[e] += a * pk;
-    const double rk = d.r[e] - a * sk;
-    d.r[e] = rk;
+    const int le = q * SUB_THREADS + t;
+    const int64_t e = 3 * base + le;
+    const double r0 = d.r[e];
+    const double rm = th != 0.0 ? d.s[e] : r0;   // a first iteration: d.s is not read
+    const double rk = (r0 + th * (r0 - rm)) - al * d.w[e];
+    d.s[e] = rk;
     rs[le] = rk;
   }
   __syncthreads();
-  const int64_t i = (int64_t)tile * ROWS_PER_BLOCK + t;
   const double r[3] = {rs[3 * t], rs[3 * t + 1], rs[3 * t + 2]};
   double z[3];
-  sym_mul(bp.binv + 6 * i, r, z);
+  sym_mul(bp.binv + 6 * (base + t), r, z);
   double v[2] = {(r[0] * z[0] + r[1] * z[1]) + r[2] * z[2], (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2]};
-  __syncthreads();  // every row has read its r: rs now takes u
-  rs[3 * t] = z[0];
-  rs[3 * t + 1] = z[1];
-  rs[3 * t + 2] = z[2];
-  __syncthreads();
-  if (!bp.learned)  // learned: k_bcg_apply forms u
-#pragma unroll
-    for (int q = 0; q < 3; ++q) d.u[base + q * BLOCK_THREADS + t] = rs[q * BLOCK_THREADS + t];
-  tile_partials<2>(d, tile, 1, v);
+  if (!bp.learned) sub_store3(rs, base, z, d.u);  // learned: k_bcg_apply forms u
+  sub_partials<2>(d, sub, 1, v);
 }
 
 // the learned preconditioner: u = M^-1 r with the stored blocks (M_ii
 // symmetric FP64, M_ij row-major FP32), partial (r, u) into slot 1 (over the
 // (r, B r) the vector pass or residual round left there).  mode 0 after a
 // vector pass, 1 in a residual round.  Entry-parallel as k_bcg_spmv.
-__global__ __launch_bounds__(BLOCK_THREADS) void k_bcg_apply(DevPtrs d, BlockPtrs bp, int mode) {
-  const int tile = xcd_block(blockIdx.x, d.nblk);
-  if (tile >= d.nblk) return;
-  const BcgRep& B = bp.bcg[d.blk_rep[tile]];
+__global__ __launch_bounds__(SUB_THREADS) void k_bcg_apply(DevPtrs d, BlockPtrs bp, int mode) {
+  const int sub = block_sub(d);
+  if (sub < 0) return;
+  const BcgRep& B = bp.bcg[d.blk_rep[sub / SUBS_PER_TILE]];
   if (B.state != (mode == 0 ? 0 : 1)) return;
   __shared__ double prod[3][BCAP];
-  __shared__ double io[3 * ROWS_PER_BLOCK];
+  __shared__ double io[3 * SUB_ROWS];
   double acc[3], ri[3];
-  bep_tile(d, tile, d.r,
+  bep_tile(d, sub, d.r,
            [&](int64_t e, const double (&g)[3], double (&o)[3]) { full_mul(bp.xo + 9 * e, g, o); },
            prod, io, acc, ri);
-  const int64_t base = (int64_t)tile * ROWS_PER_BLOCK;
-  const int64_t i = base + threadIdx.x;
+  const int64_t base = (int64_t)sub * SUB_ROWS;
   double dg[3];
-  sym_mul(bp.xd + 6 * i, ri, dg);
+  sym_mul(bp.xd + 6 * (base + threadIdx.x), ri, dg);
   double u[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) u[k] = dg[k] + acc[k];
   double v[1] = {(ri[0] * u[0] + ri[1] * u[1]) + ri[2] * u[2]};
-  tile_store3(io, base, u, d.u);
-  tile_partials<1>(d, tile, 1, v);
+  sub_store3(io, base, u, d.u);
+  sub_partials<1>(d, sub, 1, v);
 }
 
-// one block per replica: the tile partials [(w, u), (r, u), (r, r)] in tile
-// order, then
+// The ring's pending terms into x and the direction p (as k_cg_flush, one
+// recurrence per replica).  forced = 1: iterating replicas, the ring full;
+// forced = 0: before a residual round, the replicas that wait for it.  d.u:
+// the first slot.
+__global__ __launch_bounds__(SUB_THREADS) void k_bcg_flush(DevPtrs d, BlockPtrs bp, int forced) {
+  const int sub = block_sub(d);
+  if (sub < 0) return;
+  const int rid = d.blk_rep[sub / SUBS_PER_TILE];
+  const BcgRep& B = bp.bcg[rid];
+  const int m = B.pend;
+  if (B.state != (forced ? 0 : 1) || m == 0) return;
+  static_assert(U_RING <= 64, "one lane per term");
+  __shared__ double h[U_RING][2], hp[2];
+  const int t = threadIdx.x;
+  if (t < 64) {
+    int slot = B.cbase + t;
+    slot = slot >= d.ring ? slot - d.ring : slot;
+    const double* hs = d.hist + ((int64_t)rid * U_RING + slot) * 3;
+    const double ga = t < m ? hs[2] : 1.0;
+    double s = t < m ? hs[0] * ga : 0.0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double up = __shfl_down(s, o, 64);
+      s += t + o < 64 ? up : 0.0;
+    }
+    const double last = __shfl(ga, m - 1, 64);
+    if (t < m) {
+      h[t][0] = s / ga;
+      h[t][1] = last / ga;
+    }
+    if (t == 0) {
+      hp[0] = hs[1] * (s / ga);
+      hp[1] = hs[1] * (last / ga);
+    }
+  }
+  __syncthreads();
+  const int64_t base = (int64_t)sub * SUB_ROWS * 3, ring = 3 * d.rows;
+  double ax[3] = {0.0, 0.0, 0.0}, ap[3] = {0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int j = 0; j < m; ++j) {  // independent loads: 24 in flight per lane
+    int slot = B.cbase + j;
+    slot = slot >= d.ring ? slot - d.ring : slot;
+    const double c = h[j][0], dd = h[j][1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double uj = __builtin_nontemporal_load(d.u + slot * ring + base + q * SUB_THREADS + t);
+      ax[q] += c * uj;
+      ap[q] += dd * uj;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int64_t e = base + q * SUB_THREADS + t;
+    if (hp[1] != 0.0) {  // a direction from before the ring's first term
+      const double p0 = d.p[e];
+      ax[q] += hp[0] * p0;
+      ap[q] += hp[1] * p0;
+    }
+    d.x[e] += ax[q];
+    if (forced) d.p[e] = ap[q];
+  }
+}
+
+// one block per replica: the sub-tile partials [(w, u), (r, u), (r, r)] in a
+// fixed order, then
 //   mode 0 (after w = A u):   convergence of the recursive residual (-> a
 //                             residual round), else beta and alpha of the
 //                             next vector pass
 //   mode 2 (residual round):  ||b||^2 on the first round; done if the true
 //                             residual meets the tolerance, else (re)start
-__global__ __launch_bounds__(256) void k_bcg_finish(DevPtrs d, BlockPtrs bp, int mode) {
+// `slot` is the ring slot of the u just multiplied (mode 0) or written (mode
+// 2); `flushed` (mode 0): the terms before it were added to x.
+constexpr int BFIN = 1024;
+__global__ __launch_bounds__(BFIN) void k_bcg_finish(DevPtrs d, BlockPtrs bp, int mode, int slot,
+                                                     int flushed) {
   const int rid = blockIdx.x;
   BcgRep& B = bp.bcg[rid];
   if (B.state != (mode == 2 ? 1 : 0)) return;
   const RepDev& R = d.rep[rid];
-  __shared__ double lds[4][3];
+  __shared__ double lds[BFIN / 64][3];
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int t = threadIdx.x; t < R.nblk; t += blockDim.x) {
-    const double* src = d.partial + (int64_t)(R.blk_off + t) * NPART;
+  for (int t = threadIdx.x; t < SUBS_PER_TILE * R.nblk; t += blockDim.x) {
+    const double* src = d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off + t) * NPART;
     acc[0] += src[0];
     acc[1] += src[1];
     acc[2] += src[2];
@@ -511,33 +581,49 @@ __global__ __launch_bounds__(256) void k_bcg_finish(DevPtrs d, BlockPtrs bp, int
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
-  double tot[3];
+  double tot[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-  for (int k = 0; k < 3; ++k) tot[k] = ((lds[0][k] + lds[1][k]) + lds[2][k]) + lds[3][k];
+  for (int w = 0; w < BFIN / 64; ++w)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tot[k] += lds[w][k];
   const double delta = tot[0], gamma = tot[1];
   if (mode == 0) {
+    if (flushed) {
+      B.pend = 0;
+      B.cbase = slot;
+    }
     B.rr = tot[2];
     if (tot[2] <= B.tol2 * B.bb) {
       B.state = 1;
       return;
     }
-    double beta = 0.0, den = delta;
+    double beta = 0.0, bal = 0.0;   // beta, beta / the previous alpha
     if (!B.first) {
       beta = gamma / B.rz;
-      den = delta - beta * gamma / B.alpha;
+      bal = beta / B.alpha;
     }
+    const double den = delta - bal * gamma;
     if (!(den > 0.0) || !(gamma > 0.0)) {
       B.breakdown = 1;
       B.state = 2;
       return;
     }
+    const double al = gamma / den;
+    double* hs = d.hist + ((int64_t)rid * U_RING + slot) * 3;
+    hs[0] = al;
+    hs[1] = beta;
+    hs[2] = gamma;
+    B.pend += 1;
     B.beta = beta;
-    B.alpha = gamma / den;
+    B.theta = al * bal;
+    B.alpha = al;
     B.rz = gamma;
     B.first = 0;
     B.it += 1;
   } else {
     if (B.bb < 0.0) B.bb = tot[2];
+    B.pend = 0;
+    B.cbase = slot;
     B.rr = tot[2];
     if (tot[2] <= B.tol2 * B.bb) {
       B.state = 2;
@@ -593,23 +679,40 @@ hipError_t launch_bcg_warm(const DevPtrs& d, const BlockPtrs& bp, const int64_t*
   hipLaunchKernelGGL(k_bcg_rearm, dim3((d.nrep + 255) / 256), dim3(256), 0, s, d, bp);
   return hipGetLastError();
 }
-hipError_t launch_bcg_residual(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s) {
-  hipLaunchKernelGGL(k_bcg_spmv<false>, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, bp, 1);
-  if (bp.learned)
-    hipLaunchKernelGGL(k_bcg_apply, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, bp, 1);
-  hipLaunchKernelGGL(k_bcg_finish, dim3(d.nrep), dim3(256), 0, s, d, bp, 2);
+hipError_t launch_bcg_flush(const DevPtrs& d, const BlockPtrs& bp, int forced, hipStream_t s) {
+  hipLaunchKernelGGL(k_bcg_flush, dim3(xcd_grid(SUBS_PER_TILE * d.nblk)), dim3(SUB_THREADS), 0, s, d,
+                     bp, forced);
+  return hipGetLastError();
+}
+hipError_t launch_bcg_residual(const DevPtrs& d, const BlockPtrs& bp, int slot, hipStream_t s) {
+  const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(SUB_THREADS);
+  hipLaunchKernelGGL(k_bcg_spmv<false>, g, b, 0, s, d, bp, 1);
+  if (bp.learned) hipLaunchKernelGGL(k_bcg_apply, g, b, 0, s, d, bp, 1);
+  hipLaunchKernelGGL(k_bcg_finish, dim3(d.nrep), dim3(BFIN), 0, s, d, bp, 2, slot, 0);
   return hipGetLastError();
 }
 
-hipError_t launch_bcg_iteration(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s) {
-  if (bp.fp32)
-    hipLaunchKernelGGL(k_bcg_spmv<true>, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, bp, 0);
-  else
-    hipLaunchKernelGGL(k_bcg_spmv<false>, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, bp, 0);
-  hipLaunchKernelGGL(k_bcg_finish, dim3(d.nrep), dim3(256), 0, s, d, bp, 0);
-  hipLaunchKernelGGL(k_bcg_vec, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, bp);
-  if (bp.learned)
-    hipLaunchKernelGGL(k_bcg_apply, dim3(xcd_grid(d.nblk)), dim3(BLOCK_THREADS), 0, s, d, bp, 0);
+// w = A u and the scalars (u in ring slot `slot`)
+hipError_t launch_bcg_product(const DevPtrs& d, const BlockPtrs& bp, int slot, int flushed,
+                              hipStream_t s) {
+  const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(SUB_THREADS);
+  if (bp.fp32) hipLaunchKernelGGL(k_bcg_spmv<true>, g, b, 0, s, d, bp, 0);
+  else hipLaunchKernelGGL(k_bcg_spmv<false>, g, b, 0, s, d, bp, 0);
+  hipLaunchKernelGGL(k_bcg_finish, dim3(d.nrep), dim3(BFIN), 0, s, d, bp, 0, slot, flushed);
+  return hipGetLastError();
+}
+
+// the new residual over d.s and, without the learned preconditioner, u
+hipError_t launch_bcg_vec(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s) {
+  hipLaunchKernelGGL(k_bcg_vec, dim3(xcd_grid(SUBS_PER_TILE * d.nblk)), dim3(SUB_THREADS), 0, s, d,
+                     bp);
+  return hipGetLastError();
+}
+
+// u = M^-1 r of the learned preconditioner
+hipError_t launch_bcg_apply(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s) {
+  hipLaunchKernelGGL(k_bcg_apply, dim3(xcd_grid(SUBS_PER_TILE * d.nblk)), dim3(SUB_THREADS), 0, s, d,
+                     bp, 0);
   return hipGetLastError();
 }
 

@@ -138,7 +138,10 @@ struct BcgRep {         // per-replica scalars of the block CG (3n stacked unkno
   int32_t restarts;
   int32_t breakdown;
   int32_t first;        // 1: the next vector pass starts the recurrences (beta = 0)
+  int32_t pend;         // ring terms not yet added to x, from slot cbase
+  int32_t cbase;
   int32_t pad0;
+  double theta;         // alpha beta / alpha of the previous iteration
 };
 struct BlockPtrs {
   double* bval;         // -W_ij per CSR entry: xx, xy, xz, yy, yz, zz
@@ -160,10 +163,14 @@ struct BlockPtrs {
 };
 hipError_t launch_pair_block(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s);
 hipError_t launch_bcg_reset(const DevPtrs& d, const BlockPtrs& bp, double tol, hipStream_t s);
-hipError_t launch_bcg_residual(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s);
+hipError_t launch_bcg_residual(const DevPtrs& d, const BlockPtrs& bp, int slot, hipStream_t s);
+hipError_t launch_bcg_flush(const DevPtrs& d, const BlockPtrs& bp, int forced, hipStream_t s);
 hipError_t launch_bcg_warm(const DevPtrs& d, const BlockPtrs& bp, const int64_t* id_off,
                            hipStream_t s);
-hipError_t launch_bcg_iteration(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s);
+hipError_t launch_bcg_product(const DevPtrs& d, const BlockPtrs& bp, int slot, int flushed,
+                              hipStream_t s);
+hipError_t launch_bcg_vec(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s);
+hipError_t launch_bcg_apply(const DevPtrs& d, const BlockPtrs& bp, hipStream_t s);
 hipError_t launch_block_export(const DevPtrs& d, const BlockPtrs& bp, const int64_t* id_off,
                                int64_t* rows, int64_t* cols, double* vals, double* diag,
                                double* rhs, hipStream_t s);

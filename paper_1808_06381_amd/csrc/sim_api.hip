@@ -837,12 +837,14 @@ static int bcg_solve(sim_t* s, double tol, bool warm, sim_stats* st) {
   HIPCHK(hipMemcpyAsync(s->ctrl_h, s->d.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
   if (s->ctrl_h->overflow) return SIM_EOVERFLOW_INTERNAL;
+  s->ring = sim_t::CgRing();
   HIPCHK(launch_bcg_reset(s->d, s->bp, tol, s->stream));
-  HIPCHK(launch_bcg_residual(s->d, s->bp, s->stream));
+  HIPCHK(launch_bcg_residual(cg_view(s), s->bp, 0, s->stream));
   if (warm) {
     HIPCHK(launch_bcg_warm(s->d, s->bp, s->id_off_d, s->stream));
-    HIPCHK(launch_bcg_residual(s->d, s->bp, s->stream));
+    HIPCHK(launch_bcg_residual(cg_view(s), s->bp, 0, s->stream));
   }
+  bool flushed = false;  // the ring was emptied since the last product
   const int maxit = cg_maxit(s);
   int chunk = std::max(4, std::min(32, s->last_iters > 0 ? s->last_iters : 8));
   int status = SIM_OK;
@@ -878,8 +880,24 @@ static int bcg_solve(sim_t* s, double tol, bool warm, sim_stats* st) {
       }
     }
     const int k = std::min(chunk, maxit - itmax);
-    for (int q = 0; q < k; ++q) HIPCHK(launch_bcg_iteration(s->d, s->bp, s->stream));
-    HIPCHK(launch_bcg_residual(s->d, s->bp, s->stream));
+    for (int q = 0; q < k; ++q) {
+      DevPtrs dk = cg_view(s);
+      HIPCHK(launch_bcg_product(dk, s->bp, s->ring.slot, flushed, s->stream));
+      // the ring holds the slot just multiplied and those before it; the
+      // vector pass writes one more
+      flushed = ++s->ring.used == s->d.ring - 1;
+      if (flushed) {
+        HIPCHK(launch_bcg_flush(s->d, s->bp, 1, s->stream));
+        s->ring.used = 0;
+      }
+      s->ring.slot = s->ring.slot + 1 == s->d.ring ? 0 : s->ring.slot + 1;
+      dk.u = cg_view(s).u;
+      HIPCHK(launch_bcg_vec(dk, s->bp, s->stream));
+      std::swap(s->ring.r, s->ring.s);
+      if (s->bp.learned) HIPCHK(launch_bcg_apply(cg_view(s), s->bp, s->stream));
+    }
+    HIPCHK(launch_bcg_flush(s->d, s->bp, 0, s->stream));  // x complete where a round is pending
+    HIPCHK(launch_bcg_residual(cg_view(s), s->bp, s->ring.slot, s->stream));
     chunk = 8;
   }
   int itmax = 0, restarts = 0;
@@ -1137,8 +1155,8 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   // least 16.  Step times with 16 / 32 / 64 slots: N = 1e3 (ten steps, Jacobi)
   // 12.2 / 12.2 / 12.0 ms, N = 1e5 (two, learned) 2.52 / 2.51 / 2.47, N = 1e6
   // 4.07 / 4.00 / 3.99; N = 8e6 29.2 with 16 and 32 (29.8 with 8, 31.0 with 4)
-  d.ring = s->block ? 1 : (int32_t)std::min<int64_t>(
-                              U_RING, std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
+  d.ring = (int32_t)std::min<int64_t>(U_RING,
+                                      std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
   const size_t slots = d.ring;
   ALLOC(d.u, sizeof(double) * 3 * rows * slots);
   if (!s->block && !s->ic0 && s->rows <= FUSED_ROWS) {

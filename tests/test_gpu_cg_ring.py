@@ -116,3 +116,27 @@ def test_graph_steps_past_the_ring_bitwise_equal_eager():
             out.append(sim.state()[:2] + (its,))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
     assert out[0][2] == out[1][2] and max(its) > 128
+
+
+@pytest.mark.parametrize("pc", ["jacobi", "learned"])
+@pytest.mark.parametrize("gamma0", [1e-1, 1e-3])
+def test_block_solves_longer_than_the_ring(pc, gamma0):
+    """The block system's ring, alone and in a batch with a replica that
+    finishes early; the same bound with the stacked residual."""
+    cfgs = [dict(stiff(700, gamma0, 6), friction_par=2.0, friction_perp=0.5, stream=0),
+            dict(inputs.cube_params(500, 0.2, seed=7), gamma0=50.0, friction_par=0.5,
+                 friction_perp=1.5, stream=1)]
+    pos = [inputs.uniform_positions(c["n"], c["box"], 70 + r) for r, c in enumerate(cfgs)]
+    b = [np.random.default_rng(r).normal(size=(c["n"], 3)) for r, c in enumerate(cfgs)]
+    tol = 1e-10
+    with S.Sim(cfgs, np.concatenate(pos), tol=tol, precond=pc) as sim:
+        if pc == "learned":
+            sim.set_weights(precond.block_params(precond.load(WEIGHTS)))
+        v, st = sim.solve(np.concatenate(b))
+    for c, p, bb, vv in zip(cfgs, pos, b, np.split(v, [cfgs[0]["n"]])):
+        A = oracle.block_dense(oracle.build_block_system(c, p, c["friction_par"], c["friction_perp"]))
+        x = np.linalg.solve(A, bb.reshape(-1))
+        err = np.linalg.norm(vv.reshape(-1) - x) / np.linalg.norm(x)
+        assert err <= np.linalg.cond(A) * tol, (err, st)
+    if gamma0 < 1e-2 and not st["fallback"] and pc == "jacobi":
+        assert max(st["iters"]) > 128
