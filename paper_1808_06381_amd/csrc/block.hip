@@ -556,22 +556,22 @@ __global__ __launch_bounds__(SUB_THREADS) void k_bcg_flush(DevPtrs d, BlockPtrs 
 //   mode 2 (residual round):  ||b||^2 on the first round; done if the true
 //                             residual meets the tolerance, else (re)start
 // `slot` is the ring slot of the u just multiplied (mode 0) or written (mode
-// 2); `flushed` (mode 0): the terms before it were added to x.
-constexpr int BFIN = 1024;
-__global__ __launch_bounds__(BFIN) void k_bcg_finish(DevPtrs d, BlockPtrs bp, int mode, int slot,
-                                                     int flushed) {
-  const int rid = blockIdx.x;
-  BcgRep& B = bp.bcg[rid];
-  if (B.state != (mode == 2 ? 1 : 0)) return;
-  const RepDev& R = d.rep[rid];
+// 2); `flushed` (mode 0): the terms before it were added to x.  Several blocks
+// share a large replica as in k_cg_finish (one block of 1024 threads took 12.5
+// us at N = 1e6, now 6.5).
+constexpr int BFIN = 256;
+
+// sum of `count` slots from `first` in a fixed order, in tot (LDS)
+template <bool SHARED>
+__device__ __forceinline__ void block_slots(const double* first, int count, double* tot) {
   __shared__ double lds[BFIN / 64][3];
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int t = threadIdx.x; t < SUBS_PER_TILE * R.nblk; t += blockDim.x) {
-    const double* src = d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off + t) * NPART;
-    acc[0] += src[0];
-    acc[1] += src[1];
-    acc[2] += src[2];
-  }
+  for (int t = threadIdx.x; t < count; t += BFIN)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double* src = first + (int64_t)t * NPART + k;
+      acc[k] += SHARED ? load_shared(src) : *src;
+    }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 3; ++k) acc[k] = wave_sum(acc[k]);
@@ -580,12 +580,35 @@ __global__ __launch_bounds__(BFIN) void k_bcg_finish(DevPtrs d, BlockPtrs bp, in
     for (int k = 0; k < 3; ++k) lds[wave][k] = acc[k];
   }
   __syncthreads();
+  if (threadIdx.x < 3) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < BFIN / 64; ++w) s += lds[w][threadIdx.x];
+    tot[threadIdx.x] = s;
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(BFIN) void k_bcg_finish(DevPtrs d, BlockPtrs bp, int mode, int slot,
+                                                     int flushed) {
+  const int b = blockIdx.x;
+  const int rid = d.fin_rep[b];
+  BcgRep& B = bp.bcg[rid];
+  if (B.state != (mode == 2 ? 1 : 0)) return;
+  const RepDev& R = d.rep[rid];
+  __shared__ double tot[3];
+  const int nsub = SUBS_PER_TILE * R.nblk;
+  const double* part = d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART;
+  if (R.fin_cnt > 1) {
+    const int s0 = (b - R.fin_off) * L1_SUBS;
+    block_slots<false>(part + (int64_t)s0 * NPART, min(L1_SUBS, nsub - s0), tot);
+    if (threadIdx.x < 3) store_shared(d.partial2 + (int64_t)b * NPART + threadIdx.x, tot[threadIdx.x]);
+    if (!last_block(d.fin_ticket + rid, R.fin_cnt)) return;
+    block_slots<true>(d.partial2 + (int64_t)R.fin_off * NPART, R.fin_cnt, tot);
+  } else {
+    block_slots<false>(part, nsub, tot);
+  }
   if (threadIdx.x != 0) return;
-  double tot[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-  for (int w = 0; w < BFIN / 64; ++w)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) tot[k] += lds[w][k];
   const double delta = tot[0], gamma = tot[1];
   if (mode == 0) {
     if (flushed) {
@@ -688,7 +711,7 @@ hipError_t launch_bcg_residual(const DevPtrs& d, const BlockPtrs& bp, int slot, 
   const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(SUB_THREADS);
   hipLaunchKernelGGL(k_bcg_spmv<false>, g, b, 0, s, d, bp, 1);
   if (bp.learned) hipLaunchKernelGGL(k_bcg_apply, g, b, 0, s, d, bp, 1);
-  hipLaunchKernelGGL(k_bcg_finish, dim3(d.nrep), dim3(BFIN), 0, s, d, bp, 2, slot, 0);
+  hipLaunchKernelGGL(k_bcg_finish, dim3(d.fin_total), dim3(BFIN), 0, s, d, bp, 2, slot, 0);
   return hipGetLastError();
 }
 
@@ -698,7 +721,7 @@ hipError_t launch_bcg_product(const DevPtrs& d, const BlockPtrs& bp, int slot, i
   const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(SUB_THREADS);
   if (bp.fp32) hipLaunchKernelGGL(k_bcg_spmv<true>, g, b, 0, s, d, bp, 0);
   else hipLaunchKernelGGL(k_bcg_spmv<false>, g, b, 0, s, d, bp, 0);
-  hipLaunchKernelGGL(k_bcg_finish, dim3(d.nrep), dim3(BFIN), 0, s, d, bp, 0, slot, flushed);
+  hipLaunchKernelGGL(k_bcg_finish, dim3(d.fin_total), dim3(BFIN), 0, s, d, bp, 0, slot, flushed);
   return hipGetLastError();
 }
 

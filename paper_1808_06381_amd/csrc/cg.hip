@@ -742,9 +742,10 @@ __device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, 
 
 // Sum `count` partial slots starting at `first` in a fixed order (thread t
 // takes slots t, t + blockDim, ...; then the wave and block trees).  Totals
-// in tot (LDS), valid for every thread.
-__device__ __forceinline__ void sum_slots(const double* __restrict__ first, int count,
-                                          double* tot) {
+// in tot (LDS), valid for every thread.  SHARED: slots that other blocks of
+// this launch wrote.
+template <bool SHARED = false>
+__device__ __forceinline__ void sum_slots(const double* first, int count, double* tot) {
   __shared__ double lds[FINISH_THREADS / 64][9];
   double acc[9];
 #pragma unroll
@@ -752,8 +753,7 @@ __device__ __forceinline__ void sum_slots(const double* __restrict__ first, int 
   for (int t = threadIdx.x; t < count; t += blockDim.x) {
     const double* src = first + (int64_t)t * NPART;
 #pragma unroll
-    for (int k = 0; k < 9; ++k)
-      acc[k] += src[k];
+    for (int k = 0; k < 9; ++k) acc[k] += SHARED ? load_shared(src + k) : src[k];
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -850,21 +850,6 @@ __device__ __forceinline__ bool finish_work(const CgRep& c, int mode) {
          (mode == 3 && c.check) || (mode == 4 && c.run);
 }
 
-// First level of a large replica's reduction: block b sums L1_SUBS of the
-// replica's sub-tile partials into partial2[b].
-__global__ __launch_bounds__(FINISH_THREADS) void k_cg_reduce1(DevPtrs d, int mode) {
-  const int b = blockIdx.x;
-  const int rid = d.l1_rep[b];
-  const RepDev& R = d.rep[rid];
-  if (!finish_work(d.cg[rid], mode)) return;
-  const int s0 = (b - R.l1_off) * L1_SUBS;
-  const int nsub = SUBS_PER_TILE * R.nblk;
-  const int cnt = nsub - s0 < L1_SUBS ? nsub - s0 : L1_SUBS;
-  __shared__ double tot[9];
-  sum_slots(d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off + s0) * NPART, cnt, tot);
-  if (threadIdx.x < 9) d.partial2[(int64_t)b * NPART + threadIdx.x] = tot[threadIdx.x];
-}
-
 // words of the per-replica state, as copied between memory and LDS
 constexpr int CG_WORDS = sizeof(CgRep) / 8;
 __device__ __forceinline__ void copy_state(CgRep* dst, const CgRep* src) {
@@ -873,13 +858,17 @@ __device__ __forceinline__ void copy_state(CgRep* dst, const CgRep* src) {
         reinterpret_cast<const uint64_t*>(src)[threadIdx.x];
 }
 
-// One block per replica: its sub-tile partials (or, for a large replica,
-// the first-level sums) in a fixed order, then the recurrences.  `from`: the
-// state to advance into d.cg (d.cg itself, or the other copy after an odd
-// number of fused iterations).
+// Sub-tile partials in a fixed order, then the recurrences.  A replica of few
+// sub-tiles is one block's work.  Of a larger one, block b sums L1_SUBS
+// sub-tiles into partial2[b], and the last block to finish (last_block) adds
+// those sums in order and advances: one launch of 7.2 us at N = 1e6 where two
+// of 4.6 and 4.7 were.  `from`: the state to advance into
+// d.cg (d.cg itself, or the other copy after an odd number of fused
+// iterations; small handles only, so one block).
 __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode, int slot,
                                                               int flushed, const CgRep* from) {
-  const int rid = blockIdx.x;
+  const int b = blockIdx.x;
+  const int rid = d.fin_rep[b];
   const RepDev& R = d.rep[rid];
   CgRep& c = d.cg[rid];
   if (from != d.cg) {
@@ -888,11 +877,18 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mod
   }
   if (!finish_work(c, mode)) return;
   __shared__ double tot[9];
-  if (R.l1_cnt > 0)
-    sum_slots(d.partial2 + (int64_t)R.l1_off * NPART, R.l1_cnt, tot);
-  else
-    sum_slots(d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART, SUBS_PER_TILE * R.nblk,
-              tot);
+  const int nsub = SUBS_PER_TILE * R.nblk;
+  const double* part = d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART;
+  if (R.fin_cnt > 1) {
+    const int s0 = (b - R.fin_off) * L1_SUBS;
+    sum_slots(part + (int64_t)s0 * NPART, min(L1_SUBS, nsub - s0), tot);
+    double* out = d.partial2 + (int64_t)b * NPART;
+    if (threadIdx.x < 9) store_shared(out + threadIdx.x, tot[threadIdx.x]);
+    if (!last_block(d.fin_ticket + rid, R.fin_cnt)) return;
+    sum_slots<true>(d.partial2 + (int64_t)R.fin_off * NPART, R.fin_cnt, tot);
+  } else {
+    sum_slots(part, nsub, tot);
+  }
   if (threadIdx.x < 64) cg_advance(d, rid, c, mode, tot, slot, flushed, true);
 }
 
@@ -1199,9 +1195,7 @@ hipError_t launch_cg_fused(const DevPtrs& d, const CgFused& f, hipStream_t s) {
 
 hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s,
                             const CgRep* from) {
-  if (d.l1_total > 0)
-    hipLaunchKernelGGL(k_cg_reduce1, dim3(d.l1_total), dim3(FINISH_THREADS), 0, s, d, mode);
-  hipLaunchKernelGGL(k_cg_finish, dim3(d.nrep), dim3(FINISH_THREADS), 0, s, d, mode, slot, flushed,
+  hipLaunchKernelGGL(k_cg_finish, dim3(d.fin_total), dim3(FINISH_THREADS), 0, s, d, mode, slot, flushed,
                      from ? from : d.cg);
   return hipGetLastError();
 }

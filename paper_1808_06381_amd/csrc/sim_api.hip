@@ -1087,16 +1087,16 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   d.rows = s->rows;
   d.nblk = blk_off;
   d.want_er = s->learned ? 1 : 0;
-  // two-level reduction of the CG partials for replicas of many sub-tiles
-  std::vector<int32_t> l1_rep_h;
+  // the blocks that reduce the CG partials: one for a replica of few sub-tiles
+  std::vector<int32_t> fin_rep_h;
   for (int r = 0; r < replicas; ++r) {
     RepDev& R = s->reph[r];
     const int nsub = SUBS_PER_TILE * R.nblk;
-    R.l1_off = (int32_t)l1_rep_h.size();
-    R.l1_cnt = nsub > L1_MIN_SUBS ? (nsub + L1_SUBS - 1) / L1_SUBS : 0;
-    for (int b = 0; b < R.l1_cnt; ++b) l1_rep_h.push_back(r);
+    R.fin_off = (int32_t)fin_rep_h.size();
+    R.fin_cnt = nsub > L1_MIN_SUBS ? (nsub + L1_SUBS - 1) / L1_SUBS : 1;
+    for (int b = 0; b < R.fin_cnt; ++b) fin_rep_h.push_back(r);
   }
-  d.l1_total = (int32_t)l1_rep_h.size();
+  d.fin_total = (int32_t)fin_rep_h.size();
   d.nrep = replicas;
   d.ncell_entries = (int32_t)seg_off;
   d.spmv_fp32 = params[0].spmv_fp32;
@@ -1127,10 +1127,11 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   ALLOC(blk_rep_d, sizeof(int32_t) * d.nblk);
   d.blk_rep = blk_rep_d;
   ALLOC(d.partial, sizeof(double) * NPART * SUBS_PER_TILE * d.nblk);
-  ALLOC(d.partial2, sizeof(double) * NPART * std::max(d.l1_total, 1));
-  int32_t* l1_rep_d = nullptr;
-  ALLOC(l1_rep_d, sizeof(int32_t) * std::max<size_t>(l1_rep_h.size(), 1));
-  d.l1_rep = l1_rep_d;
+  ALLOC(d.partial2, sizeof(double) * NPART * d.fin_total);
+  int32_t* fin_rep_d = nullptr;
+  ALLOC(fin_rep_d, sizeof(int32_t) * fin_rep_h.size());
+  d.fin_rep = fin_rep_d;
+  ALLOC(d.fin_ticket, sizeof(int32_t) * replicas);
   ALLOC(d.pos, sizeof(double4) * rows);
   ALLOC(d.pos_alt, sizeof(double4) * rows);
   ALLOC(d.cellidx, sizeof(int32_t) * rows);
@@ -1241,10 +1242,10 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
     return fail(e, "upload replicas");
   if ((e = hipMemcpy(blk_rep_d, s->blk_rep_h.data(), sizeof(int32_t) * d.nblk, hipMemcpyHostToDevice)))
     return fail(e, "upload block table");
-  if (!l1_rep_h.empty() &&
-      (e = hipMemcpy(l1_rep_d, l1_rep_h.data(), sizeof(int32_t) * l1_rep_h.size(),
+  if ((e = hipMemcpy(fin_rep_d, fin_rep_h.data(), sizeof(int32_t) * fin_rep_h.size(),
                      hipMemcpyHostToDevice)))
     return fail(e, "upload reduction table");
+  if ((e = hipMemset(d.fin_ticket, 0, sizeof(int32_t) * replicas))) return fail(e, "clear tickets");
   if (s->block) {
     std::vector<BlockRep> br((size_t)replicas);
     for (int r = 0; r < replicas; ++r) {

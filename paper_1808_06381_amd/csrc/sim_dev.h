@@ -49,8 +49,8 @@ struct RepDev {
   double tol2;                // cg_tol^2
   int32_t weight_law, potential, noise_mode, precond;
   int32_t brick;              // brick edge of the cell order, in cells (>= every nc: z-major)
-  int32_t l1_cnt;             // first-level reduction blocks of the CG partials (0: none)
-  int32_t l1_off;             // the first of them
+  int32_t fin_cnt;            // blocks that reduce the replica's CG partials
+  int32_t fin_off;            // the first of them
   int32_t bshift;             // log2 of the brick edge (31: one brick)
   uint64_t seed, stream;
 };
@@ -121,8 +121,9 @@ struct DevPtrs {
   Ctrl* ctrl;
   const int32_t* blk_rep;   // block -> replica
   double* partial;          // [sub-tiles][NPART] (the block CG: [tiles][NPART])
-  double* partial2;         // [first-level blocks][NPART]
-  const int32_t* l1_rep;    // first-level block -> replica
+  double* partial2;         // [finishing blocks][NPART]
+  const int32_t* fin_rep;   // finishing block -> replica
+  int32_t* fin_ticket;      // [replicas] finished blocks of the current reduction (0 between launches)
   double4* pos;             // current positions (sorted order)
   double4* pos_alt;         // scatter target
   int32_t* cellidx;
@@ -172,7 +173,7 @@ struct DevPtrs {
   int32_t apply_var;
   int32_t ic0;              // 1: u = M^-1 r by the IC(0) triangular solves
   int32_t pc_none;          // 1: no preconditioner, u = r
-  int32_t l1_total;         // first-level reduction blocks over all replicas
+  int32_t fin_total;        // finishing blocks over all replicas
   int32_t want_er;          // 1: the pair terms write er (the network's edge input)
   int32_t vec_nt;           // 1: the CG vector kernel streams with nontemporal accesses
   int32_t ring;             // slots of the ring of u
@@ -193,11 +194,11 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 
 // The per-replica CG finisher sums the replica's sub-tile partials with
 // FINISH_THREADS threads.  A replica of more than L1_MIN_SUBS sub-tiles has
-// them summed first by blocks of L1_SUBS sub-tiles each (in parallel, one
-// launch) and the finisher adds those blocks' sums: a single block reading
-// every partial of an N = 8e6 box (31,252 slots, 4 MB) took about 60 us per
-// iteration.  Both are functions of the replica alone, so its totals do not
-// depend on the rest of a batch.
+// them summed first by blocks of L1_SUBS sub-tiles each (in parallel), the
+// last of which adds those blocks' sums: a single block reading every partial
+// of an N = 8e6 box (31,252 slots, 4 MB) took about 60 us per iteration.  Both
+// are functions of the replica alone, so its totals do not depend on the rest
+// of a batch.
 #define FINISH_THREADS 256
 #define L1_SUBS 256
 #define L1_MIN_SUBS 2048
@@ -433,6 +434,35 @@ __device__ __forceinline__ double wave_sum(double v) {
   v += __shfl_xor(v, 16, 64);
   v += __shfl_xor(v, 32, 64);
   return v;
+}
+
+// Values handed from block to block within a launch, past the XCDs' own
+// caches (relaxed agent-scope accesses; last_block orders them)
+__device__ __forceinline__ void store_shared(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_shared(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Whether this block is the last of `count` blocks to get here, for all its
+// threads.  The values it publishes are stored by its first wave
+// (store_shared): that wave waits for its stores to be performed and then
+// counts the block, so the last one finds every block's.  No block waits for
+// another.  The ticket is back at 0 for the next launch.
+__device__ __forceinline__ bool last_block(int32_t* ticket, int count) {
+  __shared__ int last;
+  if (threadIdx.x < 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    if (threadIdx.x == 0) {
+      const int seen =
+          __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = seen == count - 1;
+      if (last) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  __syncthreads();
+  return last != 0;
 }
 
 // sums K values over the block; result valid in thread 0
