@@ -96,7 +96,8 @@ __device__ __forceinline__ void turns_to_components(const double (&vt)[TURNS<LAN
 }
 
 // sub-tile partial sums: [gamma0..2, delta0..2, rr0..2]; `first`..`first+n`
-// written (blocks of SUB_THREADS threads)
+// written (blocks of SUB_THREADS threads).  With d.qper an array per sum, of one
+// slot per sub-tile or per wave (k_cg_fused's layout).
 template <int N>
 __device__ __forceinline__ void write_partials(const DevPtrs& d, int sub, int first,
                                                double (&v)[N]) {
@@ -104,6 +105,14 @@ __device__ __forceinline__ void write_partials(const DevPtrs& d, int sub, int fi
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
+  if (d.qper == 4) {
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        d.partial[(int64_t)(first + k) * d.qstride + 4 * sub + wave] = v[k];
+    }
+    return;
+  }
   if (lane == 0) {
 #pragma unroll
     for (int k = 0; k < N; ++k) lds[wave][k] = v[k];
@@ -112,7 +121,8 @@ __device__ __forceinline__ void write_partials(const DevPtrs& d, int sub, int fi
   if (threadIdx.x < N) {
     double s = 0.0;
     for (int w = 0; w < SUB_THREADS / 64; ++w) s += lds[w][threadIdx.x];
-    d.partial[(int64_t)sub * NPART + first + threadIdx.x] = s;
+    if (d.qper) d.partial[(int64_t)(first + threadIdx.x) * d.qstride + sub] = s;
+    else d.partial[(int64_t)sub * NPART + first + threadIdx.x] = s;
   }
 }
 
@@ -197,7 +207,8 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
   const bool ext = d.learned || d.ic0;  // u = M^-1 r comes from a separate pass
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const int le = q * SUB_THREADS + threadIdx.x;
+    // a wave takes the elements of its 64 rows (as in k_cg_fused)
+    const int le = 192 * (threadIdx.x >> 6) + 64 * q + (threadIdx.x & 63);
     const int k = le % 3;
     if (!on_k(on, k)) continue;
     const int64_t e = base + le;
@@ -740,21 +751,10 @@ __device__ __forceinline__ void cg_advance(const DevPtrs& d, int rid, CgRep& c, 
   }
 }
 
-// Sum `count` partial slots starting at `first` in a fixed order (thread t
-// takes slots t, t + blockDim, ...; then the wave and block trees).  Totals
-// in tot (LDS), valid for every thread.  SHARED: slots that other blocks of
-// this launch wrote.
-template <bool SHARED = false>
-__device__ __forceinline__ void sum_slots(const double* first, int count, double* tot) {
+// acc of FINISH_THREADS threads summed over the block (wave trees, then the
+// waves in order) into tot (LDS), valid for every thread
+__device__ __forceinline__ void block_sums(double (&acc)[9], double* tot) {
   __shared__ double lds[FINISH_THREADS / 64][9];
-  double acc[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) acc[k] = 0.0;
-  for (int t = threadIdx.x; t < count; t += blockDim.x) {
-    const double* src = first + (int64_t)t * NPART;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) acc[k] += SHARED ? load_shared(src + k) : src[k];
-  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = wave_sum(acc[k]);
@@ -770,6 +770,45 @@ __device__ __forceinline__ void sum_slots(const double* first, int count, double
     tot[threadIdx.x] = s;
   }
   __syncthreads();
+}
+
+// This thread's share (sub-tiles t, t + FINISH_THREADS, ...) of the sums of
+// `count` sub-tiles from sub-tile `first`, in the layout of k_cg_fused: QPER
+// neighbouring slots per sub-tile
+template <int QPER>
+__device__ __forceinline__ void slot_sums(const double* __restrict__ part, int qstride, int first,
+                                          int count, double (&acc)[9]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) acc[k] = 0.0;
+  for (int q = threadIdx.x; q < count; q += FINISH_THREADS) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const double* p = part + (int64_t)k * qstride + (int64_t)QPER * (first + q);
+      if constexpr (QPER == 4) {
+        const double4 w = *reinterpret_cast<const double4*>(p);
+        acc[k] += ((w.x + w.y) + w.z) + w.w;
+      } else {
+        acc[k] += *p;
+      }
+    }
+  }
+}
+
+// Sum `count` partial slots starting at `first` in a fixed order (thread t
+// takes slots t, t + FINISH_THREADS, ...; then block_sums).  Totals
+// in tot (LDS), valid for every thread.  SHARED: slots that other blocks of
+// this launch wrote.
+template <bool SHARED = false>
+__device__ __forceinline__ void sum_slots(const double* first, int count, double* tot) {
+  double acc[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) acc[k] = 0.0;
+  for (int t = threadIdx.x; t < count; t += FINISH_THREADS) {
+    const double* src = first + (int64_t)t * NPART;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[k] += SHARED ? load_shared(src + k) : src[k];
+  }
+  block_sums(acc, tot);
 }
 
 // CSR product over the sub-tile's 256 rows.
@@ -877,9 +916,14 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mod
   }
   if (!finish_work(c, mode)) return;
   __shared__ double tot[9];
-  const int nsub = SUBS_PER_TILE * R.nblk;
-  const double* part = d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART;
-  if (R.fin_cnt > 1) {
+  const int nsub = SUBS_PER_TILE * R.nblk, sub0 = SUBS_PER_TILE * R.blk_off;
+  const double* part = d.partial + (int64_t)sub0 * NPART;
+  if (d.qper) {
+    double acc[9];
+    if (d.qper == 4) slot_sums<4>(d.partial, d.qstride, sub0, nsub, acc);
+    else slot_sums<1>(d.partial, d.qstride, sub0, nsub, acc);
+    block_sums(acc, tot);
+  } else if (R.fin_cnt > 1) {
     const int s0 = (b - R.fin_off) * L1_SUBS;
     sum_slots(part + (int64_t)s0 * NPART, min(L1_SUBS, nsub - s0), tot);
     double* out = d.partial2 + (int64_t)b * NPART;
@@ -907,46 +951,62 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mod
 // Every sum has the operands and the order of the separate kernels (product
 // in entry order), so both forms give the same bits.  Three gathers per entry
 // in place of one: for large handles the separate passes are faster.
-// Bound by launch and memory latency (a sub-tile's chain is partials -> scalars
-// -> products -> row sums; entries and the rows they gather are loaded before
-// the scalars are known).  T threads for the 256 rows: with few tiles the
-// chip is filled by their entries (T at a time); rows and elements are the
-// first 256 threads' work.
+// Bound by launch and memory latency: the longest chain of loads is row pointer
+// -> column -> gathered rows, and everything else that the scalars need (the
+// partials, the state, the block's table entry) loads beside it.  A block has
+// 64 * W rows and T threads: all threads take entries, W waves the elements
+// (r', u and their sums), the next ones add up the rows' products.  Small
+// handles use W = 1, which spreads their entries over four times as many units
+// (N = 1000, ten steps: 7.4 -> 5.5 ms); every block of it writes one slot per
+// sum and reads four per sub-tile of its replica, in the order in which a
+// 256-row block adds its waves, so both forms give the same bits.
 // The times and the limits are beside FUSED_ROWS.
 // ---------------------------------------------------------------------------
-template <int T, bool LEARNED, bool FP32>
+template <int T, int W, bool LEARNED, bool FP32>
 __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
-  const int sub = sub_of_block(d);
-  if (sub < 0) return;
-  const int rid = d.blk_rep[sub / SUBS_PER_TILE];
-  const RepDev& R = d.rep[rid];
+  constexpr int ROWS = 64 * W, QPER = 4 / W;
+  constexpr int RC = T >= 256 * W ? 1 : 3;      // components per row thread
+  constexpr int RWAVES = W * (3 / RC);          // waves W .. W + RWAVES - 1
+  static_assert(T >= FINISH_THREADS && T >= 64 * (W + RWAVES) && CG_WORDS <= 64, "roles of waves");
+  const int per = QPER * ((SUBS_PER_TILE * d.nblk + 7) >> 3);  // blocks per XCD, whole sub-tiles
+  const int qb = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (qb >= QPER * SUBS_PER_TILE * d.nblk) return;
   __shared__ CgRep c;
   __shared__ double prod[3][T];
-  __shared__ double io[3 * SUB_ROWS];   // the source's own rows, then the results
-  __shared__ double lds[SUB_THREADS / 64][9];
+  __shared__ double io[3 * ROWS];     // the source's own rows
+  __shared__ double res[3 * ROWS];    // the results
+  __shared__ double lds[FINISH_THREADS / 64][9];
   __shared__ double tot[9];
+  __shared__ double own[W][9];        // this block's sums
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const bool rowt = t < SUB_ROWS;       // this thread has a row (and three elements)
-  const int64_t base = (int64_t)sub * SUB_ROWS;
-  copy_state(&c, f.cg_in + rid);
-  // everything that does not depend on the scalars is loaded first
-  const int cap = (int)d.nnz_cap;       // clamped as in lane_tile
+  const int64_t base = (int64_t)qb * ROWS;
+  // everything that does not depend on the scalars is loaded first: the
+  // entries with the rows they gather, the last launch's partials, the state
+  const int4 info = d.blk_info[qb / (QPER * SUBS_PER_TILE)];
+  const int rid = info.x;
+  const int cap = (int)d.nnz_cap;     // clamped as in lane_tile
   const int E0 = min(d.rowptr[base], cap);
-  const int ne = min(d.rowptr[base + SUB_ROWS], cap) - E0;
+  const int ne = min(d.rowptr[base + ROWS], cap) - E0;
+  // waves 0 .. W - 1: the elements of 64 rows each; the next RWAVES: the sums
+  // of 64 rows' products, of one component or of all three
+  const bool elems = wave < W, sums = wave >= W && wave < W + RWAVES;
+  const int comp = RC == 1 ? (wave - W) / W : 0;
+  const int group = elems ? wave : (wave - W) % W, row = 64 * group + lane;
   int r0 = 0, r1 = 0;
   double dgi = 0.0, er[3], es[3], ew[3], ed[3];
-  if (rowt) {
-    r0 = min(d.rowptr[base + t], cap) - E0;
-    r1 = min(d.rowptr[base + t + 1], cap) - E0;
-    dgi = LEARNED ? d.mdiag[base + t] : d.diag[base + t];
+  if (elems) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const int le = q * SUB_THREADS + t;
+      const int le = 192 * wave + 64 * q + lane;
       er[q] = d.r[3 * base + le];
       es[q] = d.s[3 * base + le];
       ew[q] = d.w[3 * base + le];
       ed[q] = LEARNED || d.pc_none ? 1.0 : d.dinv[base + le / 3];
     }
+  } else if (sums) {
+    r0 = min(d.rowptr[base + row], cap) - E0;
+    r1 = min(d.rowptr[base + row + 1], cap) - E0;
+    dgi = LEARNED ? d.mdiag[base + row] : d.diag[base + row];
   }
   auto value = [&](int e) {
     if constexpr (LEARNED) return d.moff[e];
@@ -956,7 +1016,7 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
   using VT = decltype(value(0));
   VT m = VT(0);
   double gr[3], gs[3], gw[3], gd = 1.0;
-  auto load = [&](int e) {   // entry e of the sub-tile and the rows it gathers
+  auto load = [&](int e) {   // entry e of the block and the rows it gathers
     const int j = d.col[E0 + e];
     m = value(E0 + e);
 #pragma unroll
@@ -967,28 +1027,23 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
     }
     if (!LEARNED && !d.pc_none) gd = d.dinv[j];
   };
+  if (t < CG_WORDS)
+    reinterpret_cast<uint64_t*>(&c)[t] = reinterpret_cast<const uint64_t*>(f.cg_in + rid)[t];
   if (t < ne) load(t);
+  double acc[9];
+  if (!f.first && t < FINISH_THREADS) {
+    slot_sums<QPER>(f.part_in, d.qstride, info.y, info.z, acc);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[k] = wave_sum(acc[k]);
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) lds[wave][k] = acc[k];
+    }
+  }
   __syncthreads();
+  const bool leader = qb == QPER * info.y;
   // the state is advanced unless the last launch left it advanced
   if (!f.first && c.run) {
-    const int nsub = SUBS_PER_TILE * R.nblk;
-    const double* first = f.part_in + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART;
-    if (rowt) {
-      double acc[9];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) acc[k] = 0.0;
-      for (int q = t; q < nsub; q += FINISH_THREADS) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) acc[k] += first[(int64_t)q * NPART + k];
-      }
-#pragma unroll
-      for (int k = 0; k < 9; ++k) acc[k] = wave_sum(acc[k]);
-      if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) lds[wave][k] = acc[k];
-      }
-    }
-    __syncthreads();
     if (t < 9) {
       double s = 0.0;
 #pragma unroll
@@ -996,11 +1051,10 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
       tot[t] = s;
     }
     __syncthreads();
-    if (t < 64)
-      cg_advance(d, rid, c, 2, tot, f.slot, f.flushed, sub == SUBS_PER_TILE * R.blk_off);
+    if (t < 64) cg_advance(d, rid, c, 2, tot, f.slot, f.flushed, leader);
     __syncthreads();
   }
-  if (sub == SUBS_PER_TILE * R.blk_off) copy_state(f.cg_out + rid, &c);
+  if (leader) copy_state(f.cg_out + rid, &c);
   if (!c.run) return;
   bool on[3];
   double al[3], th[3];
@@ -1015,11 +1069,11 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
     const double rm = tk != 0.0 ? s : r;
     return (r + tk * (r - rm)) - a * w;
   };
-  double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};  // (r,u), (w,u), (r,r)
-  if (rowt) {
+  double v[6] = {0, 0, 0, 0, 0, 0};  // (r,u), (r,r) of the elements
+  if (elems) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const int le = q * SUB_THREADS + t, k = le % 3;
+      const int le = 192 * wave + 64 * q + lane, k = le % 3;
       double src = 0.0;
       if (on_k(on, k)) {
         const double rk = next(er[q], es[q], ew[q], pick3(al, k), pick3(th, k));
@@ -1030,12 +1084,12 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
           d.u[3 * base + le] = src;
           v[k] += rk * src;
         }
-        v[6 + k] += rk * rk;
+        v[3 + k] += rk * rk;
       }
       io[le] = src;
     }
   }
-  double a[3] = {0.0, 0.0, 0.0};
+  double a[RC] = {};
   for (int c0 = 0; c0 < ne; c0 += T) {
     if (c0 + t < ne) {
 #pragma unroll
@@ -1047,53 +1101,44 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
       if (c0 + T + t < ne) load(c0 + T + t);
     }
     __syncthreads();
-    const int lo = r0 > c0 ? r0 : c0, hi = r1 < c0 + T ? r1 : c0 + T;
-    for (int e = lo; e < hi; ++e) {
-      a[0] += prod[0][e - c0];
-      a[1] += prod[1][e - c0];
-      a[2] += prod[2][e - c0];
-    }
-    __syncthreads();
-  }
-  if (ne == 0) __syncthreads();
-  double out[3] = {0.0, 0.0, 0.0};
-  if (rowt) {
+    if (sums) {
+      const int lo = r0 > c0 ? r0 : c0, hi = r1 < c0 + T ? r1 : c0 + T;
+      for (int e = lo; e < hi; ++e) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const double sk = io[3 * t + k];
-      if (on_k(on, k)) {
-        out[k] = dgi * sk + a[k];
-        // learned: (r, u), u the result; Jacobi: (w, u), u the source
-        if constexpr (LEARNED) v[k] += sk * out[k];
-        else v[3 + k] += out[k] * sk;
+        for (int k = 0; k < RC; ++k) a[k] += prod[comp + k][e - c0];
       }
     }
+    if (c0 + T < ne) __syncthreads();
   }
-  __syncthreads();  // every own row read
-  if (rowt) {
+  if (ne == 0) __syncthreads();
+  if (elems) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) io[3 * t + k] = out[k];
+    for (int k = LEARNED ? 3 : 0; k < 6; ++k) {
+      const double s = wave_sum(v[k]);
+      if (lane == 0) own[wave][k < 3 ? k : k + 3] = s;
+    }
+  } else if (sums) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) v[k] = wave_sum(v[k]);
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < 9; ++k) lds[wave][k] = v[k];
+    for (int k = 0; k < RC; ++k) {
+      const double sk = io[3 * row + comp + k];
+      const double out = dgi * sk + a[k];
+      res[3 * row + comp + k] = out;
+      // learned: (r, u), u the result (k_cg_spmv adds (w, u)); Jacobi: (w, u)
+      const double s = wave_sum(on_k(on, comp + k) ? out * sk : 0.0);
+      if (lane == 0) own[group][(LEARNED ? 0 : 3) + comp + k] = s;
     }
   }
   __syncthreads();
-  if (rowt) {
+  if (t < 3 * ROWS) {
     double* __restrict__ dst = LEARNED ? d.u : f.wnew;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int le = q * SUB_THREADS + t;
-      if (on_k(on, le % 3)) dst[3 * base + le] = io[le];
-    }
+    for (int le = t; le < 3 * ROWS; le += T)
+      if (on_k(on, le % 3)) dst[3 * base + le] = res[le];
   }
-  if (t < 9 && !(LEARNED && t / 3 == 1)) {  // learned: k_cg_spmv writes (w, u)
+  if (t < 9 && !(LEARNED && t / 3 == 1)) {
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < SUB_THREADS / 64; ++w) s += lds[w][t];
-    d.partial[(int64_t)sub * NPART + t] = s;
+    for (int w = 0; w < W; ++w) s += own[w][t];
+    d.partial[(int64_t)t * d.qstride + qb] = s;
   }
 }
 
@@ -1176,20 +1221,20 @@ hipError_t launch_cg_flush(const DevPtrs& d, int forced, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int T>
+template <int T, int W>
 static void launch_fused_t(const DevPtrs& d, const CgFused& f, hipStream_t s) {
-  const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(T);
+  const dim3 g(4 / W * xcd_grid(SUBS_PER_TILE * d.nblk)), b(T);
   if (d.learned)
-    hipLaunchKernelGGL((k_cg_fused<T, true, false>), g, b, 0, s, d, f);
+    hipLaunchKernelGGL((k_cg_fused<T, W, true, false>), g, b, 0, s, d, f);
   else if (d.spmv_fp32)
-    hipLaunchKernelGGL((k_cg_fused<T, false, true>), g, b, 0, s, d, f);
+    hipLaunchKernelGGL((k_cg_fused<T, W, false, true>), g, b, 0, s, d, f);
   else
-    hipLaunchKernelGGL((k_cg_fused<T, false, false>), g, b, 0, s, d, f);
+    hipLaunchKernelGGL((k_cg_fused<T, W, false, false>), g, b, 0, s, d, f);
 }
 
 hipError_t launch_cg_fused(const DevPtrs& d, const CgFused& f, hipStream_t s) {
-  if (SUBS_PER_TILE * d.nblk <= FUSED_WIDE_SUBS) launch_fused_t<1024>(d, f, s);
-  else launch_fused_t<512>(d, f, s);
+  if (d.qper == 4) launch_fused_t<512, 1>(d, f, s);
+  else launch_fused_t<512, 4>(d, f, s);
   return hipGetLastError();
 }
 

@@ -1126,7 +1126,15 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   int32_t* blk_rep_d = nullptr;
   ALLOC(blk_rep_d, sizeof(int32_t) * d.nblk);
   d.blk_rep = blk_rep_d;
-  ALLOC(d.partial, sizeof(double) * NPART * SUBS_PER_TILE * d.nblk);
+  int4* blk_info_d = nullptr;
+  ALLOC(blk_info_d, sizeof(int4) * d.nblk);
+  d.blk_info = blk_info_d;
+  // handles with fused iterations keep a partial per wave, one array per sum
+  const bool fused = !s->block && !s->ic0 && s->rows <= FUSED_ROWS;
+  d.qper = fused ? (SUBS_PER_TILE * d.nblk <= FUSED_SPLIT_SUBS ? 4 : 1) : 0;
+  d.qstride = d.qper * SUBS_PER_TILE * d.nblk;
+  const size_t npart = fused ? (size_t)9 * d.qstride : (size_t)NPART * SUBS_PER_TILE * d.nblk;
+  ALLOC(d.partial, sizeof(double) * npart);
   ALLOC(d.partial2, sizeof(double) * NPART * d.fin_total);
   int32_t* fin_rep_d = nullptr;
   ALLOC(fin_rep_d, sizeof(int32_t) * fin_rep_h.size());
@@ -1160,9 +1168,9 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
                                       std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
   const size_t slots = d.ring;
   ALLOC(d.u, sizeof(double) * 3 * rows * slots);
-  if (!s->block && !s->ic0 && s->rows <= FUSED_ROWS) {
+  if (fused) {
     ALLOC(s->cg2, sizeof(CgRep) * replicas);
-    ALLOC(s->partial2nd, sizeof(double) * NPART * SUBS_PER_TILE * d.nblk);
+    ALLOC(s->partial2nd, sizeof(double) * npart);
     ALLOC(s->rbuf[2], sizeof(double) * 3 * rows);
     ALLOC(s->wbuf[1], sizeof(double) * 3 * rows);
   }
@@ -1241,6 +1249,13 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   if ((e = hipMemcpy(s->rep_d, s->reph.data(), sizeof(RepDev) * replicas, hipMemcpyHostToDevice)))
     return fail(e, "upload replicas");
   if ((e = hipMemcpy(blk_rep_d, s->blk_rep_h.data(), sizeof(int32_t) * d.nblk, hipMemcpyHostToDevice)))
+    return fail(e, "upload block table");
+  std::vector<int4> info((size_t)d.nblk);
+  for (int b = 0; b < d.nblk; ++b) {
+    const RepDev& R = s->reph[s->blk_rep_h[b]];
+    info[b] = make_int4(s->blk_rep_h[b], SUBS_PER_TILE * R.blk_off, SUBS_PER_TILE * R.nblk, 0);
+  }
+  if ((e = hipMemcpy(blk_info_d, info.data(), sizeof(int4) * d.nblk, hipMemcpyHostToDevice)))
     return fail(e, "upload block table");
   if ((e = hipMemcpy(fin_rep_d, fin_rep_h.data(), sizeof(int32_t) * fin_rep_h.size(),
                      hipMemcpyHostToDevice)))

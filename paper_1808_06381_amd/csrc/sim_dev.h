@@ -120,7 +120,10 @@ struct DevPtrs {
   CgRep* cg;
   Ctrl* ctrl;
   const int32_t* blk_rep;   // block -> replica
-  double* partial;          // [sub-tiles][NPART] (the block CG: [tiles][NPART])
+  double* partial;          // [sub-tiles][NPART]; handles with fused iterations: [9][qstride]
+  int32_t qper;             // ... of so many slots per sub-tile (1 or 4; else 0)
+  int32_t qstride;          // ... slots over all sub-tiles
+  const int4* blk_info;     // block -> replica, its first sub-tile, its sub-tiles
   double* partial2;         // [finishing blocks][NPART]
   const int32_t* fin_rep;   // finishing block -> replica
   int32_t* fin_ticket;      // [replicas] finished blocks of the current reduction (0 between launches)
@@ -204,17 +207,20 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 #define L1_MIN_SUBS 2048
 
 // Handles of at most FUSED_ROWS rows run finisher, vector pass and product as
-// one launch (k_cg_fused).  Per step, separate kernels against fused with 256 /
-// 512 / 1024 threads per 256-row sub-tile: N = 1e3 (ten steps) 12.0 ms against
-// 10.3 / 8.8 / 8.4; 4 x 20060 rows of 15 entries (ten) 20.8 against 23.0 / 18.8 /
-// 21.2; N = 1e5 learned (two) 2.51 against 2.39 / 2.31 / 2.49; a solve at
-// N = 2.5e5 2.28 against 2.33 / 2.51 / 3.30.  So 1024 threads where the
-// sub-tiles leave half the chip's 256 units idle, else 512.
+// one launch (k_cg_fused), of at most FUSED_SPLIT_SUBS sub-tiles with a block
+// per 64 rows (512 threads), else per 256.  Per step in us, separate kernels /
+// 256-row blocks / 64-row blocks, one box of 5.5 entries per row: Jacobi
+// N = 1000 1200 / 714 / 522, 8000 - / 874 / 613, 32000 - / 1061 / 842,
+// 64000 - / 1127 / 1390, 120000 - / 1474 / 2621; learned 1000 - / 588 / 502,
+// 32000 - / 826 / 742, 64000 - / 931 / 1060; past two blocks per unit (32768
+// rows) the finer split is at once the slower one: Jacobi N = 33000 1071 and
+// 1168.  256 or 1024 threads per 64 rows: N = 1000 569 and 630.  The other line: a solve at
+// N = 2.5e5 takes 2.28 ms with separate kernels and 2.33 fused.
 #define FUSED_ROWS (128 * 1024)
+#define FUSED_SPLIT_SUBS 128
 // ... and build their system with kernels that spread a particle's search and
 // a row's entries over more lanes (k_nbr_count_wide, k_pair_terms<64>)
 #define SMALL_ROWS 131072
-#define FUSED_WIDE_SUBS 128
 
 // ---------------------------------------------------------------------------
 // Block -> tile mapping: hardware dispatches workgroups round-robin over the
