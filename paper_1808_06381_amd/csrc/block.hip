@@ -558,7 +558,7 @@ __global__ __launch_bounds__(SUB_THREADS) void k_bcg_flush(DevPtrs d, BlockPtrs 
 // `slot` is the ring slot of the u just multiplied (mode 0) or written (mode
 // 2); `flushed` (mode 0): the terms before it were added to x.  Several blocks
 // share a large replica as in k_cg_finish (one block of 1024 threads took 12.5
-// us at N = 1e6, now 6.5).
+// us at N = 1e6, now 5.9).
 constexpr int BFIN = 256;
 
 // sum of `count` slots from `first` in a fixed order, in tot (LDS)
@@ -591,22 +591,18 @@ __device__ __forceinline__ void block_slots(const double* first, int count, doub
 
 __global__ __launch_bounds__(BFIN) void k_bcg_finish(DevPtrs d, BlockPtrs bp, int mode, int slot,
                                                      int flushed) {
-  const int b = blockIdx.x;
-  const int rid = d.fin_rep[b];
+  const FinBlock F = d.fin[blockIdx.x];
+  const int rid = F.rep;
   BcgRep& B = bp.bcg[rid];
-  if (B.state != (mode == 2 ? 1 : 0)) return;
-  const RepDev& R = d.rep[rid];
+  const bool work = B.state == (mode == 2 ? 1 : 0);
   __shared__ double tot[3];
-  const int nsub = SUBS_PER_TILE * R.nblk;
-  const double* part = d.partial + (int64_t)(SUBS_PER_TILE * R.blk_off) * NPART;
-  if (R.fin_cnt > 1) {
-    const int s0 = (b - R.fin_off) * L1_SUBS;
-    block_slots<false>(part + (int64_t)s0 * NPART, min(L1_SUBS, nsub - s0), tot);
-    if (threadIdx.x < 3) store_shared(d.partial2 + (int64_t)b * NPART + threadIdx.x, tot[threadIdx.x]);
-    if (!last_block(d.fin_ticket + rid, R.fin_cnt)) return;
-    block_slots<true>(d.partial2 + (int64_t)R.fin_off * NPART, R.fin_cnt, tot);
-  } else {
-    block_slots<false>(part, nsub, tot);
+  block_slots<false>(d.partial + (int64_t)F.sub0 * NPART, F.nsub, tot);
+  if (!work) return;
+  if (F.cnt > 1) {
+    double* out = d.partial2 + (int64_t)blockIdx.x * NPART;
+    if (threadIdx.x < 3) store_shared(out + threadIdx.x, tot[threadIdx.x]);
+    if (!last_block(d.fin_ticket + rid, F.cnt)) return;
+    block_slots<true>(d.partial2 + (int64_t)F.off * NPART, F.cnt, tot);
   }
   if (threadIdx.x != 0) return;
   const double delta = tot[0], gamma = tot[1];

@@ -254,13 +254,20 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
 // every component with pending terms; forced = 0: before a check, the
 // components whose check is pending (p is not needed after it).  The
 // finisher that follows marks the terms as added.
-__global__ __launch_bounds__(SUB_THREADS) void k_cg_flush(DevPtrs d, int forced) {
-  const int sub = sub_of_block(d);
-  if (sub < 0) return;
+// NE elements per thread, NT threads: 3 and 256 stream a sub-tile; small
+// handles, whose few blocks would each wait for the ring's slots in rounds, use
+// 1 and 192 (64 rows; limit and times beside FLUSH_SPLIT_SUBS).  An element's
+// terms are added in the same order.
+template <int NE, int NT>
+__global__ __launch_bounds__(NT) void k_cg_flush(DevPtrs d, int forced) {
+  constexpr int PARTS = VEC_ELEMS / (NE * NT);  // blocks per sub-tile
+  const int per = PARTS * ((SUBS_PER_TILE * d.nblk + 7) >> 3);
+  const int part = (blockIdx.x & 7) * per + (blockIdx.x >> 3), sub = part / PARTS;
+  if (sub >= SUBS_PER_TILE * d.nblk) return;
   const int rid = d.blk_rep[sub / SUBS_PER_TILE];
   const CgRep& cr = d.cg[rid];
   if (forced ? !cr.run : !cr.check) return;
-  static_assert(U_RING <= 64 && SUB_THREADS >= 192, "one lane per term, one wave per component");
+  static_assert(U_RING <= 64 && NT >= 192 && NT % 3 == (NE > 1 ? 1 : 0), "one lane per term, one wave per component");
   __shared__ double h[U_RING][3][2];       // c, d
   __shared__ double hp[3][2];              // the factors of p
   __shared__ int cnt[3], off[3];
@@ -291,14 +298,14 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_flush(DevPtrs d, int forced)
     }
   }
   __syncthreads();
-  const int64_t base = (int64_t)sub * VEC_ELEMS, ring = 3 * d.rows;
-  double ax[3] = {0.0, 0.0, 0.0}, ap[3] = {0.0, 0.0, 0.0};
+  const int64_t base = (int64_t)part * (NE * NT), ring = 3 * d.rows;
+  double ax[NE] = {}, ap[NE] = {};
   const int m = max(cnt[0], max(cnt[1], cnt[2]));
-#pragma unroll 8
-  for (int j = 0; j < m; ++j) {  // independent loads: 24 in flight per lane
+#pragma unroll NE == 1 ? 16 : 8
+  for (int j = 0; j < m; ++j) {  // independent loads
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int le = q * SUB_THREADS + t;
+    for (int q = 0; q < NE; ++q) {
+      const int le = q * NT + t;
       const int k = le % 3;
       if (j >= cnt[k]) continue;
       int slot = off[k] + j;
@@ -309,8 +316,8 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_flush(DevPtrs d, int forced)
     }
   }
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const int le = q * SUB_THREADS + t;
+  for (int q = 0; q < NE; ++q) {
+    const int le = q * NT + t;
     const int k = le % 3;
     if (cnt[k] == 0) continue;
     const int64_t e = base + le;
@@ -794,13 +801,10 @@ __device__ __forceinline__ void slot_sums(const double* __restrict__ part, int q
   }
 }
 
-// Sum `count` partial slots starting at `first` in a fixed order (thread t
-// takes slots t, t + FINISH_THREADS, ...; then block_sums).  Totals
-// in tot (LDS), valid for every thread.  SHARED: slots that other blocks of
-// this launch wrote.
+// ... and of `count` slots of NPART doubles.  SHARED: slots that other blocks
+// of this launch wrote.
 template <bool SHARED = false>
-__device__ __forceinline__ void sum_slots(const double* first, int count, double* tot) {
-  double acc[9];
+__device__ __forceinline__ void slot_sums(const double* first, int count, double (&acc)[9]) {
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = 0.0;
   for (int t = threadIdx.x; t < count; t += FINISH_THREADS) {
@@ -808,7 +812,6 @@ __device__ __forceinline__ void sum_slots(const double* first, int count, double
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[k] += SHARED ? load_shared(src + k) : src[k];
   }
-  block_sums(acc, tot);
 }
 
 // CSR product over the sub-tile's 256 rows.
@@ -900,38 +903,35 @@ __device__ __forceinline__ void copy_state(CgRep* dst, const CgRep* src) {
 // Sub-tile partials in a fixed order, then the recurrences.  A replica of few
 // sub-tiles is one block's work.  Of a larger one, block b sums L1_SUBS
 // sub-tiles into partial2[b], and the last block to finish (last_block) adds
-// those sums in order and advances: one launch of 7.2 us at N = 1e6 where two
-// of 4.6 and 4.7 were.  `from`: the state to advance into
+// those sums in order and advances: one launch where two were (9.3 us at
+// N = 1e6, now 6.9).  `from`: the state to advance into
 // d.cg (d.cg itself, or the other copy after an odd number of fused
 // iterations; small handles only, so one block).
 __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode, int slot,
                                                               int flushed, const CgRep* from) {
-  const int b = blockIdx.x;
-  const int rid = d.fin_rep[b];
-  const RepDev& R = d.rep[rid];
+  const FinBlock F = d.fin[blockIdx.x];
+  const int rid = F.rep;
   CgRep& c = d.cg[rid];
   if (from != d.cg) {
     copy_state(&c, from + rid);
     __syncthreads();
   }
-  if (!finish_work(c, mode)) return;
   __shared__ double tot[9];
-  const int nsub = SUBS_PER_TILE * R.nblk, sub0 = SUBS_PER_TILE * R.blk_off;
-  const double* part = d.partial + (int64_t)sub0 * NPART;
-  if (d.qper) {
-    double acc[9];
-    if (d.qper == 4) slot_sums<4>(d.partial, d.qstride, sub0, nsub, acc);
-    else slot_sums<1>(d.partial, d.qstride, sub0, nsub, acc);
-    block_sums(acc, tot);
-  } else if (R.fin_cnt > 1) {
-    const int s0 = (b - R.fin_off) * L1_SUBS;
-    sum_slots(part + (int64_t)s0 * NPART, min(L1_SUBS, nsub - s0), tot);
-    double* out = d.partial2 + (int64_t)b * NPART;
+  // summed before the state says whether they are needed: the two loads are
+  // the launch's longest waits, and neither waits for the other
+  const bool work = finish_work(c, mode);
+  double acc[9];
+  if (d.qper == 4) slot_sums<4>(d.partial, d.qstride, F.sub0, F.nsub, acc);
+  else if (d.qper) slot_sums<1>(d.partial, d.qstride, F.sub0, F.nsub, acc);
+  else slot_sums(d.partial + (int64_t)F.sub0 * NPART, F.nsub, acc);
+  block_sums(acc, tot);
+  if (!work) return;
+  if (F.cnt > 1) {
+    double* out = d.partial2 + (int64_t)blockIdx.x * NPART;
     if (threadIdx.x < 9) store_shared(out + threadIdx.x, tot[threadIdx.x]);
-    if (!last_block(d.fin_ticket + rid, R.fin_cnt)) return;
-    sum_slots<true>(d.partial2 + (int64_t)R.fin_off * NPART, R.fin_cnt, tot);
-  } else {
-    sum_slots(part, nsub, tot);
+    if (!last_block(d.fin_ticket + rid, F.cnt)) return;
+    slot_sums<true>(d.partial2 + (int64_t)F.off * NPART, F.cnt, acc);
+    block_sums(acc, tot);
   }
   if (threadIdx.x < 64) cg_advance(d, rid, c, mode, tot, slot, flushed, true);
 }
@@ -1216,8 +1216,11 @@ hipError_t launch_cg_warm(const DevPtrs& d, const int64_t* id_off, hipStream_t s
 
 // d.u: the first ring slot
 hipError_t launch_cg_flush(const DevPtrs& d, int forced, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_flush, dim3(xcd_grid(SUBS_PER_TILE * d.nblk)), dim3(SUB_THREADS), 0, s, d,
-                     forced);
+  const int g = xcd_grid(SUBS_PER_TILE * d.nblk);
+  if (SUBS_PER_TILE * d.nblk <= FLUSH_SPLIT_SUBS)
+    hipLaunchKernelGGL((k_cg_flush<1, 192>), dim3(4 * g), dim3(192), 0, s, d, forced);
+  else
+    hipLaunchKernelGGL((k_cg_flush<3, 256>), dim3(g), dim3(256), 0, s, d, forced);
   return hipGetLastError();
 }
 

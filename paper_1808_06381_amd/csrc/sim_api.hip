@@ -1088,15 +1088,22 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   d.nblk = blk_off;
   d.want_er = s->learned ? 1 : 0;
   // the blocks that reduce the CG partials: one for a replica of few sub-tiles
-  std::vector<int32_t> fin_rep_h;
+  std::vector<FinBlock> fin_h;
   for (int r = 0; r < replicas; ++r) {
     RepDev& R = s->reph[r];
     const int nsub = SUBS_PER_TILE * R.nblk;
-    R.fin_off = (int32_t)fin_rep_h.size();
-    R.fin_cnt = nsub > L1_MIN_SUBS ? (nsub + L1_SUBS - 1) / L1_SUBS : 1;
-    for (int b = 0; b < R.fin_cnt; ++b) fin_rep_h.push_back(r);
+    FinBlock F{};
+    F.rep = r;
+    F.off = (int32_t)fin_h.size();
+    F.cnt = nsub > L1_MIN_SUBS ? (nsub + L1_SUBS - 1) / L1_SUBS : 1;
+    const int32_t each = F.cnt > 1 ? L1_SUBS : nsub;
+    for (int b = 0; b < F.cnt; ++b) {
+      F.sub0 = SUBS_PER_TILE * R.blk_off + b * each;
+      F.nsub = std::min<int32_t>(each, nsub - b * each);
+      fin_h.push_back(F);
+    }
   }
-  d.fin_total = (int32_t)fin_rep_h.size();
+  d.fin_total = (int32_t)fin_h.size();
   d.nrep = replicas;
   d.ncell_entries = (int32_t)seg_off;
   d.spmv_fp32 = params[0].spmv_fp32;
@@ -1136,9 +1143,9 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   const size_t npart = fused ? (size_t)9 * d.qstride : (size_t)NPART * SUBS_PER_TILE * d.nblk;
   ALLOC(d.partial, sizeof(double) * npart);
   ALLOC(d.partial2, sizeof(double) * NPART * d.fin_total);
-  int32_t* fin_rep_d = nullptr;
-  ALLOC(fin_rep_d, sizeof(int32_t) * fin_rep_h.size());
-  d.fin_rep = fin_rep_d;
+  FinBlock* fin_d = nullptr;
+  ALLOC(fin_d, sizeof(FinBlock) * fin_h.size());
+  d.fin = fin_d;
   ALLOC(d.fin_ticket, sizeof(int32_t) * replicas);
   ALLOC(d.pos, sizeof(double4) * rows);
   ALLOC(d.pos_alt, sizeof(double4) * rows);
@@ -1257,7 +1264,7 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   }
   if ((e = hipMemcpy(blk_info_d, info.data(), sizeof(int4) * d.nblk, hipMemcpyHostToDevice)))
     return fail(e, "upload block table");
-  if ((e = hipMemcpy(fin_rep_d, fin_rep_h.data(), sizeof(int32_t) * fin_rep_h.size(),
+  if ((e = hipMemcpy(fin_d, fin_h.data(), sizeof(FinBlock) * fin_h.size(),
                      hipMemcpyHostToDevice)))
     return fail(e, "upload reduction table");
   if ((e = hipMemset(d.fin_ticket, 0, sizeof(int32_t) * replicas))) return fail(e, "clear tickets");

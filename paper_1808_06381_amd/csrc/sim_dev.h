@@ -49,8 +49,6 @@ struct RepDev {
   double tol2;                // cg_tol^2
   int32_t weight_law, potential, noise_mode, precond;
   int32_t brick;              // brick edge of the cell order, in cells (>= every nc: z-major)
-  int32_t fin_cnt;            // blocks that reduce the replica's CG partials
-  int32_t fin_off;            // the first of them
   int32_t bshift;             // log2 of the brick edge (31: one brick)
   uint64_t seed, stream;
 };
@@ -115,6 +113,17 @@ __device__ __forceinline__ bool ctrl_commit_ok(const Ctrl* c) {
   return c->n_notdone == 0 && c->overflow == 0 && c->breakdown == 0;
 }
 
+// One block of the reduction of the CG partials: everything it needs to start
+// its loads, in one table entry
+struct FinBlock {
+  int32_t rep;   // replica
+  int32_t sub0;  // its sub-tiles: the first ...
+  int32_t nsub;  // ... and how many
+  int32_t off;   // the first of the replica's blocks ...
+  int32_t cnt;   // ... and how many
+  int32_t pad[3];
+};
+
 struct DevPtrs {
   const RepDev* rep;
   CgRep* cg;
@@ -125,7 +134,7 @@ struct DevPtrs {
   int32_t qstride;          // ... slots over all sub-tiles
   const int4* blk_info;     // block -> replica, its first sub-tile, its sub-tiles
   double* partial2;         // [finishing blocks][NPART]
-  const int32_t* fin_rep;   // finishing block -> replica
+  const FinBlock* fin;      // the finishing blocks
   int32_t* fin_ticket;      // [replicas] finished blocks of the current reduction (0 between launches)
   double4* pos;             // current positions (sorted order)
   double4* pos_alt;         // scatter target
@@ -196,15 +205,16 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
   X(8, 0, 2) X(9, 0, 3)
 
 // The per-replica CG finisher sums the replica's sub-tile partials with
-// FINISH_THREADS threads.  A replica of more than L1_MIN_SUBS sub-tiles has
-// them summed first by blocks of L1_SUBS sub-tiles each (in parallel), the
-// last of which adds those blocks' sums: a single block reading every partial
-// of an N = 8e6 box (31,252 slots, 4 MB) took about 60 us per iteration.  Both
-// are functions of the replica alone, so its totals do not depend on the rest
-// of a batch.
+// FINISH_THREADS threads.  A replica of more than L1_MIN_SUBS sub-tiles (two
+// rounds of loads for one block) has them summed first by blocks of L1_SUBS
+// sub-tiles each, the last of which adds those blocks' sums: a single block
+// reading every partial of an N = 8e6 box (31,252 slots, 4 MB) took about 60 us
+// per iteration.  A solve at N = 2.5e5 with the line at 2048 / 512 and blocks of
+// 256 / 256 / 128 / 64 sub-tiles: 2.236 / 2.215 / 2.226 / 2.208 ms.  Both are functions of
+// the replica alone, so its totals do not depend on the rest of a batch.
 #define FINISH_THREADS 256
-#define L1_SUBS 256
-#define L1_MIN_SUBS 2048
+#define L1_SUBS 64
+#define L1_MIN_SUBS 512
 
 // Handles of at most FUSED_ROWS rows run finisher, vector pass and product as
 // one launch (k_cg_fused), of at most FUSED_SPLIT_SUBS sub-tiles with a block
@@ -218,6 +228,11 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 // N = 2.5e5 takes 2.28 ms with separate kernels and 2.33 fused.
 #define FUSED_ROWS (128 * 1024)
 #define FUSED_SPLIT_SUBS 128
+// ... and handles of at most so many sub-tiles add the ring to x with a thread
+// per element (k_cg_flush<1, 192>): per pass 17.8 -> 7.5 us at N = 1000, 46 -> 21
+// at N = 8e4; at N = 1e6 both stream at 5 TB/s and the coarser form has fewer
+// ring tables to form
+#define FLUSH_SPLIT_SUBS 1024
 // ... and build their system with kernels that spread a particle's search and
 // a row's entries over more lanes (k_nbr_count_wide, k_pair_terms<64>)
 #define SMALL_ROWS 131072

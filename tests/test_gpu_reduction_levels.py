@@ -1,5 +1,5 @@
 """The CG's partial sums on both sides of the line from which several blocks
-share a replica's reduction (more than 2048 sub-tiles of 256 rows), scalar and
+share a replica's reduction (more than 512 sub-tiles of 256 rows), scalar and
 block system, alone and next to a small replica.
 
 Oracle: the residual of the returned solution, formed on the host from the
@@ -13,10 +13,10 @@ from paper_1808_06381_amd import inputs
 from paper_1808_06381_amd import sim as S
 
 pytestmark = pytest.mark.gpu
-LINE = 2048 * 256
+LINE = 512 * 256
 
 
-@pytest.mark.parametrize("n", [LINE, LINE + 1, LINE + 257 * 256])
+@pytest.mark.parametrize("n", [LINE, LINE + 1, LINE + 65 * 256, 4 * LINE + 257])
 def test_scalar_system(n):
     cfg = dict(inputs.cube_params(n, 0.3, seed=2), stream=0)
     small = dict(inputs.cube_params(700, 0.3, seed=3), stream=1)
