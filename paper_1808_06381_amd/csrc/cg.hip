@@ -173,76 +173,6 @@ __device__ __forceinline__ void stv(T* p, T v) {
   else *p = v;
 }
 
-// Element-parallel vector work of one sub-tile (3 * 256 consecutive doubles
-// of the AoS arrays; element e is row e/3, component e%3).  NT: the streams
-// that are not read again within the iteration (r twice, w, 1/diag) are
-// loaded and stored as nontemporal, u (gathered by the product next) as
-// usual: on a working set larger than the last-level cache this streams
-// faster (measured at N = 8e6), below it the ordinary form keeps the
-// vectors cached; the autotuner picks.  Same bits either way.
-//   mode 0 (fresh start):   x = 0, r = b, u = M^-1 r
-//   mode 1 (restart, r already = b - A x):   u = M^-1 r
-//   mode 2 (iteration):     d.s = r + theta (r - d.s) - alpha w, u = M^-1 (new r)
-// In mode 2 the new residual overwrites the one before r; the host swaps the
-// two for the launches that follow, and points d.u at the next ring slot.
-// With theta = 0 (a first iteration) the old d.s is not read.
-// Partials (r, u) and (r, r) of the components touched.
-template <bool NT>
-__global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode) {
-  const int sub = sub_of_block(d);
-  if (sub < 0) return;
-  const int rid = d.blk_rep[sub / SUBS_PER_TILE];
-  const CgRep& cr = d.cg[rid];
-  if ((mode == 1 && !cr.restart) || (mode == 2 && !cr.run)) return;
-  bool on[3];
-  double al[3], th[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    on[k] = mode == 0 ? true : (mode == 1 ? cr.state[k] == 3 : cr.state[k] == 0);
-    al[k] = cr.alpha[k];
-    th[k] = cr.theta[k];
-  }
-  double v[6] = {0, 0, 0, 0, 0, 0};  // (r,u)[3], (r,r)[3]
-  const int64_t base = (int64_t)sub * VEC_ELEMS;
-  const bool ext = d.learned || d.ic0;  // u = M^-1 r comes from a separate pass
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    // a wave takes the elements of its 64 rows (as in k_cg_fused)
-    const int le = 192 * (threadIdx.x >> 6) + 64 * q + (threadIdx.x & 63);
-    const int k = le % 3;
-    if (!on_k(on, k)) continue;
-    const int64_t e = base + le;
-    // 1/diag only where this kernel applies Jacobi itself
-    const double di =
-        (ext || d.pc_none) ? 1.0 : ldv<NT>(d.dinv + (int64_t)sub * SUB_ROWS + le / 3);
-    double rk;
-    if (mode == 0) {
-      rk = d.b[e];
-      d.x[e] = 0.0;
-      d.r[e] = rk;
-    } else if (mode == 1) {
-      rk = d.r[e];
-    } else {
-      const double r0 = ldv<NT>(d.r + e), t = pick3(th, k);
-      const double rm = t != 0.0 ? ldv<NT>(d.s + e) : r0;
-      rk = (r0 + t * (r0 - rm)) - pick3(al, k) * ldv<NT>(d.w + e);
-      stv<NT>(d.s + e, rk);
-    }
-    if (!ext) {
-      const double uk = di * rk;
-      d.u[e] = uk;
-      v[k] += rk * uk;
-    }
-    v[3 + k] += rk * rk;
-  }
-  double g[3] = {v[0], v[1], v[2]}, rr[3] = {v[3], v[4], v[5]};
-  if (!ext) {
-    write_partials<3>(d, sub, 0, g);
-    __syncthreads();
-  }
-  write_partials<3>(d, sub, 6, rr);
-}
-
 // The ring's pending terms u_0 .. u_{m-1} (slots cbase ..) of a component
 // into x and into the direction p that the later terms build on.  With
 // p_j = u_j + beta_j p_{j-1} and x += sum_j alpha_j p_j, the beta are ratios of
@@ -900,32 +830,174 @@ __device__ __forceinline__ void copy_state(CgRep* dst, const CgRep* src) {
         reinterpret_cast<const uint64_t*>(src)[threadIdx.x];
 }
 
+// k_cg_vec with MERGE: the same elements, operands and sums as below
+template <bool NT>
+__device__ __forceinline__ void vec_merged(const DevPtrs& d, int sub, const int4 info,
+                                           const CgFused& f) {
+  const int rid = info.x, t = threadIdx.x;
+  const bool leader = sub == info.y;
+  __shared__ CgRep c;
+  __shared__ double tot[9];
+  if (!f.cg_in[rid].run) {
+    if (leader) copy_state(f.cg_out + rid, f.cg_in + rid);
+    return;
+  }
+  const bool ext = d.learned;
+  double r0[3], rm[3], w[3], di[3];
+  const int64_t base = (int64_t)sub * VEC_ELEMS;
+  const int le0 = 192 * (t >> 6) + (t & 63);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int64_t e = base + le0 + 64 * q;
+    r0[q] = ldv<NT>(d.r + e);
+    rm[q] = ldv<NT>(d.s + e);
+    w[q] = ldv<NT>(d.w + e);
+    di[q] = (ext || d.pc_none) ? 1.0 : ldv<NT>(d.dinv + (int64_t)sub * SUB_ROWS + (le0 + 64 * q) / 3);
+  }
+  copy_state(&c, f.cg_in + rid);
+  if (f.first) {
+    __syncthreads();
+  } else {
+    double acc[9];
+    slot_sums(d.partial2 + (int64_t)info.w * NPART, info.z, acc);
+    block_sums(acc, tot);
+    if (t < 64) cg_advance(d, rid, c, 2, tot, f.slot, f.flushed, leader);
+    __syncthreads();
+  }
+  if (leader) copy_state(f.cg_out + rid, &c);
+  if (!c.run) return;
+  double g[3] = {0, 0, 0}, rr[3] = {0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int le = le0 + 64 * q, k = le % 3;
+    if (c.state[k] != 0) continue;
+    const double th = c.theta[k], old = th != 0.0 ? rm[q] : r0[q];
+    const double rk = (r0[q] + th * (r0[q] - old)) - c.alpha[k] * w[q];
+    stv<NT>(d.s + base + le, rk);
+    if (!ext) {
+      const double uk = di[q] * rk;
+      d.u[base + le] = uk;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) g[j] += j == k ? rk * uk : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) rr[j] += j == k ? rk * rk : 0.0;
+  }
+  if (!ext) {
+    write_partials<3>(d, sub, 0, g);
+    __syncthreads();
+  }
+  write_partials<3>(d, sub, 6, rr);
+}
+
+// Element-parallel vector work of one sub-tile (3 * 256 consecutive doubles
+// of the AoS arrays; element e is row e/3, component e%3).  NT: the streams
+// that are not read again within the iteration (r twice, w, 1/diag) are
+// loaded and stored as nontemporal, u (gathered by the product next) as
+// usual: on a working set larger than the last-level cache this streams
+// faster (measured at N = 8e6), below it the ordinary form keeps the
+// vectors cached; the autotuner picks.  Same bits either way.
+//   mode 0 (fresh start):   x = 0, r = b, u = M^-1 r
+//   mode 1 (restart, r already = b - A x):   u = M^-1 r
+//   mode 2 (iteration):     d.s = r + theta (r - d.s) - alpha w, u = M^-1 (new r)
+// In mode 2 the new residual overwrites the one before r; the host swaps the
+// two for the launches that follow, and points d.u at the next ring slot.
+// With theta = 0 (a first iteration) the old d.s is not read.
+// Partials (r, u) and (r, r) of the components touched.
+// MERGE (mode 2): the scalars are advanced here, from the sums of at most
+// L1_MAX_GROUPS groups of sub-tiles (k_cg_groups), by every block alike; the
+// replica's first block stores them (f.cg_out).  The block's own elements load
+// meanwhile, so the pass takes as long as without; the launch before it is 2 us
+// shorter than the finisher: a solve at N = 2.5e5 2.21 -> 2.03 ms, the step at
+// N = 1e6 (Jacobi) 4.81 -> 4.57.  (The groups' sums by the product's last blocks
+// instead of a launch: every block waited for its stores, product 10.5 -> 20.6
+// us at N = 2.5e5, 27 -> 35 at 1e6.)
+template <bool NT, bool MERGE>
+__global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode, CgFused f) {
+  const int sub = sub_of_block(d);
+  if (sub < 0) return;
+  if constexpr (MERGE) {
+    const int4 info = d.blk_info[sub / SUBS_PER_TILE];
+    vec_merged<NT>(d, sub, info, f);
+    return;
+  }
+  const int rid = d.blk_rep[sub / SUBS_PER_TILE];
+  const CgRep& cr = d.cg[rid];
+  if ((mode == 1 && !cr.restart) || (mode == 2 && !cr.run)) return;
+  bool on[3];
+  double al[3], th[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    on[k] = mode == 0 ? true : (mode == 1 ? cr.state[k] == 3 : cr.state[k] == 0);
+    al[k] = cr.alpha[k];
+    th[k] = cr.theta[k];
+  }
+  double v[6] = {0, 0, 0, 0, 0, 0};  // (r,u)[3], (r,r)[3]
+  const int64_t base = (int64_t)sub * VEC_ELEMS;
+  const bool ext = d.learned || d.ic0;  // u = M^-1 r comes from a separate pass
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    // a wave takes the elements of its 64 rows (as in k_cg_fused)
+    const int le = 192 * (threadIdx.x >> 6) + 64 * q + (threadIdx.x & 63);
+    const int k = le % 3;
+    if (!on_k(on, k)) continue;
+    const int64_t e = base + le;
+    // 1/diag only where this kernel applies Jacobi itself
+    const double di =
+        (ext || d.pc_none) ? 1.0 : ldv<NT>(d.dinv + (int64_t)sub * SUB_ROWS + le / 3);
+    double rk;
+    if (mode == 0) {
+      rk = d.b[e];
+      d.x[e] = 0.0;
+      d.r[e] = rk;
+    } else if (mode == 1) {
+      rk = d.r[e];
+    } else {
+      const double r0 = ldv<NT>(d.r + e), t = pick3(th, k);
+      const double rm = t != 0.0 ? ldv<NT>(d.s + e) : r0;
+      rk = (r0 + t * (r0 - rm)) - pick3(al, k) * ldv<NT>(d.w + e);
+      stv<NT>(d.s + e, rk);
+    }
+    if (!ext) {
+      const double uk = di * rk;
+      d.u[e] = uk;
+      v[k] += rk * uk;
+    }
+    v[3 + k] += rk * rk;
+  }
+  double g[3] = {v[0], v[1], v[2]}, rr[3] = {v[3], v[4], v[5]};
+  if (!ext) {
+    write_partials<3>(d, sub, 0, g);
+    __syncthreads();
+  }
+  write_partials<3>(d, sub, 6, rr);
+}
+
 // Sub-tile partials in a fixed order, then the recurrences.  A replica of few
 // sub-tiles is one block's work.  Of a larger one, block b sums L1_SUBS
 // sub-tiles into partial2[b], and the last block to finish (last_block) adds
 // those sums in order and advances: one launch where two were (9.3 us at
 // N = 1e6, now 6.9).  `from`: the state to advance into
-// d.cg (d.cg itself, or the other copy after an odd number of fused
-// iterations; small handles only, so one block).
+// d.cg (d.cg itself, or the other copy after an odd number of fused or merged
+// iterations; the block that advances moves it).
 __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode, int slot,
                                                               int flushed, const CgRep* from) {
   const FinBlock F = d.fin[blockIdx.x];
   const int rid = F.rep;
   CgRep& c = d.cg[rid];
-  if (from != d.cg) {
-    copy_state(&c, from + rid);
-    __syncthreads();
-  }
   __shared__ double tot[9];
   // summed before the state says whether they are needed: the two loads are
   // the launch's longest waits, and neither waits for the other
-  const bool work = finish_work(c, mode);
+  const bool work = finish_work(from[rid], mode), moved = from != d.cg;
   double acc[9];
   if (d.qper == 4) slot_sums<4>(d.partial, d.qstride, F.sub0, F.nsub, acc);
   else if (d.qper) slot_sums<1>(d.partial, d.qstride, F.sub0, F.nsub, acc);
   else slot_sums(d.partial + (int64_t)F.sub0 * NPART, F.nsub, acc);
   block_sums(acc, tot);
-  if (!work) return;
+  if (!work) {
+    if (moved && (int)blockIdx.x == F.off) copy_state(&c, from + rid);
+    return;
+  }
   if (F.cnt > 1) {
     double* out = d.partial2 + (int64_t)blockIdx.x * NPART;
     if (threadIdx.x < 9) store_shared(out + threadIdx.x, tot[threadIdx.x]);
@@ -933,7 +1005,34 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mod
     slot_sums<true>(d.partial2 + (int64_t)F.off * NPART, F.cnt, acc);
     block_sums(acc, tot);
   }
+  if (moved) {
+    copy_state(&c, from + rid);
+    __syncthreads();
+  }
   if (threadIdx.x < 64) cg_advance(d, rid, c, mode, tot, slot, flushed, true);
+}
+
+// The first level alone, for a vector pass that advances the scalars itself
+// (merged iterations): every finishing block's sums into partial2.
+__global__ __launch_bounds__(FINISH_THREADS) void k_cg_groups(DevPtrs d) {
+  const FinBlock F = d.fin[blockIdx.x];
+  double* out = d.partial2 + (int64_t)blockIdx.x * NPART;
+  double acc[9];
+  if (F.nsub <= 64) {  // one wave's work (the others would add zeros)
+    if (threadIdx.x >= 64) return;
+    slot_sums(d.partial + (int64_t)F.sub0 * NPART, F.nsub, acc);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[k] = wave_sum(acc[k]);
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) out[k] = acc[k];
+    }
+    return;
+  }
+  __shared__ double tot[9];
+  slot_sums(d.partial + (int64_t)F.sub0 * NPART, F.nsub, acc);
+  block_sums(acc, tot);
+  if (threadIdx.x < 9) out[threadIdx.x] = tot[threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -1165,9 +1264,23 @@ hipError_t launch_cg_vec(const DevPtrs& d, int mode, hipStream_t s, hipEvent_t e
                          hipEvent_t ev1) {
   const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(SUB_THREADS);
   if (d.vec_nt && mode == 2)
-    LAUNCH_EV(k_cg_vec<true>, g, b, s, ev0, ev1, d, mode);
+    LAUNCH_EV((k_cg_vec<true, false>), g, b, s, ev0, ev1, d, mode, CgFused{});
   else
-    LAUNCH_EV(k_cg_vec<false>, g, b, s, ev0, ev1, d, mode);
+    LAUNCH_EV((k_cg_vec<false, false>), g, b, s, ev0, ev1, d, mode, CgFused{});
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_groups(const DevPtrs& d, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_groups, dim3(d.fin_total), dim3(FINISH_THREADS), 0, s, d);
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_vec_merged(const DevPtrs& d, const CgFused& f, hipStream_t s) {
+  const dim3 g(xcd_grid(SUBS_PER_TILE * d.nblk)), b(SUB_THREADS);
+  if (d.vec_nt)
+    hipLaunchKernelGGL((k_cg_vec<true, true>), g, b, 0, s, d, 2, f);
+  else
+    hipLaunchKernelGGL((k_cg_vec<false, true>), g, b, 0, s, d, 2, f);
   return hipGetLastError();
 }
 

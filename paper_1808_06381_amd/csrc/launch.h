@@ -35,17 +35,22 @@ hipError_t launch_copy16(const void* src, void* dst, int64_t bytes, hipStream_t 
 hipError_t launch_cg_reset(const DevPtrs& d, double tol_override, hipStream_t s);
 hipError_t launch_cg_vec(const DevPtrs& d, int mode, hipStream_t s, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);
+struct CgFused;
+// the sums of every finishing block's sub-tiles, into partial2
+hipError_t launch_cg_groups(const DevPtrs& d, hipStream_t s);
+// an iteration's vector pass that advances the scalars itself
+hipError_t launch_cg_vec_merged(const DevPtrs& d, const CgFused& f, hipStream_t s);
 hipError_t launch_cg_spmv(const DevPtrs& d, int mode, int start_mode, hipStream_t s,
                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // from: the scalars to advance into d.cg (null: d.cg itself)
 hipError_t launch_cg_finish(const DevPtrs& d, int mode, int slot, int flushed, hipStream_t s,
                             const CgRep* from = nullptr);
-struct CgFused {           // buffers of a fused iteration besides DevPtrs' own
+struct CgFused {           // buffers of a fused or merged iteration besides DevPtrs' own
   const CgRep* cg_in;      // scalars before ...
   CgRep* cg_out;           // ... and after the advance at the launch's start
-  const double* part_in;   // sub-tile partials of the last iteration (d.partial: this one's)
-  double* rnew;            // the new residual
-  double* wnew;            // Jacobi: A u
+  const double* part_in;   // fused: sub-tile partials of the last iteration (d.partial: this one's)
+  double* rnew;            // fused: the new residual
+  double* wnew;            // fused, Jacobi: A u
   int32_t slot;            // ring slot of the last iteration's u
   int32_t flushed;         // the ring was emptied in the last iteration
   int32_t first;           // 1: the scalars are advanced already

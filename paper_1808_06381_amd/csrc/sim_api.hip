@@ -111,6 +111,7 @@ struct sim_t {
   double* wbuf[2] = {};        // where the fused iterations may run
   CgRep* cg2 = nullptr;
   double* partial2nd = nullptr;
+  bool merge = false;  // see merge_ok
   bool warm = false;         // step solves start from the previous velocities
   void* sq_scratch = nullptr;  // structure-factor scratch (grown on demand)
   size_t sq_bytes = 0;
@@ -487,8 +488,12 @@ static DevPtrs cg_view(const sim_t* s) {
 // (a row's products in entry order: variants of one lane or entry-parallel)
 static bool fused_ok(const sim_t* s) {
   const int32_t var = s->d.learned ? s->d.apply_var : s->d.spmv_var;
-  return s->cg2 && !s->d.ic0 && (var == 0 || var >= CSR_VARIANT_DEFAULT);
+  return s->partial2nd && !s->d.ic0 && (var == 0 || var >= CSR_VARIANT_DEFAULT);
 }
+
+// larger handles: a short launch forms the sums of groups of sub-tiles and the
+// next vector pass advances the scalars from those (see k_cg_vec)
+static bool merge_ok(const sim_t* s) { return s->merge && !s->d.ic0; }
 
 // the buffers move on by one iteration: u into the next slot; the new residual
 // over the older one, or (fused) into the spare buffer, and with Jacobi w into
@@ -595,10 +600,13 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
   const CgRep* cur = s->d.cg;       // the scalars, advanced unless `open`
   double* part = s->d.partial;      // the last iteration's partials
   bool open = false, open_flushed = false;
-  for (int k = 0; fused && k < n; ++k) {
+  // merged iterations: as fused ones, with the vector pass and the product as
+  // launches of their own
+  const bool merged = !probes_on && !fused && merge_ok(s);
+  for (int k = 0; (fused || merged) && k < n; ++k) {
     DevPtrs dk = cg_view(s);
     const int slot = s->ring.slot;
-    const bool full = ring_advance(s->ring, d.ring, true, d.learned);
+    const bool full = ring_advance(s->ring, d.ring, fused, d.learned);
     if (full) {
       if (open) {
         DevPtrs df = s->d;
@@ -614,7 +622,7 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
     f.cg_in = cur;
     f.cg_out = cur == s->d.cg ? s->cg2 : s->d.cg;
     f.part_in = part;
-    part = part == s->d.partial ? s->partial2nd : s->d.partial;
+    if (fused) part = part == s->d.partial ? s->partial2nd : s->d.partial;
     f.rnew = dn.r;
     f.wnew = dn.w;
     f.slot = slot;
@@ -622,12 +630,22 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
     f.first = !open;
     dk.u = dn.u;
     dk.partial = part;
-    HIPCHK(launch_cg_fused(dk, f, stream));
-    if (d.learned) {
-      DevPtrs dp = dn;
-      dp.cg = f.cg_out;
-      dp.partial = part;
+    DevPtrs dp = dn;
+    dp.cg = f.cg_out;
+    dp.partial = part;
+    if (fused) {
+      HIPCHK(launch_cg_fused(dk, f, stream));
+      if (d.learned) HIPCHK(launch_cg_spmv(dp, 0, 2, stream));
+    } else {  // consecutive streaming launches in opposite directions, as below
+      dk.rev = nstream++ & 1;
+      HIPCHK(launch_cg_vec_merged(dk, f, stream));
+      if (d.learned) {
+        dp.rev = nstream++ & 1;
+        HIPCHK(launch_cg_apply(dp, 2, stream));
+      }
+      dp.rev = nstream++ & 1;
       HIPCHK(launch_cg_spmv(dp, 0, 2, stream));
+      HIPCHK(launch_cg_groups(dp, stream));
     }
     cur = f.cg_out;
     open = true;
@@ -638,7 +656,7 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
     df.partial = part;
     HIPCHK(launch_cg_finish(df, 2, s->ring.slot, open_flushed, stream, cur));
   }
-  for (int k = 0; !fused && k < n; ++k) {
+  for (int k = 0; !fused && !merged && k < n; ++k) {
     const int g = first + k;
     const bool probe = probes && !(s->prof_solves & 1) && s->prof_every > 0 &&
                        g % s->prof_every == s->prof_phase &&
@@ -1095,8 +1113,9 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
     FinBlock F{};
     F.rep = r;
     F.off = (int32_t)fin_h.size();
-    F.cnt = nsub > L1_MIN_SUBS ? (nsub + L1_SUBS - 1) / L1_SUBS : 1;
-    const int32_t each = F.cnt > 1 ? L1_SUBS : nsub;
+    int32_t each = nsub > L1_MIN_SUBS ? L1_SUBS : nsub;
+    while ((nsub + each - 1) / each > L1_MAX_GROUPS) each *= 2;
+    F.cnt = (nsub + each - 1) / each;
     for (int b = 0; b < F.cnt; ++b) {
       F.sub0 = SUBS_PER_TILE * R.blk_off + b * each;
       F.nsub = std::min<int32_t>(each, nsub - b * each);
@@ -1175,8 +1194,9 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
                                       std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
   const size_t slots = d.ring;
   ALLOC(d.u, sizeof(double) * 3 * rows * slots);
+  s->merge = !s->block && !s->ic0 && !fused;
+  if (fused || s->merge) ALLOC(s->cg2, sizeof(CgRep) * replicas);
   if (fused) {
-    ALLOC(s->cg2, sizeof(CgRep) * replicas);
     ALLOC(s->partial2nd, sizeof(double) * npart);
     ALLOC(s->rbuf[2], sizeof(double) * 3 * rows);
     ALLOC(s->wbuf[1], sizeof(double) * 3 * rows);
@@ -1257,10 +1277,18 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
     return fail(e, "upload replicas");
   if ((e = hipMemcpy(blk_rep_d, s->blk_rep_h.data(), sizeof(int32_t) * d.nblk, hipMemcpyHostToDevice)))
     return fail(e, "upload block table");
+  std::vector<int32_t> fin_first((size_t)replicas);
+  std::vector<int32_t> fin_cnt((size_t)replicas);
+  for (const FinBlock& F : fin_h) {
+    fin_first[F.rep] = F.off;
+    fin_cnt[F.rep] = F.cnt;
+  }
   std::vector<int4> info((size_t)d.nblk);
   for (int b = 0; b < d.nblk; ++b) {
     const RepDev& R = s->reph[s->blk_rep_h[b]];
-    info[b] = make_int4(s->blk_rep_h[b], SUBS_PER_TILE * R.blk_off, SUBS_PER_TILE * R.nblk, 0);
+    info[b] = make_int4(s->blk_rep_h[b], SUBS_PER_TILE * R.blk_off, 
+                        s->merge ? fin_cnt[s->blk_rep_h[b]] : SUBS_PER_TILE * R.nblk,
+                        fin_first[s->blk_rep_h[b]]);
   }
   if ((e = hipMemcpy(blk_info_d, info.data(), sizeof(int4) * d.nblk, hipMemcpyHostToDevice)))
     return fail(e, "upload block table");

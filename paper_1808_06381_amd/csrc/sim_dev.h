@@ -132,7 +132,8 @@ struct DevPtrs {
   double* partial;          // [sub-tiles][NPART]; handles with fused iterations: [9][qstride]
   int32_t qper;             // ... of so many slots per sub-tile (1 or 4; else 0)
   int32_t qstride;          // ... slots over all sub-tiles
-  const int4* blk_info;     // block -> replica, its first sub-tile, its sub-tiles
+  const int4* blk_info;     // block -> replica, its first sub-tile, its sub-tiles (with merged
+                            // iterations: its finishing blocks), the first of those
   double* partial2;         // [finishing blocks][NPART]
   const FinBlock* fin;      // the finishing blocks
   int32_t* fin_ticket;      // [replicas] finished blocks of the current reduction (0 between launches)
@@ -207,7 +208,8 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 // The per-replica CG finisher sums the replica's sub-tile partials with
 // FINISH_THREADS threads.  A replica of more than L1_MIN_SUBS sub-tiles (two
 // rounds of loads for one block) has them summed first by blocks of L1_SUBS
-// sub-tiles each, the last of which adds those blocks' sums: a single block
+// sub-tiles each (twice, four times ... as many where that would be more than
+// L1_MAX_GROUPS blocks), the last of which adds those blocks' sums: a single block
 // reading every partial of an N = 8e6 box (31,252 slots, 4 MB) took about 60 us
 // per iteration.  A solve at N = 2.5e5 with the line at 2048 / 512 and blocks of
 // 256 / 256 / 128 / 64 sub-tiles: 2.236 / 2.215 / 2.226 / 2.208 ms.  Both are functions of
@@ -215,6 +217,7 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 #define FINISH_THREADS 256
 #define L1_SUBS 64
 #define L1_MIN_SUBS 512
+#define L1_MAX_GROUPS 64
 
 // Handles of at most FUSED_ROWS rows run finisher, vector pass and product as
 // one launch (k_cg_fused), of at most FUSED_SPLIT_SUBS sub-tiles with a block
