@@ -370,7 +370,7 @@ def iteration_roofline(r, copy_gbs, traffic):
     out = dict(bound="hbm", achieved=round(it["gbs"], 1), peak=PEAK_HBM_GBS, unit="GB/s",
                frac=round(it["gbs"] / PEAK_HBM_GBS, 4),
                traffic=None if traffic is None else traffic["bytes_per_iteration"],
-               kernel="cg_iteration: k_cg_vec + k_cg_apply + k_cg_spmv + k_cg_finish and the "
+               kernel="cg_iteration: k_cg_vec + k_cg_apply + k_cg_spmv + k_cg_groups and the "
                       "gaps between them",
                basis="algorithmic bytes per CG iteration: 12(k+1)+4 (matrix) + 200 (vectors) per "
                      "particle, + 12(k+1)+4 for the learned M^-1 product",

@@ -417,7 +417,8 @@ int sim_debug_precond(sim_t* sim, int64_t* rows, int64_t* cols, double* vals, in
  * every sample_every-th CG iteration has its three kernels (k_cg_vec,
  * k_cg_spmv, k_cg_apply) bracketed by HIP events on the library's stream
  * (the sampled residue of the iteration index advances by one per such
- * solve, so every position in a solve is sampled alike).  Iteration form
+ * solve, so every position in a solve is sampled alike); the scalars are
+ * then advanced by a launch of their own (the same bits).  Iteration form
  * ("cg_iteration"): one event pair around the first chunk's iterations
  * except its last two -- every kernel, the finisher and the gaps between
  * launches -- counted as that many launches, each priced at the solve's

@@ -23,15 +23,19 @@
 //
 // Per iteration three launches (four with the learned M^-1 product,
 // k_cg_apply), none with a cache write-back fence:
-//   k_cg_vec   the new residual (and u with Jacobi), element-parallel (fully
-//              coalesced), and the partial sums of (r, u) and (r, r) per
-//              sub-tile of 256 rows;
+//   k_cg_vec   the scalar recurrences and the convergence state (every block
+//              alike, from k_cg_groups' sums), then the new residual (and u
+//              with Jacobi), element-parallel (fully coalesced), and the
+//              partial sums of (r, u) and (r, r) per sub-tile of 256 rows;
 //   k_cg_spmv  w = A u, by default entry-parallel (the sub-tile's entries
 //              striped over its threads, the products summed per row from
 //              LDS), or with a group of 1, 2, 4 or 8 lanes per CSR row (the
 //              tuning variants); partial sums of (w, u);
-//   k_cg_finish one block per replica: the sub-tile partials in a fixed order,
-//              then the scalar recurrences and the convergence state.
+//   k_cg_groups the partials of at most 64 groups of sub-tiles per replica, in
+//              a fixed order.
+// Starts, checks, passes over the ring, IC(0) and solves under the timing probe
+// use k_cg_finish (the same sums, then the recurrences) instead; small handles
+// run an iteration as one launch, k_cg_fused.
 // Sums are deterministic (fixed trees, no floating-point atomics).
 #include "sim_dev.h"
 #include "launch.h"

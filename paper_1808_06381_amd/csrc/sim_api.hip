@@ -586,9 +586,9 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
   // iteration form of the probe: an event before iteration 0 of the first
   // chunk and one after each of its iterations; the poll keeps the longest
   // run of iterations that every component went through
-  const bool probes_on = probes && s->prof_every > 0;  // times the separate kernels
   const bool run_form = probes && s->prof_every > 0 && (s->prof_solves & 1) && first == 0 &&
                         n + 1 <= (int)s->prof_run_ev.size();
+  const bool probes_on = probes && s->prof_every > 0 && !run_form;  // times the separate kernels
   if (run_form) {
     s->prof_run_n = n;
     HIPCHK(hipEventRecord(s->prof_run_ev[0], stream));
@@ -647,6 +647,7 @@ static int cg_queue_chunk(sim_t* s, int n, int first, bool probes) {
       HIPCHK(launch_cg_spmv(dp, 0, 2, stream));
       HIPCHK(launch_cg_groups(dp, stream));
     }
+    if (run_form) HIPCHK(hipEventRecord(s->prof_run_ev[k + 1], stream));
     cur = f.cg_out;
     open = true;
     open_flushed = full;
@@ -1152,9 +1153,14 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   int32_t* blk_rep_d = nullptr;
   ALLOC(blk_rep_d, sizeof(int32_t) * d.nblk);
   d.blk_rep = blk_rep_d;
-  int4* blk_info_d = nullptr;
-  ALLOC(blk_info_d, sizeof(int4) * d.nblk);
-  d.blk_info = blk_info_d;
+  // one table, uploaded at once: block entries, finishing blocks, their tickets (zero)
+  const size_t info_b = sizeof(int4) * d.nblk, fin_b = sizeof(FinBlock) * fin_h.size();
+  std::vector<char> table(info_b + fin_b + sizeof(int32_t) * replicas);
+  char* table_d = nullptr;
+  ALLOC(table_d, table.size());
+  d.blk_info = reinterpret_cast<const int4*>(table_d);
+  d.fin = reinterpret_cast<const FinBlock*>(table_d + info_b);
+  d.fin_ticket = reinterpret_cast<int32_t*>(table_d + info_b + fin_b);
   // handles with fused iterations keep a partial per wave, one array per sum
   const bool fused = !s->block && !s->ic0 && s->rows <= FUSED_ROWS;
   d.qper = fused ? (SUBS_PER_TILE * d.nblk <= FUSED_SPLIT_SUBS ? 4 : 1) : 0;
@@ -1162,10 +1168,6 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   const size_t npart = fused ? (size_t)9 * d.qstride : (size_t)NPART * SUBS_PER_TILE * d.nblk;
   ALLOC(d.partial, sizeof(double) * npart);
   ALLOC(d.partial2, sizeof(double) * NPART * d.fin_total);
-  FinBlock* fin_d = nullptr;
-  ALLOC(fin_d, sizeof(FinBlock) * fin_h.size());
-  d.fin = fin_d;
-  ALLOC(d.fin_ticket, sizeof(int32_t) * replicas);
   ALLOC(d.pos, sizeof(double4) * rows);
   ALLOC(d.pos_alt, sizeof(double4) * rows);
   ALLOC(d.cellidx, sizeof(int32_t) * rows);
@@ -1277,25 +1279,23 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
     return fail(e, "upload replicas");
   if ((e = hipMemcpy(blk_rep_d, s->blk_rep_h.data(), sizeof(int32_t) * d.nblk, hipMemcpyHostToDevice)))
     return fail(e, "upload block table");
-  std::vector<int32_t> fin_first((size_t)replicas);
-  std::vector<int32_t> fin_cnt((size_t)replicas);
-  for (const FinBlock& F : fin_h) {
-    fin_first[F.rep] = F.off;
-    fin_cnt[F.rep] = F.cnt;
+  {
+    std::vector<int32_t> fin_first((size_t)replicas), fin_cnt((size_t)replicas);
+    for (const FinBlock& F : fin_h) {
+      fin_first[F.rep] = F.off;
+      fin_cnt[F.rep] = F.cnt;
+    }
+    int4* info = reinterpret_cast<int4*>(table.data());
+    for (int b = 0; b < d.nblk; ++b) {
+      const int r = s->blk_rep_h[b];
+      const RepDev& R = s->reph[r];
+      info[b] = make_int4(r, SUBS_PER_TILE * R.blk_off,
+                          s->merge ? fin_cnt[r] : SUBS_PER_TILE * R.nblk, fin_first[r]);
+    }
+    memcpy(table.data() + info_b, fin_h.data(), fin_b);
   }
-  std::vector<int4> info((size_t)d.nblk);
-  for (int b = 0; b < d.nblk; ++b) {
-    const RepDev& R = s->reph[s->blk_rep_h[b]];
-    info[b] = make_int4(s->blk_rep_h[b], SUBS_PER_TILE * R.blk_off, 
-                        s->merge ? fin_cnt[s->blk_rep_h[b]] : SUBS_PER_TILE * R.nblk,
-                        fin_first[s->blk_rep_h[b]]);
-  }
-  if ((e = hipMemcpy(blk_info_d, info.data(), sizeof(int4) * d.nblk, hipMemcpyHostToDevice)))
-    return fail(e, "upload block table");
-  if ((e = hipMemcpy(fin_d, fin_h.data(), sizeof(FinBlock) * fin_h.size(),
-                     hipMemcpyHostToDevice)))
-    return fail(e, "upload reduction table");
-  if ((e = hipMemset(d.fin_ticket, 0, sizeof(int32_t) * replicas))) return fail(e, "clear tickets");
+  if ((e = hipMemcpy(table_d, table.data(), table.size(), hipMemcpyHostToDevice)))
+    return fail(e, "upload block and reduction tables");
   if (s->block) {
     std::vector<BlockRep> br((size_t)replicas);
     for (int r = 0; r < replicas; ++r) {

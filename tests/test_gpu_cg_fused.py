@@ -25,7 +25,7 @@ def both(cfgs, steps=3, tol=1e-10, **kw):
         with S.Sim(cfgs, pos, tol=tol, **kw) as sim:
             if kw.get("precond") == "learned":
                 sim.load_precond(WEIGHTS)
-            sim.profile_enable(probe)   # 1: every step by the separate kernels
+            sim.profile_enable(probe)   # 1: every other step by the separate kernels
             its = [tuple(sim.step(1)["iters"]) for _ in range(steps)]
             out.append(sim.state()[:2] + (its,))
     assert out[0][2] == out[1][2], (out[0][2], out[1][2])

@@ -1,8 +1,8 @@
 """Handles past the fused iterations' size advance the CG scalars in the vector
-pass, from sums that the product's last blocks leave per group of sub-tiles.
-They must give the bits of the separate finisher, which the timing probe
-selects: one group and several, the largest replica that takes them and one
-sub-tile more, uneven batches, replicas that finish early, rings that wrap."""
+pass, from sums that a short launch leaves per group of sub-tiles.  They must
+give the bits of the separate finisher, which the timing probe selects in
+every other solve: one group and several, groups of 64 and of 128 sub-tiles,
+uneven batches, replicas that finish early, rings that wrap."""
 import numpy as np
 import pytest
 
