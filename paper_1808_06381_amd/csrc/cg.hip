@@ -1063,19 +1063,26 @@ __global__ __launch_bounds__(FINISH_THREADS) void k_cg_groups(DevPtrs d) {
 // (N = 1000, ten steps: 7.4 -> 5.5 ms); every block of it writes one slot per
 // sum and reads four per sub-tile of its replica, in the order in which a
 // 256-row block adds its waves, so both forms give the same bits.
+// A 256-row block (W = 4) takes two entries per thread and pass: a pass is a
+// barrier, a chain of a row's additions and another barrier, and with one entry
+// per thread the paper's box (15 entries per row) had 7.5 of them in 23 us; the
+// additions' operands are read four at a time.  4 x 20060 rows, ten steps: 16.8
+// -> 15.4 -> 14.8 ms, N = 1e5 learned 1.91 -> 1.80 (three entries per thread: 19.4
+// and 1.88, three waves per SIMD; eight operands: 15.7).
 // The times and the limits are beside FUSED_ROWS.
 // ---------------------------------------------------------------------------
 template <int T, int W, bool LEARNED, bool FP32>
 __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
   constexpr int ROWS = 64 * W, QPER = 4 / W;
   constexpr int RC = T >= 256 * W ? 1 : 3;      // components per row thread
+  constexpr int EPT = W == 4 ? 2 : 1, CAP = EPT * T;  // entries per thread and pass
   constexpr int RWAVES = W * (3 / RC);          // waves W .. W + RWAVES - 1
   static_assert(T >= FINISH_THREADS && T >= 64 * (W + RWAVES) && CG_WORDS <= 64, "roles of waves");
   const int per = QPER * ((SUBS_PER_TILE * d.nblk + 7) >> 3);  // blocks per XCD, whole sub-tiles
   const int qb = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (qb >= QPER * SUBS_PER_TILE * d.nblk) return;
   __shared__ CgRep c;
-  __shared__ double prod[3][T];
+  __shared__ double prod[3][CAP];
   __shared__ double io[3 * ROWS];     // the source's own rows
   __shared__ double res[3 * ROWS];    // the results
   __shared__ double lds[FINISH_THREADS / 64][9];
@@ -1117,22 +1124,34 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
     else return d.val[e];
   };
   using VT = decltype(value(0));
-  VT m = VT(0);
-  double gr[3], gs[3], gw[3], gd = 1.0;
-  auto load = [&](int e) {   // entry e of the block and the rows it gathers
-    const int j = d.col[E0 + e];
-    m = value(E0 + e);
+  VT m[EPT];
+  double gr[EPT][3], gs[EPT][3], gw[EPT][3], gd[EPT];
+  auto load = [&](int c0) {   // entries of the pass at c0 and the rows they gather
+    int j[EPT];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      gr[k] = d.r[3 * (int64_t)j + k];
-      gs[k] = d.s[3 * (int64_t)j + k];
-      gw[k] = d.w[3 * (int64_t)j + k];
+    for (int q = 0; q < EPT; ++q) {
+      const int e = c0 + q * T + t;
+      j[q] = -1;
+      if (e < ne) {
+        j[q] = d.col[E0 + e];
+        m[q] = value(E0 + e);
+      }
     }
-    if (!LEARNED && !d.pc_none) gd = d.dinv[j];
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+      if (j[q] < 0) continue;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        gr[q][k] = d.r[3 * (int64_t)j[q] + k];
+        gs[q][k] = d.s[3 * (int64_t)j[q] + k];
+        gw[q][k] = d.w[3 * (int64_t)j[q] + k];
+      }
+      gd[q] = LEARNED || d.pc_none ? 1.0 : d.dinv[j[q]];
+    }
   };
   if (t < CG_WORDS)
     reinterpret_cast<uint64_t*>(&c)[t] = reinterpret_cast<const uint64_t*>(f.cg_in + rid)[t];
-  if (t < ne) load(t);
+  load(0);
   double acc[9];
   if (!f.first && t < FINISH_THREADS) {
     slot_sums<QPER>(f.part_in, d.qstride, info.y, info.z, acc);
@@ -1193,25 +1212,28 @@ __global__ __launch_bounds__(T) void k_cg_fused(DevPtrs d, CgFused f) {
     }
   }
   double a[RC] = {};
-  for (int c0 = 0; c0 < ne; c0 += T) {
-    if (c0 + t < ne) {
+  for (int c0 = 0; c0 < ne; c0 += CAP) {
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+      if (c0 + q * T + t >= ne) continue;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        double src = next(gr[k], gs[k], gw[k], al[k], th[k]);
-        if constexpr (!LEARNED) src = gd * src;
-        prod[k][t] = (double)m * src;
+        double src = next(gr[q][k], gs[q][k], gw[q][k], al[k], th[k]);
+        if constexpr (!LEARNED) src = gd[q] * src;
+        prod[k][q * T + t] = (double)m[q] * src;
       }
-      if (c0 + T + t < ne) load(c0 + T + t);
     }
+    if (c0 + CAP < ne) load(c0 + CAP);
     __syncthreads();
     if (sums) {
-      const int lo = r0 > c0 ? r0 : c0, hi = r1 < c0 + T ? r1 : c0 + T;
+      const int lo = r0 > c0 ? r0 : c0, hi = r1 < c0 + CAP ? r1 : c0 + CAP;
+#pragma unroll 4
       for (int e = lo; e < hi; ++e) {
 #pragma unroll
         for (int k = 0; k < RC; ++k) a[k] += prod[comp + k][e - c0];
       }
     }
-    if (c0 + T < ne) __syncthreads();
+    if (c0 + CAP < ne) __syncthreads();
   }
   if (ne == 0) __syncthreads();
   if (elems) {

@@ -221,16 +221,15 @@ static_assert(sizeof(DevPtrs) % 8 == 0, "DevPtrs must have no implicit tail padd
 
 // Handles of at most FUSED_ROWS rows run finisher, vector pass and product as
 // one launch (k_cg_fused), of at most FUSED_SPLIT_SUBS sub-tiles with a block
-// per 64 rows (512 threads), else per 256.  Per step in us, separate kernels /
-// 256-row blocks / 64-row blocks, one box of 5.5 entries per row: Jacobi
-// N = 1000 1200 / 714 / 522, 8000 - / 874 / 613, 32000 - / 1061 / 842,
-// 64000 - / 1127 / 1390, 120000 - / 1474 / 2621; learned 1000 - / 588 / 502,
-// 32000 - / 826 / 742, 64000 - / 931 / 1060; past two blocks per unit (32768
-// rows) the finer split is at once the slower one: Jacobi N = 33000 1071 and
+// per 64 rows (512 threads), else per 256.  Per step in us, 256-row / 64-row
+// blocks, one box of 5.5 entries per row: Jacobi N = 1000 714 / 522, 8000 874 /
+// 613, 32000 1061 / 842, 64000 1127 / 1390, 120000 1474 / 2621; learned 1000
+// 588 / 502, 32000 826 / 742, 64000 931 / 1060; past two blocks per unit (32768
+// rows) the finer split is at once the slower one: Jacobi N = 33000 947 and
 // 1168.  256 or 1024 threads per 64 rows: N = 1000 569 and 630.
 // The other line is also two blocks per unit: fused / separate (advancing in the
-// vector pass) N = 90000 1332 / 1715, 130000 1451 / 1779, 140000 2052 / 1898,
-// 250000 2679 / 2382; learned 130000 1140 / 1282, 140000 1437 / 1334.
+// vector pass) N = 90000 1271 / 1715, 130000 1371 / 1779, 140000 2052 / 1875;
+// learned 130000 1097 / 1282, 140000 1437 / 1331.
 #define FUSED_ROWS (128 * 1024)
 #define FUSED_SPLIT_SUBS 128
 // ... and handles of at most so many sub-tiles add the ring to x with a thread
