@@ -412,8 +412,9 @@ __device__ __forceinline__ bool cell_inside(const RepDev& R, int cx, int cy, int
 template <typename F>
 __device__ __forceinline__ void for_candidates_inside(const RepDev& R, const int32_t* cell_row,
                                                       int cx, int cy, int cz, int64_t self, F&& f) {
-  const int first = ((((cx - 1) >> R.bshift) + 1) << R.bshift) - (cx - 1);  // cells to the brick's end
-  const int run = R.bshift < 31 && first < 3 ? first : 3;
+  // cells to the brick's end (a power of two long, where there are bricks)
+  const int first = R.bshift < 31 ? R.brick - ((cx - 1) & (R.brick - 1)) : 3;
+  const int run = first < 3 ? first : 3;
   for (int dz = -1; dz <= 1; ++dz)
     for (int dy = -1; dy <= 1; ++dy) {
       int c0 = R.seg_off + cell_key(R, cx - 1, cy + dy, cz + dz);
