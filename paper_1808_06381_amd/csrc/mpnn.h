@@ -11,7 +11,6 @@
 #define MP_THREADS 256 // threads per block (8 nodes x 32 features)
 #define MP_ROWS 64     // rows per block
 #define MP_MSG 0.125f  // message scale
-#define MP_BW_BLOCKS 4096 // blocks of a layer's backward kernels at most
 #define MP_GSLICES 32     // slices of the parameter gradient's sum over blocks
 #define MP_EPS_LAM 0.3 // default floor of the diagonal head lam
 

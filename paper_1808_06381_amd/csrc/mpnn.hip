@@ -999,13 +999,27 @@ __device__ __forceinline__ int bw_row(int r) {
   return 8 * (r >> 2) + 4 * ((threadIdx.x & 63) >> 5) + (r & 3);
 }
 
-// acc[k][q] += sum over the tile's MP_ROWS rows of x[row][k] z[row][q]
-__device__ __forceinline__ void bw_outer(const float* x, const float* z, f32x16& acc) {
+// sum over the tile's MP_ROWS rows of x[row][k] z[row][q]: the rows n, n + NODES,
+// ... in one product chain each, then those NODES sums in order: eight and eight
+// roundings, as sums kept per node have.  (dU at 2000 rows is 2.8e-8 of its norm
+// from the 64-bit gradient; with one chain over the 64 rows it was 3.5e-8.  The
+// time is the same.)
+__device__ __forceinline__ f32x16 bw_outer(const float* x, const float* z) {
   const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
-#pragma unroll 8
-  for (int r = 0; r < MP_ROWS; r += 2)
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[(r + hi) * BW_S + lo], z[(r + hi) * BW_S + lo],
-                                               acc, 0, 0, 0);
+  f32x16 acc;
+#pragma unroll
+  for (int n = 0; n < NODES; ++n) {
+    f32x16 part;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[r] = 0.0f;
+#pragma unroll
+    for (int p = 0; p < PASSES; p += 2) {
+      const int o = (n + NODES * (p + hi)) * BW_S + lo;
+      part = __builtin_amdgcn_mfma_f32_32x32x2f32(x[o], z[o], part, 0, 0, 0);
+    }
+    acc = n == 0 ? part : acc + part;
+  }
+  return acc;
 }
 
 // out[row][k] = sum_q x[row][q] W[q][k] for the 32 rows from `row0` (W row-major)
@@ -1025,23 +1039,6 @@ __device__ __forceinline__ void bw_store_matrix(const f32x16& acc, float* dst) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) dst[bw_row(r) * MP_H + (threadIdx.x & 31)] = acc[r];
 }
-
-// Blocks of the layers' backward kernels: each walks a share of the tiles of
-// one XCD's contiguous eighth (the gathered rows stay in that XCD's L2) and
-// leaves one set of partial sums.
-static inline unsigned bw_blocks(int64_t ntiles) {
-  const int64_t n8 = (ntiles + 7) / 8, per = (8 * n8 + MP_BW_BLOCKS - 1) / MP_BW_BLOCKS;
-  return (unsigned)(8 * ((n8 + per - 1) / per));
-}
-struct BwTiles {
-  int tile, end, step;
-  __device__ explicit BwTiles(int ntiles) {
-    const int n8 = (ntiles + 7) >> 3, x = blockIdx.x & 7;
-    tile = x * n8 + (blockIdx.x >> 3);
-    end = min((x + 1) * n8, ntiles);
-    step = gridDim.x >> 3;
-  }
-};
 
 // heads: dL/dh^3 (into dh) and the head parameters v, v0, z, ze, z0.  The
 // FP64 work of an entry (dL/dS of it and of its reverse) is done once, by one
@@ -1149,15 +1146,21 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_heads_bwd(DevPtrs d, MpPtrs m
 }
 
 // layer l backward, part A (per node i): da = dh * [a > 0];
-// dU, dV, dd; dh_in = dh + U^T da; dm = V^T da.  A block walks its tiles of 64
-// rows: the tile's da, h and m go to LDS, then wave 0 adds da h^T to dU, wave 1
-// da m^T to dV, waves 2 and 3 form U^T da and V^T da, all as FP32 matrix
-// products; the accumulators stay in registers over the tiles.  (One lane per
-// feature walking 32 x 32 scalar products took 204 us at 1e5 rows; 50 us now)
+// dU, dV, dd; dh_in = dh + U^T da; dm = V^T da.  A block owns a tile of 64 rows:
+// its da, h and m go to LDS, then wave 0 forms da h^T (dU), wave 1 da m^T (dV),
+// waves 2 and 3 U^T da and V^T da, all as FP32 matrix products.  Every tile
+// leaves its own FP32 sums, which k_mp_grad_part adds in FP64.  (One lane per
+// feature walking 32 x 32 scalar products took 204 us at 1e5 rows; 51 us
+// now.  Blocks that walked several tiles with their sums in FP32 registers lost
+// the FP64 sum over tiles; a probe step at N = 2e6 took 11.0 ms with them, 11.5
+// so)
 __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_a(DevPtrs d, MpPtrs m, int l) {
   __shared__ float UV[2][MP_H * MP_H];
   __shared__ float sda[MP_ROWS * BW_S], shm[2][MP_ROWS * BW_S];
   __shared__ float red[NODES * MP_H];
+  const int tile = xcd_block(blockIdx.x, (int)(m.rows / MP_ROWS));   // XCD-contiguous tiles
+  if (tile >= m.rows / MP_ROWS) return;
+  const int64_t i0 = (int64_t)tile * MP_ROWS;
   const int base = MP_OFF_L0 + l * MP_L_SIZE;
   load_w(m, UV[0], base + MP_L_U, MP_H * MP_H);
   load_w(m, UV[1], base + MP_L_V, MP_H * MP_H);
@@ -1166,39 +1169,34 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_a(DevPtrs d, MpPtrs
   const float* __restrict__ mm = m.m + (int64_t)l * m.rows * MP_H;
   const float* __restrict__ aa = m.a + (int64_t)l * m.rows * MP_H;
   f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
   float accd = 0.0f;
-  for (BwTiles w((int)(m.rows / MP_ROWS)); w.tile < w.end; w.tile += w.step) {
-    const int64_t i0 = (int64_t)w.tile * MP_ROWS;
 #pragma unroll
-    for (int pass = 0; pass < PASSES; ++pass) {
-      const int row = pass * NODES + slot;
-      const int64_t o = (i0 + row) * MP_H + k;
-      const float da = aa[o] > 0.0f ? m.dh[o] : 0.0f;
-      accd += da;
-      sda[row * BW_S + k] = da;
-      shm[0][row * BW_S + k] = act_in(m, hin[o]);
-      shm[1][row * BW_S + k] = act_in(m, mm[o]);
-    }
-    __syncthreads();
-    if (wave < 2) {
-      bw_outer(sda, shm[wave], acc);
-    } else {
+  for (int pass = 0; pass < PASSES; ++pass) {
+    const int row = pass * NODES + slot;
+    const int64_t o = (i0 + row) * MP_H + k;
+    const float da = aa[o] > 0.0f ? m.dh[o] : 0.0f;
+    accd += da;
+    sda[row * BW_S + k] = da;
+    shm[0][row * BW_S + k] = act_in(m, hin[o]);
+    shm[1][row * BW_S + k] = act_in(m, mm[o]);
+  }
+  __syncthreads();
+  if (wave < 2) {
+    acc = bw_outer(sda, shm[wave]);
+  } else {
 #pragma unroll
-      for (int row0 = 0; row0 < MP_ROWS; row0 += 32) {
-        const f32x16 s = bw_rows(sda, row0, UV[wave - 2]);
+    for (int row0 = 0; row0 < MP_ROWS; row0 += 32) {
+      const f32x16 s = bw_rows(sda, row0, UV[wave - 2]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t o = (i0 + row0 + bw_row(r)) * MP_H + k;
-          if (wave == 2) m.dh2[o] = m.dh[o] + s[r];
-          else m.dm[o] = s[r];
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int64_t o = (i0 + row0 + bw_row(r)) * MP_H + k;
+        if (wave == 2) m.dh2[o] = m.dh[o] + s[r];
+        else m.dm[o] = s[r];
       }
     }
-    __syncthreads();
   }
-  float* dst = m.gpart + (int64_t)blockIdx.x * MP_NPARAMS_ALL + base;
+  __syncthreads();
+  float* dst = m.gpart + (int64_t)tile * MP_NPARAMS_ALL + base;
   if (wave == 0) bw_store_matrix(acc, dst + MP_L_U);
   if (wave == 1) bw_store_matrix(acc, dst + MP_L_V);
   slot_reduce_store(accd, red, dst + MP_L_D);
@@ -1207,10 +1205,10 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_a(DevPtrs d, MpPtrs
 // layer l backward, part B (per node j, pulling from its neighbours i):
 // dy_j = 1/8 sum_i dm_i [y_j + Q e_ij + c > 0]; dQ, dc, dP; dh_in_j += P^T dy_j.
 // Half a wave per row walks its entries, a feature per lane, four gathers in
-// flight; the tile's dy and h go to LDS, then wave 0 adds dy h^T to dP and
-// waves 1 and 2 form P^T dy as FP32 matrix products (210 us at 1e5 rows with
-// scalar products, two barriers per eight rows and three dependent loads per
-// entry; 86 us now).
+// flight; the tile's dy and h go to LDS, then wave 0 forms dy h^T (dP) and
+// waves 1 and 2 P^T dy as FP32 matrix products (210 us at 1e5 rows with scalar
+// products, two barriers per eight rows and three dependent loads per entry;
+// 69 us now).
 constexpr int BB_E = 512;   // entries staged at a time
 __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_b(DevPtrs d, MpPtrs m, int l) {
   if (d.ctrl->overflow) return;  // row pointers may exceed the capacity
@@ -1219,6 +1217,9 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_b(DevPtrs d, MpPtrs
   __shared__ float red[NODES * MP_H];
   __shared__ int rp[MP_ROWS + 1];
   __shared__ float4 sef[BB_E];   // an entry's features and its column
+  const int tile = xcd_block(blockIdx.x, (int)(m.rows / MP_ROWS));   // XCD-contiguous tiles
+  if (tile >= m.rows / MP_ROWS) return;
+  const int64_t i0 = (int64_t)tile * MP_ROWS;
   const int base = MP_OFF_L0 + l * MP_L_SIZE;
   load_w(m, P, base + MP_L_P, MP_H * MP_H);
   load_w(m, Q, base + MP_L_Q, MP_H * MP_FE);
@@ -1229,70 +1230,65 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_layer_bwd_b(DevPtrs d, MpPtrs
   const float* __restrict__ y = m.y + (int64_t)l * m.rows * MP_H;
   const float q0 = Q[k * MP_FE], q1 = Q[k * MP_FE + 1], q2 = Q[k * MP_FE + 2], ck = c[k];
   f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
   float accQ[MP_FE] = {0.0f, 0.0f, 0.0f}, accc = 0.0f;
-  for (BwTiles w((int)(m.rows / MP_ROWS)); w.tile < w.end; w.tile += w.step) {
-    const int64_t i0 = (int64_t)w.tile * MP_ROWS;
-    if (threadIdx.x <= MP_ROWS) rp[threadIdx.x] = d.rowptr[i0 + threadIdx.x];
-    float dy[PASSES], yj[PASSES];
+  if (threadIdx.x <= MP_ROWS) rp[threadIdx.x] = d.rowptr[i0 + threadIdx.x];
+  float dy[PASSES], yj[PASSES];
 #pragma unroll
-    for (int pass = 0; pass < PASSES; ++pass) {
-      dy[pass] = 0.0f;
-      yj[pass] = y[(i0 + pass * NODES + slot) * MP_H + k] + ck;
+  for (int pass = 0; pass < PASSES; ++pass) {
+    dy[pass] = 0.0f;
+    yj[pass] = y[(i0 + pass * NODES + slot) * MP_H + k] + ck;
+  }
+  __syncthreads();
+  const int E0 = rp[0], E1 = rp[MP_ROWS];
+  for (int cb = E0; cb < E1; cb += BB_E) {
+    // the chunk's columns and features: one gather per entry is then the
+    // only load that a row's walk waits for
+    const int ce = min(E1, cb + BB_E);
+    for (int e = cb + threadIdx.x; e < ce; e += MP_THREADS) {
+      const float* efp = m.ef + 3 * (int64_t)e;
+      sef[e - cb] = make_float4(act_in(m, efp[0]), act_in(m, efp[1]), act_in(m, efp[2]),
+                                __int_as_float(d.col[e]));
     }
     __syncthreads();
-    const int E0 = rp[0], E1 = rp[MP_ROWS];
-    for (int cb = E0; cb < E1; cb += BB_E) {
-      // the chunk's columns and features: one gather per entry is then the
-      // only load that a row's walk waits for
-      const int ce = min(E1, cb + BB_E);
-      for (int e = cb + threadIdx.x; e < ce; e += MP_THREADS) {
-        const float* efp = m.ef + 3 * (int64_t)e;
-        sef[e - cb] = make_float4(act_in(m, efp[0]), act_in(m, efp[1]), act_in(m, efp[2]),
-                                  __int_as_float(d.col[e]));
-      }
-      __syncthreads();
-#pragma unroll
-      for (int pass = 0; pass < PASSES; ++pass) {
-        const int row = pass * NODES + slot;
-        const int lo = max(rp[row], cb), hi = min(rp[row + 1], ce);
-#pragma unroll 4
-        for (int e = lo; e < hi; ++e) {
-          const float4 f = sef[e - cb];
-          const float s = ((yj[pass] + q0 * f.x) + q1 * f.y) + q2 * f.z;
-          const float dmi = m.dm[(int64_t)__float_as_int(f.w) * MP_H + k];
-          const float ds = s > 0.0f ? MP_MSG * dmi : 0.0f;
-          dy[pass] += ds;
-          accc += ds;
-          accQ[0] += ds * f.x;
-          accQ[1] += ds * f.y;
-          accQ[2] += ds * f.z;
-        }
-      }
-      __syncthreads();
-    }
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
       const int row = pass * NODES + slot;
-      sdy[row * BW_S + k] = dy[pass];
-      sh[row * BW_S + k] = act_in(m, hin[(i0 + row) * MP_H + k]);
-    }
-    __syncthreads();
-    if (wave == 0) {
-      bw_outer(sdy, sh, acc);
-    } else if (wave <= MP_ROWS / 32) {
-      const int row0 = 32 * (wave - 1);
-      const f32x16 s = bw_rows(sdy, row0, P);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t o = (i0 + row0 + bw_row(r)) * MP_H + k;
-        m.dh[o] = m.dh2[o] + s[r];  // dL/dh^l for the next part A
+      const int lo = max(rp[row], cb), hi = min(rp[row + 1], ce);
+#pragma unroll 4
+      for (int e = lo; e < hi; ++e) {
+        const float4 f = sef[e - cb];
+        const float s = ((yj[pass] + q0 * f.x) + q1 * f.y) + q2 * f.z;
+        const float dmi = m.dm[(int64_t)__float_as_int(f.w) * MP_H + k];
+        const float ds = s > 0.0f ? MP_MSG * dmi : 0.0f;
+        dy[pass] += ds;
+        accc += ds;
+        accQ[0] += ds * f.x;
+        accQ[1] += ds * f.y;
+        accQ[2] += ds * f.z;
       }
     }
     __syncthreads();
   }
-  float* dst = m.gpart + (int64_t)blockIdx.x * MP_NPARAMS_ALL + base;
+#pragma unroll
+  for (int pass = 0; pass < PASSES; ++pass) {
+    const int row = pass * NODES + slot;
+    sdy[row * BW_S + k] = dy[pass];
+    sh[row * BW_S + k] = act_in(m, hin[(i0 + row) * MP_H + k]);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    acc = bw_outer(sdy, sh);
+  } else if (wave <= MP_ROWS / 32) {
+    const int row0 = 32 * (wave - 1);
+    const f32x16 s = bw_rows(sdy, row0, P);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t o = (i0 + row0 + bw_row(r)) * MP_H + k;
+      m.dh[o] = m.dh2[o] + s[r];  // dL/dh^l for the next part A
+    }
+  }
+  __syncthreads();
+  float* dst = m.gpart + (int64_t)tile * MP_NPARAMS_ALL + base;
   if (wave == 0) bw_store_matrix(acc, dst + MP_L_P);
   slot_reduce_store(accc, red, dst + MP_L_C);
   for (int f = 0; f < MP_FE; ++f) {
@@ -1346,16 +1342,13 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_encode_bwd(DevPtrs d, MpPtrs 
   }
 }
 
-// gsum[g][p] = sum of gpart[b][p] over the blocks b = g, g + MP_GSLICES, ..
-// that hold parameter p (`layers` blocks for the layers' parameters, `tiles`
-// for the others), in order
-__global__ __launch_bounds__(256) void k_mp_grad_part(MpPtrs m, int tiles, int layers) {
+// gsum[g][p] = sum of gpart[b][p] over the tiles b = g, g + MP_GSLICES, .. in order
+__global__ __launch_bounds__(256) void k_mp_grad_part(MpPtrs m, int tiles) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= m.nparams) return;
-  const int nblk = p >= MP_OFF_L0 && p < MP_OFF_HEAD ? layers : tiles;
   double s = 0.0;
 #pragma unroll 4
-  for (int b = blockIdx.y; b < nblk; b += MP_GSLICES) s += m.gpart[(int64_t)b * MP_NPARAMS_ALL + p];
+  for (int b = blockIdx.y; b < tiles; b += MP_GSLICES) s += m.gpart[(int64_t)b * MP_NPARAMS_ALL + p];
   m.gsum[(int64_t)blockIdx.y * MP_NPARAMS_ALL + p] = s;
 }
 
@@ -1941,14 +1934,14 @@ hipError_t launch_mp_loss(const DevPtrs& d, const MpPtrs& m, hipStream_t s) {
 // parameter gradient
 static hipError_t launch_mp_trunk_backward(const DevPtrs& d, const MpPtrs& m, hipStream_t s) {
   const unsigned blocks = (unsigned)(d.rows / MP_ROWS);
-  const unsigned lb = bw_blocks(blocks);
+  const unsigned lb = (unsigned)xcd_grid((int)blocks);
   for (int l = MP_NL - 1; l >= 0; --l) {
     hipLaunchKernelGGL(k_mp_layer_bwd_a, dim3(lb), dim3(MP_THREADS), 0, s, d, m, l);
     hipLaunchKernelGGL(k_mp_layer_bwd_b, dim3(lb), dim3(MP_THREADS), 0, s, d, m, l);
   }
   hipLaunchKernelGGL(k_mp_encode_bwd, dim3(blocks), dim3(MP_THREADS), 0, s, d, m);
   hipLaunchKernelGGL(k_mp_grad_part, dim3(nb(MP_NPARAMS_ALL, 256), MP_GSLICES), dim3(256), 0, s, m,
-                     (int)blocks, (int)lb);
+                     (int)blocks);
   hipLaunchKernelGGL(k_mp_grad_reduce, dim3(nb(MP_NPARAMS_ALL, 256)), dim3(256), 0, s, m);
   return hipGetLastError();
 }
