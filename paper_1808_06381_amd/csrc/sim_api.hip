@@ -57,7 +57,8 @@ struct sim_t {
   DevPtrs d{};
   RepDev* rep_d = nullptr;
   int32_t* scan_tmp = nullptr;
-  int32_t* nbr_slots = nullptr;  // [NBR_SLOTS][rows] neighbours kept by the count pass
+  int32_t* nbr_slots = nullptr;  // [NBR_SLOTS][rows] neighbours kept by the count pass (in the
+                                 // memory of x, b, r, s, w, p)
   int32_t* bsum = nullptr;
   int64_t* id_off_d = nullptr;
   double* io = nullptr;  // n_total x 3 staging for the boundary
@@ -150,12 +151,19 @@ static void drop_graphs(sim_t* s) {
   s->graphs.clear();
 }
 
+static bool shrink_ring(sim_t* s);
+
 static int dalloc(sim_t* s, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) bytes = 8;
   if (hipMalloc(p, bytes) != hipSuccess) {
-    *p = nullptr;
-    return SIM_ENOMEM;
+    (void)hipGetLastError();  // not for the next launch to report
+    // the ring of u may be holding what this allocation needs
+    if (!shrink_ring(s) || hipMalloc(p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      *p = nullptr;
+      return SIM_ENOMEM;
+    }
   }
   s->allocs.push_back(*p);
   return SIM_OK;
@@ -167,6 +175,42 @@ static void dfree(sim_t* s, void* p) {
   if (it != s->allocs.end()) s->allocs.erase(it);
   (void)hipFree(p);
 }
+
+// The ring of u: `slots` slots if there is room, else half as many, and so on
+// down to RING_MIN.  No solve is under way.
+static int alloc_ring(sim_t* s, int32_t slots) {
+  const size_t slot_b = sizeof(double) * 3 * (size_t)s->rows;
+  void* u = nullptr;
+  for (;; slots = std::max(slots / 2, RING_MIN)) {
+    if (hipMalloc(&u, slot_b * slots) == hipSuccess) break;
+    (void)hipGetLastError();
+    if (slots == RING_MIN) return SIM_ENOMEM;
+  }
+  s->allocs.push_back(u);
+  s->d.u = (double*)u;
+  s->d.ring = slots;
+  s->ring = sim_t::CgRing();
+  // padding rows keep u = 0 (the IC(0) passes write real rows only)
+  if (s->ic0) {
+    HIPCHK(hipMemset(u, 0, slot_b * slots));
+    HIPCHK(hipDeviceSynchronize());
+  }
+  return SIM_OK;
+}
+
+// Gives the ring's memory back but for RING_MIN slots, to an allocation that
+// found no room.  False: there was nothing to give.
+static bool shrink_ring(sim_t* s) {
+  if (!s->d.u || s->d.ring <= RING_MIN) return false;
+  if (hipStreamSynchronize(s->stream) != hipSuccess) return false;
+  drop_graphs(s);
+  dfree(s, s->d.u);
+  s->d.u = nullptr;
+  return alloc_ring(s, RING_MIN) == SIM_OK;
+}
+
+// before a solve: a ring that could not be had back after it was given away
+static int need_ring(sim_t* s) { return s->d.u ? SIM_OK : alloc_ring(s, RING_MIN); }
 
 // device scratch *p of at least `need` bytes (kept between calls)
 static int grow_scratch(sim_t* s, void** p, size_t* have, size_t need) {
@@ -453,6 +497,7 @@ static int grow_and_refill(sim_t* s) {
   if (rc) return rc;
   if (need > s->d.nnz_cap) return SIM_ENOMEM;
   HIPCHK(launch_ctrl_zero(s->d, s->stream));
+  HIPCHK(launch_nbr_count(s->d, s->nbr_slots, s->stream));  // the solve took the slots' memory
   HIPCHK(launch_nbr_list(s->d, s->nbr_slots, s->stream));
   if (s->block) HIPCHK(launch_pair_block(s->d, s->bp, s->stream));
   else HIPCHK(launch_pair_terms(s->d, s->stream));
@@ -942,8 +987,10 @@ static int bcg_solve(sim_t* s, double tol, bool warm, sim_stats* st) {
 }
 
 static int cg_solve(sim_t* s, double tol, bool warm, sim_stats* st) {
+  int rc = need_ring(s);
+  if (rc) return rc;
   if (s->block) return bcg_solve(s, tol, warm, st);
-  int rc = cg_queue_start(s, tol, warm);
+  rc = cg_queue_start(s, tol, warm);
   if (rc) return rc;
   const int n = std::max(1, std::min(s->last_iters > 2 ? s->last_iters - 1 : 8, cg_maxit(s) + 1));
   if ((rc = cg_queue_chunk(s, n, 0, true))) return rc;
@@ -1176,26 +1223,20 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   ALLOC(d.cell_count, sizeof(int32_t) * d.ncell_entries);
   ALLOC(d.cell_row, sizeof(int32_t) * d.ncell_entries);
   ALLOC(s->scan_tmp, sizeof(int32_t) * d.ncell_entries);
-  ALLOC(s->nbr_slots, sizeof(int32_t) * NBR_SLOTS * rows);
   ALLOC(d.rowlen, sizeof(int32_t) * (rows + 1));
   ALLOC(d.rowptr, sizeof(int32_t) * (rows + 1));
   ALLOC(d.diag, sizeof(double) * rows);
   ALLOC(d.dinv, sizeof(double) * rows);
-  ALLOC(d.b, sizeof(double) * 3 * rows);
-  ALLOC(d.x, sizeof(double) * 3 * rows);
-  ALLOC(d.p, sizeof(double) * 3 * rows);
-  ALLOC(d.r, sizeof(double) * 3 * rows);
-  ALLOC(d.s, sizeof(double) * 3 * rows);
-  ALLOC(d.w, sizeof(double) * 3 * rows);
-  // slots of the ring of u: 64 (a whole solve of the usual length without an
-  // intermediate pass over x) while they take at most 2 GiB, else fewer, at
-  // least 16.  Step times with 16 / 32 / 64 slots: N = 1e3 (ten steps, Jacobi)
-  // 12.2 / 12.2 / 12.0 ms, N = 1e5 (two, learned) 2.52 / 2.51 / 2.47, N = 1e6
-  // 4.07 / 4.00 / 3.99; N = 8e6 29.2 with 16 and 32 (29.8 with 8, 31.0 with 4)
-  d.ring = (int32_t)std::min<int64_t>(U_RING,
-                                      std::max<int64_t>(16, ((int64_t)1 << 31) / (24 * s->rows)));
-  const size_t slots = d.ring;
-  ALLOC(d.u, sizeof(double) * 3 * rows * slots);
+  // x, b, r, s, w and p: none of them is live while a system is built, until the
+  // pair terms write b, so the neighbour slots of the count pass share their memory
+  static_assert(sizeof(int32_t) * NBR_SLOTS <= sizeof(double) * 18, "slots within six vectors");
+  ALLOC(d.x, sizeof(double) * 18 * rows);
+  s->nbr_slots = reinterpret_cast<int32_t*>(d.x);
+  d.b = d.x + 3 * rows;
+  d.r = d.x + 6 * rows;
+  d.s = d.x + 9 * rows;
+  d.w = d.x + 12 * rows;
+  d.p = d.x + 15 * rows;
   s->merge = !s->block && !s->ic0 && !fused;
   if (fused || s->merge) ALLOC(s->cg2, sizeof(CgRep) * replicas);
   if (fused) {
@@ -1262,6 +1303,16 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
     cap += s->reph[r].npad * (int64_t)std::ceil(2.0 * kmean + 16.0);
   }
   if ((rc = alloc_csr(s, cap)) != SIM_OK) { sim_destroy(s); return rc; }
+  // slots of the ring of u: 64 (a whole solve of the usual length without an
+  // intermediate pass over x) while they take at most 512 MiB, else fewer, at
+  // least 16.  Times with 3 / 8 / 16 / 24 / 64 slots in ms: ten Jacobi steps at
+  // N = 1e3 6.79 / 5.81 / 5.44 / 5.39 / 5.29, two learned at 1e5 2.02 / 1.97 / 1.81 /
+  // 1.81 / 1.79; a step at 1e6 Jacobi 5.28 / 4.74 / 4.63 / 4.59 / 4.54, learned 3.98 /
+  // 3.74 / 3.64 / 3.64 / 3.61, at 8e6 learned 29.8 / 27.5 / 27.4 / 27.4.  64 slots at
+  // 1e6 are 1.5 kB per row beside 0.8 for everything else: not worth the last 1 %.
+  const int32_t slots = (int32_t)std::min<int64_t>(
+      U_RING, std::max<int64_t>(16, ((int64_t)1 << 29) / (24 * s->rows)));
+  if ((rc = alloc_ring(s, slots)) != SIM_OK) { sim_destroy(s); return rc; }
   if (hipHostMalloc((void**)&s->ctrl_h, sizeof(Ctrl), 0) != hipSuccess ||
       hipHostMalloc((void**)&s->cg_h, sizeof(CgRep) * replicas, 0) != hipSuccess ||
       (s->block && hipHostMalloc((void**)&s->bcg_h, sizeof(BcgRep) * replicas, 0) != hipSuccess)) {
@@ -1317,8 +1368,6 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   // padding rows never receive a cell: keep their cell index a valid entry
   if ((e = hipMemset(d.cellidx, 0, sizeof(int32_t) * rows))) return fail(e, "clear cells");
   if ((e = hipMemset(d.cellidx_alt, 0, sizeof(int32_t) * rows))) return fail(e, "clear cells");
-  // padding rows keep u = 0 (the IC(0) passes write real rows only)
-  if (s->ic0 && (e = hipMemset(d.u, 0, sizeof(double) * 3 * rows * slots))) return fail(e, "clear u");
   if (s->ic0) {
     if ((e = hipMemcpy((void*)d.cell_color, ccolor_h.data(), sizeof(int32_t) * ccolor_h.size(),
                        hipMemcpyHostToDevice)))
@@ -1403,6 +1452,7 @@ int sim_autotune(sim_t* s, int32_t reps, sim_tuning* out) {
     s->mp.store_train = 0;
     HIPCHK(launch_mp_forward(d, s->mp, s->stream));
   }
+  if ((rc = need_ring(s))) return rc;
   s->system_valid = false;
   // u = M^-1 b for every component (a fresh CG start), then time the products
   d.learned = s->learned ? 1 : 0;
@@ -1739,6 +1789,7 @@ static int step_graph(sim_t* s, sim_stats* st) {
     s->mp.store_train = 0;
     s->d.learned = 1;
   }
+  if ((rc = need_ring(s))) return rc;
   const int K = graph_iters(s);
   const DevPtrs key_d = s->d;
   const MpPtrs key_m = s->mp;

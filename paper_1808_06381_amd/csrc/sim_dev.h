@@ -95,6 +95,8 @@ static_assert(sizeof(CgRep) % 8 == 0, "CgRep is an array element");
 // uses `ring` of them): x is brought up to date every ring - 1 iterations and
 // before a check.
 #define U_RING 64
+// ... and the fewest (a handle that finds no room for more)
+#define RING_MIN 3
 
 // Global control words (one per handle)
 struct Ctrl {

@@ -1,0 +1,137 @@
+"""Handles under memory pressure: the ring of preconditioned residuals takes
+what there is (down to three slots), and gives its memory back to a later
+allocation that finds none, so that a box fits wherever everything but the
+ring does.  The short ring's solves: A is at least gamma0 times the identity,
+so a solution with a residual of tol ||b|| is within tol ||b|| / gamma0 of the
+exact one, two solutions within twice that."""
+import gc
+import os
+
+import numpy as np
+import pytest
+import torch  # noqa: F401  (before any test loads the library)
+
+from paper_1808_06381_amd import inputs, precond
+from paper_1808_06381_amd import sim as S
+
+pytestmark = pytest.mark.gpu
+WEIGHTS = os.path.join(os.path.dirname(precond.__file__), "weights", "precond_n1e5.bin")
+MIB = 1 << 20
+
+
+def free_bytes():
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def most_of_the_memory():
+    """Held for all tests of the file: taking it costs seconds."""
+    held = torch.empty(max(0, free_bytes() - 8 * 1024 * MIB), dtype=torch.uint8, device="cuda")
+    yield
+    del held
+    free_bytes()
+
+
+class Fill:
+    """Holds all device memory but `left` bytes."""
+
+    def __init__(self, left):
+        self.held = []
+        for _ in range(4):
+            take = (free_bytes() - left) // (2 * MIB) * (2 * MIB)
+            if take <= 0:
+                break
+            self.held.append(torch.empty(take, dtype=torch.uint8, device="cuda"))
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *exc):
+        self.held.clear()
+        free_bytes()
+
+
+def ring_bytes(n):
+    rows = (n + 1023) // 1024 * 1024
+    return 24 * rows, min(64, max(16, (1 << 29) // (24 * rows)))
+
+
+def make(cfg, pos, pc):
+    sim = S.Sim(cfg, pos, tol=1e-9, precond="jacobi" if pc == "block" else pc)
+    if pc == "learned":
+        sim.load_precond(WEIGHTS)
+    return sim
+
+
+def rhs(n):
+    return np.random.default_rng(n).normal(size=(n, 3))
+
+
+@pytest.mark.parametrize("n,pc", [(200_000, "jacobi"), (200_000, "ic0"), (200_000, "block"),
+                                  (1_000_000, "jacobi"), (100_000, "none")])
+def test_a_box_fits_where_all_but_its_ring_does(n, pc):
+    cfg = inputs.cube_params(n, 0.2, seed=3)
+    if pc == "block":
+        cfg = dict(cfg, friction_par=2.0, friction_perp=0.5)
+    pos = inputs.uniform_positions(n, cfg["box"], 3)
+    b = rhs(n)
+    before = free_bytes()
+    with make(cfg, pos, pc) as sim:
+        used = before - free_bytes()
+        v, st = sim.solve(b)
+    slot, slots = ring_bytes(n)
+    with Fill(used - (slots - 3) * slot + 32 * MIB):
+        with make(cfg, pos, pc) as sim:
+            w, st2 = sim.solve(b)
+            sim.step(1)
+            again, _ = sim.solve(b)
+            last = sim.step(1)
+    assert max(st2["relres"]) <= 1e-9 and max(last["relres"]) <= 1e-9
+    # rounding moves the iteration that first passes by one at most
+    assert abs(max(st["iters"]) - max(st2["iters"])) <= 1
+    lim = 2 * 1e-9 * np.linalg.norm(b) / cfg["gamma0"]
+    assert np.linalg.norm(v - w) <= lim
+    assert np.all(np.isfinite(again))
+
+
+def test_the_ring_gives_way_to_the_network():
+    n = 200_000
+    cfg = inputs.cube_params(n, 0.2, seed=5)
+    pos = inputs.uniform_positions(n, cfg["box"], 5)
+    b = rhs(n)
+    with make(cfg, pos, "learned") as sim:
+        v, st = sim.solve(b)
+    slot, slots = ring_bytes(n)
+    with S.Sim(cfg, pos, tol=1e-9, precond="learned") as sim:
+        before = free_bytes()
+        with make(cfg, pos, "learned") as other:
+            other.solve(b)
+            both = before - free_bytes()          # a handle with its network
+        with S.Sim(cfg, pos, tol=1e-9, precond="learned") as other:
+            net = both - (before - free_bytes())  # the network's share
+        del other
+        with Fill(net - (slots - 3) * slot + 32 * MIB):
+            sim.load_precond(WEIGHTS)
+            w, st2 = sim.solve(b)
+            sim.graph_mode(True)
+            its = [max(sim.step(1)["iters"]) for _ in range(3)]
+    assert max(st2["relres"]) <= 1e-9 and st2["fallback"] == st["fallback"]
+    assert np.linalg.norm(v - w) <= 2 * 1e-9 * np.linalg.norm(b) / cfg["gamma0"]
+    assert all(i > 0 for i in its)
+
+
+def test_what_does_not_fit_is_refused_and_leaves_no_error_behind():
+    n = 200_000
+    cfg = inputs.cube_params(n, 0.2, seed=3)
+    pos = inputs.uniform_positions(n, cfg["box"], 3)
+    small = inputs.cube_params(500, 0.2, seed=1)
+    with S.Sim(small, inputs.uniform_positions(500, small["box"], 1)) as other:
+        other.step(1)
+        with Fill(64 * MIB):
+            with pytest.raises(S.SimError) as e:
+                S.Sim(cfg, pos)
+            assert e.value.code == -2
+            other.step(2)
