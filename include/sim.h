@@ -503,7 +503,13 @@ typedef struct sim_tuning {
   float vec_us[2];
 } sim_tuning;
 /* Time every variant `reps` times on the system at the current positions
- * (built for the purpose; the state is unchanged) and keep the fastest.
+ * (built for the purpose; the state is unchanged) and keep the fastest.  A
+ * handle of at most 131,072 rows (replicas padded to multiples of 1024) runs
+ * a CG iteration as one launch (learned: two), with its product -- learned:
+ * the M^-1 product -- in variant 0, 8 or 9; the other variants make it run
+ * separate launches, usually slower than the difference between the
+ * products.  Where another variant is the fastest product, whole iterations
+ * decide between it and the fastest of those three.
  * The choice depends on timing, so runs that must be bitwise reproducible
  * should fix it with sim_set_tuning.  out (optional) receives the choice
  * and the timings.                                                        */

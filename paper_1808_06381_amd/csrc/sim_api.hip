@@ -531,9 +531,10 @@ static DevPtrs cg_view(const sim_t* s) {
 // the fused iterations (see k_cg_fused) where the handle is small enough, has
 // their buffers, and its product is tuned to a form with their order of sums
 // (a row's products in entry order: variants of one lane or entry-parallel)
+static bool fused_variant(int32_t var) { return var == 0 || var >= CSR_VARIANT_DEFAULT; }
 static bool fused_ok(const sim_t* s) {
-  const int32_t var = s->d.learned ? s->d.apply_var : s->d.spmv_var;
-  return s->partial2nd && !s->d.ic0 && (var == 0 || var >= CSR_VARIANT_DEFAULT);
+  return s->partial2nd && !s->d.ic0 &&
+         fused_variant(s->d.learned ? s->d.apply_var : s->d.spmv_var);
 }
 
 // larger handles: a short launch forms the sums of groups of sub-tiles and the
@@ -1440,6 +1441,50 @@ int sim_set_tuning(sim_t* s, const sim_tuning* t) {
   return SIM_OK;
 }
 
+// Shortest of `reps` runs of the first 16 iterations of a solve (with its check
+// round) in the handle's present form, in us: a tolerance that none of them
+// meets keeps every component iterating.
+static int time_iterations(sim_t* s, int reps, hipEvent_t e0, hipEvent_t e1, float* us) {
+  *us = 0.0f;
+  for (int k = 0; k <= reps; ++k) {  // the first is not timed
+    int rc = cg_queue_start(s, 1e-150, false);
+    if (rc) return rc;
+    HIPCHK(hipEventRecord(e0, s->stream));
+    if ((rc = cg_queue_chunk(s, 16, 0, false))) return rc;
+    HIPCHK(hipEventRecord(e1, s->stream));
+    HIPCHK(hipEventSynchronize(e1));
+    float ms = 0.0f;
+    HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+    if (k == 1 || (k > 1 && 1000.0f * ms < *us)) *us = 1000.0f * ms;
+  }
+  return SIM_OK;
+}
+
+// On a handle that can run fused iterations: the fastest variant they take in
+// place of a faster product that they do not, unless whole iterations with that
+// product are faster.  N = 1000 with the product of 4 lanes per row, the fastest
+// alone, 1.13 ms per step against 0.53 fused.
+static int tune_fused(sim_t* s, int reps, hipEvent_t e0, hipEvent_t e1, sim_tuning* t) {
+  DevPtrs& d = s->d;
+  int32_t& pick = d.learned ? t->apply_variant : t->spmv_variant;
+  const float* each = d.learned ? t->apply_us : t->spmv_us;
+  if (!s->partial2nd || fused_variant(pick)) return SIM_OK;
+  int32_t cand = CSR_VARIANT_DEFAULT;
+  for (int v = 0; v < CSR_VARIANTS; ++v)
+    if (fused_variant(v) && each[v] < each[cand]) cand = v;
+  const int32_t alone = pick;
+  float us[2];
+  for (int form = 0; form < 2; ++form) {
+    pick = form == 0 ? alone : cand;
+    d.spmv_var = t->spmv_variant;
+    d.apply_var = t->apply_variant;
+    const int rc = time_iterations(s, reps, e0, e1, &us[form]);
+    if (rc) return rc;
+  }
+  if (us[0] < us[1]) pick = alone;
+  return SIM_OK;
+}
+
 int sim_autotune(sim_t* s, int32_t reps, sim_tuning* out) {
   if (!s || reps < 1) return SIM_EINVAL;
   if (s->block) return SIM_ENOTSUP;  // the variants tune the scalar CSR products
@@ -1500,13 +1545,16 @@ int sim_autotune(sim_t* s, int32_t reps, sim_tuning* out) {
     t.vec_us[v] = 1000.0f * ms / (float)reps;
   }
   t.vec_variant = t.vec_us[1] < t.vec_us[0] ? 1 : 0;
+  d.vec_nt = t.vec_variant;
+  if (err == hipSuccess) rc = tune_fused(s, reps, e0, e1, &t);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   d.learned = 0;
-  if (err != hipSuccess) {
+  if (err != hipSuccess || rc) {
     d.spmv_var = s->tune.spmv_variant;
     d.apply_var = s->tune.apply_variant;
     d.vec_nt = s->tune.vec_variant;
+    if (rc) return rc;
     sim_note_error(err, "autotune", __LINE__);
     return SIM_EDEVICE;
   }
