@@ -498,7 +498,9 @@ typedef struct sim_tuning {
   float apply_us[SIM_CSR_VARIANTS]; /* (0 where not measured) */
   /* CG vector kernel: 0 ordinary loads and stores, 1 nontemporal (streaming)
    * for the vectors not read again within the iteration (faster on a working
-   * set larger than the last-level cache); the same bits either way         */
+   * set larger than the last-level cache); the same bits either way.
+   * sim_autotune: vec_us is the kernel's mean duration alone, the choice is
+   * made by whole iterations (0 where an iteration is one launch)           */
   int32_t vec_variant;
   float vec_us[2];
 } sim_tuning;

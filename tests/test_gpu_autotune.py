@@ -64,6 +64,14 @@ def test_tuning_leaves_the_state_and_a_working_handle(n, pc):
         assert max(st["relres"]) <= 1e-9 and st["steps_done"] == 2 and st["fallback"] == 0
 
 
+@pytest.mark.parametrize("n", [300, 1000, 4000, 20_000, 60_000, 131_072])
+def test_the_vector_form_stays_where_no_launch_has_one(n):
+    cfg = inputs.cube_params(n, 0.1, seed=4)
+    with S.Sim(cfg, inputs.uniform_positions(n, cfg["box"], 4), tol=1e-8) as sim:
+        t = sim.autotune(reps=3)
+        assert t["spmv_variant"] not in (0, 8, 9) or t["vec_variant"] == 0
+
+
 def test_tuning_a_system_that_needs_no_iterations():
     """Every product is the diagonal's and the right-hand side is zero."""
     cfg = dict(inputs.base_params(n=64, box=(40.0, 40.0, 40.0), shear_rate=0.0, seed=1), kT=0.0)
