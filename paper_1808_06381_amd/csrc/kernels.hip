@@ -24,18 +24,23 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int32_t v, int64_t n) {
 // ---------------------------------------------------------------------------
 // exclusive scan of int32 (two passes: block sums; then each block adds the
 // sums before it and scans its own tile, with 16-byte accesses and wave scans:
-// 4.4 + 5.0 us at 1e6 rows, against 4.5 + 4.4 + 10.7 us in three passes).  One
-// launch where there is one block.
+// 4.7 + 5.2 us at 1e6 rows, against 4.5 + 4.4 + 10.7 us in three passes).  One
+// launch where there is one block.  Sums are formed in 64 bits; what passes
+// INT32_MAX is stored as INT32_MAX, so that the offsets never decrease: a reader
+// that clamps them to its capacity stays in bounds.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ int32_t scan_clamp(int64_t v) {
+  return v < (int64_t)INT32_MAX ? (int32_t)v : INT32_MAX;
+}
 #define SCAN_ITEMS 8
 #define SCAN_TILE (BLOCK_THREADS * SCAN_ITEMS)
 
 __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_reduce(const int32_t* __restrict__ in,
                                                                int64_t m,
                                                                int32_t* __restrict__ bsum) {
-  __shared__ int32_t lds[BLOCK_THREADS / 64];
+  __shared__ int64_t lds[BLOCK_THREADS / 64];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
-  int32_t s = 0;
+  int64_t s = 0;
 #pragma unroll
   for (int k = 0; k < SCAN_ITEMS; ++k) {
     const int64_t i = base + (int64_t)k * BLOCK_THREADS + threadIdx.x;
@@ -45,28 +50,26 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_reduce(const int32_t* __
   if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
-    int32_t t = 0;
+    int64_t t = 0;
     for (int w = 0; w < BLOCK_THREADS / 64; ++w) t += lds[w];
-    bsum[blockIdx.x] = t;
+    bsum[blockIdx.x] = scan_clamp(t);
   }
 }
 
-// The sums before a block are added in 64 bits: if the total passes INT32_MAX
-// the 32-bit offsets would wrap, so *too_many (optional) is raised and the
-// consumers of the offsets (the neighbour list) write nothing.
+// If the total passes INT32_MAX, *too_many (optional) is raised, and the
+// neighbour list is not filled.
 __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_down(const int32_t* __restrict__ in,
                                                              int64_t m,
                                                              const int32_t* __restrict__ bsum,
                                                              int32_t* __restrict__ out,
                                                              int32_t* __restrict__ too_many) {
   constexpr int WAVES = BLOCK_THREADS / 64;
-  __shared__ int32_t wsum[WAVES];
-  __shared__ int64_t wbase[WAVES];
+  __shared__ int64_t wsum[WAVES], wbase[WAVES];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)t * SCAN_ITEMS;
   static_assert(SCAN_ITEMS == 8, "two 16-byte loads per thread");
   int32_t v[SCAN_ITEMS];
-  int32_t tot = 0;
+  int64_t tot = 0;
   // in and out are whole allocations, so base (a multiple of 8) is aligned
   const bool whole = base + SCAN_ITEMS <= m;
   if (whole) {
@@ -82,10 +85,10 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_down(const int32_t* __re
   for (int k = 0; k < SCAN_ITEMS; ++k) tot += v[k];
   int64_t before = 0;
   for (int b = t; b < (int)blockIdx.x; b += BLOCK_THREADS) before += bsum[b];
-  int32_t inc = tot;
+  int64_t inc = tot;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int32_t up = __shfl_up(inc, o, 64);
+    const int64_t up = __shfl_up(inc, o, 64);
     inc += lane >= o ? up : 0;
     before += __shfl_xor(before, o, 64);
   }
@@ -99,11 +102,11 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_scan_down(const int32_t* __re
     run64 += wbase[w] + (w < wave ? wsum[w] : 0);
     all += wsum[w];
   }
-  int32_t run = (int32_t)run64 + inc - tot;
+  int64_t run = run64 + inc - tot;
 #pragma unroll
   for (int k = 0; k < SCAN_ITEMS; ++k) {
-    const int32_t next = run + v[k];
-    v[k] = run;
+    const int64_t next = run + v[k];
+    v[k] = scan_clamp(run);
     run = next;
   }
   if (whole) {
@@ -394,16 +397,15 @@ __global__ __launch_bounds__(NBR_THREADS) void k_nbr_list(DevPtrs d,
   if (blockIdx.x == 0 && threadIdx.x == 0 && !d.ctrl->too_many) d.ctrl->nnz = d.rowptr[d.rows];
   const int64_t i = (int64_t)tile * NBR_THREADS + threadIdx.x;
   if (i - R.row_off >= R.n) return;
-  if (d.ctrl->too_many) {  // offsets wrapped: nothing is written, the fill fails
-    atomicOr(&d.ctrl->overflow, 1);
-    return;
-  }
   const int64_t e1 = d.rowptr[i + 1];
-  if (e1 > d.nnz_cap) {
+  int64_t e = d.rowptr[i];
+  // no room: the fill fails, and the solve that is queued behind it, whose
+  // result is discarded, finds columns of this box in what there is of the row
+  if (d.ctrl->too_many || e1 > d.nnz_cap) {
     atomicOr(&d.ctrl->overflow, 1);
+    for (; e < d.nnz_cap && e < e1; ++e) d.col[e] = (int32_t)i;
     return;
   }
-  int64_t e = d.rowptr[i];
   if (e1 - e <= NBR_SLOTS) {
     for (int k = 0; e < e1; ++k, ++e) d.col[e] = slots[(int64_t)k * d.rows + i];
     return;
