@@ -164,8 +164,9 @@ def cpu_baseline(cfg, pos, step_index, tol):
 
 def measure_sq(sim, n, np, nx=64, my_max=64, reps=3):
     """Structure factor of the final state (Eq. Sfactor, 64 x 129 wavevectors,
-    mz = 0): the contraction kernel's event-timed duration, 8 flops (one
-    complex multiply-add) per particle and wavevector."""
+    mz = 0): the contraction kernel's event-timed duration, 4 flops per
+    particle and wavevector (a wavevector and its mirror share the four real
+    multiply-adds of one complex one)."""
     sim.structure_factor(nx, my_max)  # untimed first call (scratch, code load)
     ms = []
     for _ in range(reps):
@@ -173,7 +174,7 @@ def measure_sq(sim, n, np, nx=64, my_max=64, reps=3):
         ms.append(t)
     ny = 2 * my_max + 1
     return dict(grid=f"mx 0..{nx - 1} x my -{my_max}..{my_max}, mz 0", particles=n,
-                kernel_ms_events=round(float(np.mean(ms)), 4), flops_per_call=8.0 * n * nx * ny,
+                kernel_ms_events=round(float(np.mean(ms)), 4), flops_per_call=4.0 * n * nx * ny,
                 s_q0=float(s[0, 0, my_max]))
 
 
