@@ -829,10 +829,12 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
         if (s->cg_h[r].bb[k] > 0.0) itmin = std::min(itmin, s->cg_h[r].it[k]);
     const double rows = (double)s->rows, nnz = (double)s->ctrl_h->nnz;
     const double ntile = (double)(SUBS_PER_TILE * d.nblk);  // partial slots written
+    // vector kernel: the last two residuals and w read (72 B/row), the new residual
+    // written (24); where it forms u itself, u written (24) and, for Jacobi, 1/diag read (8)
+    const bool ext = learned || d.ic0;
+    const double vec_row = ext ? 96.0 : (d.pc_none ? 120.0 : 128.0);
     const double per_launch[kProfKernels] = {
-        // vector kernel: the last two residuals and w read (72 B/row), the new residual
-        // written (24); with Jacobi 1/diag read (8) and u written (24) too
-        (learned ? rows * 96.0 : rows * 128.0) + ntile * 6.0 * 8.0,
+        rows * vec_row + ntile * (ext ? 3.0 : 6.0) * 8.0,
         // product: row pointers (4), u (24), diag (8), w written (24), CSR col + value
         rows * 60.0 + 4.0 + nnz * (4.0 + (s->d.spmv_fp32 ? 4.0 : 8.0)) + ntile * 3.0 * 8.0,
         // learned apply: row pointers (4), r (24), M^-1 diagonal (8), u written (24),
