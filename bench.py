@@ -14,9 +14,11 @@ Each form is timed over whole steps replayed as HIP graphs; every
 --probe-every-th step runs eagerly with HIP events: alternately the CG
 kernels launch by launch, and a run of whole CG iterations (all kernels,
 the finisher and the gaps) between one event pair.  The roofline of the
-line is the CG iteration: its algorithmic bytes (matrix 12(k+1)+4 and
-vectors 200 per particle, plus one matrix pass for the learned M^-1
-product) over its measured time, against 8 TB/s.
+line is the CG iteration: the bytes its passes have to move (learned form:
+vector update 96, matrix product 60 + 12 k, M^-1 product 60 + 8 k per
+particle) over its measured time, against 8 TB/s; beside it the bytes of
+textbook PCG (matrix 12(k+1)+4 and vectors 200, plus 12(k+1)+4 for the M^-1
+product), which a form that keeps p and x per iteration would move.
 
 Further keys: the three N = 1e6 boxes at shear 0.01 / 0.1 / 0.5 (plain,
 learned, IC(0)) with the structure factor and the velocity correlation of
@@ -360,6 +362,15 @@ def preshear(args, S, cfg, pos, stream, name):
     return out
 
 
+def textbook_bytes(k, n, learned):
+    """Bytes of one PCG iteration that keeps x, r, p and q = A p, for n
+    particles with k off-diagonal entries each: the matrix 12(k+1)+4, the
+    vectors 200 (p read, q written and read, x and r read and written, 1/diag,
+    p written), and one more matrix pass for a learned M^-1."""
+    mat = 12.0 * (k + 1.0) + 4.0
+    return round(n * (mat + 200.0 + (mat if learned else 0.0)), 1)
+
+
 def iteration_roofline(r, copy_gbs, traffic):
     """The CG iteration measured as a whole against the HBM peak, with the
     dominant single kernel beside it."""
@@ -373,8 +384,8 @@ def iteration_roofline(r, copy_gbs, traffic):
                traffic=None if traffic is None else traffic["bytes_per_iteration"],
                kernel="cg_iteration: k_cg_vec + k_cg_apply + k_cg_spmv + k_cg_groups and the "
                       "gaps between them",
-               basis="algorithmic bytes per CG iteration: 12(k+1)+4 (matrix) + 200 (vectors) per "
-                     "particle, + 12(k+1)+4 for the learned M^-1 product",
+               basis="bytes the CG iteration's passes move per particle: vector update 96 "
+                     "(Jacobi 128), product 60+12k, learned M^-1 product 60+8k",
                k_offdiag_per_row=r["rows"]["mean_offdiag_per_row"],
                bytes_per_iteration=round(it["bytes_per_launch"], 1),
                us_per_iteration=round(it["mean_us"], 2), iterations_timed=it["launches"],
@@ -387,6 +398,9 @@ def iteration_roofline(r, copy_gbs, traffic):
                                       bytes_per_launch=round(d["bytes_per_launch"], 1),
                                       mean_us=round(d["mean_us"], 2),
                                       traffic=None if traffic is None else traffic.get(dom))
+    if r.get("particles"):
+        out["textbook_pcg_bytes"] = textbook_bytes(r["rows"]["mean_offdiag_per_row"],
+                                                   r["particles"], "k_cg_apply" in r["kernels"])
     if traffic is not None:
         out["traffic_over_algorithmic"] = round(
             traffic["bytes_per_iteration"] / traffic["algorithmic_bytes_per_iteration"], 4)

@@ -422,11 +422,11 @@ int sim_debug_precond(sim_t* sim, int64_t* rows, int64_t* cols, double* vals, in
  * ("cg_iteration"): one event pair around the first chunk's iterations
  * except its last two -- every kernel, the finisher and the gaps between
  * launches -- counted as that many launches, each priced at the solve's
- * algorithmic bytes per iteration: 12(nnz + N) + 4N (the matrix: value 8 +
- * column 4 per entry, the diagonal as one more entry, a row pointer; 8
- * instead of 12 with FP32 values) + 200N (the CG vectors) for N particles
- * and nnz off-diagonal entries, plus 12(nnz + N) + 4N for the learned
- * preconditioner's product.  Only iterations in which every component of
+ * algorithmic bytes per iteration, for N particles and nnz off-diagonal
+ * entries those of its passes: the vector update 128N (96N where a pass of its
+ * own forms u = M^-1 r; 120N without a preconditioner), the matrix product 60N
+ * + 12nnz (8nnz with FP32 values), the learned product 60N + 8nnz, the IC(0)
+ * solves 128N + 12nnz.  Only iterations in which every component of
  * every replica was still iterating are kept, so each kept record did the
  * full work of its iterations.  sample_every = 0 switches the probe off.   */
 typedef struct sim_kernel_prof {

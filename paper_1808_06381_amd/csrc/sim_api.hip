@@ -840,18 +840,18 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
         // learned apply: row pointers (4), r (24), M^-1 diagonal (8), u written (24),
         // column + FP32 value per entry
         rows * 60.0 + 4.0 + nnz * 8.0 + ntile * 3.0 * 8.0};
-    // one CG iteration's algorithmic bytes over the real particles N with
-    // nnz off-diagonal entries (k = nnz / N per row): the matrix 12(k + 1) + 4
-    // (value 8 + column 4 per entry, the diagonal as one more entry, a row
-    // pointer 4; values 4 bytes with the FP32 product) and 200 vector bytes
-    // per row (p read 24, q written and read 48, x and r read and written
-    // 96, 1/diag 8, p written 24); the learned form adds one matrix pass for
-    // its M^-1 product
+    // one CG iteration's algorithmic bytes over the real particles: those of its
+    // passes above -- the vector pass, the product (60 per row: row pointer 4, u
+    // 24, diagonal 8, w 24; column and value per entry) and the learned product
+    // (60: row pointer 4, r 24, diagonal 8, u 24; column and FP32 value) or the
+    // IC(0) solves (forward r 24, y 24, diagonal 8, row pointer and count 8;
+    // backward y and z 48, diagonal 8, pointer and count 8; 12 per entry over
+    // both).  The ring's pass over x, once per ring, is not in it.
     double npart = 0.0;
     for (const RepDev& R : s->reph) npart += (double)R.n;
-    const double vb = s->d.spmv_fp32 ? 8.0 : 12.0;
-    const double mat = vb * (nnz + npart) + 4.0 * npart;
-    const double per_iter = mat + 200.0 * npart + (learned ? 12.0 * (nnz + npart) + 4.0 * npart : 0.0);
+    double per_iter = npart * (vec_row + 60.0) + nnz * (s->d.spmv_fp32 ? 8.0 : 12.0);
+    if (learned) per_iter += npart * 60.0 + nnz * 8.0;
+    if (d.ic0) per_iter += npart * 128.0 + nnz * 12.0;
     if (s->prof_run_n > 0) {
       // iterations 0 .. m-1, which every component went through in full
       const int m = itmin == INT32_MAX ? 0 : std::min(s->prof_run_n, itmin - 1);

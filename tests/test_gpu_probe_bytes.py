@@ -37,3 +37,15 @@ def probed(pc, fp32=0):
 def test_vector_kernel(pc, row, sums):
     per, _ = probed(pc)
     assert per["k_cg_vec"] == pytest.approx(row * ROWS + sums * 8 * SLOTS, rel=1e-12)
+
+
+@pytest.mark.parametrize("pc,fp32,row,entry", [
+    ("jacobi", 0, 128 + 60, 12), ("jacobi", 1, 128 + 60, 8), ("none", 0, 120 + 60, 12),
+    ("ic0", 0, 96 + 60 + 128, 12 + 12), ("learned", 0, 96 + 60 + 60, 12 + 8)])
+def test_iteration(pc, fp32, row, entry):
+    per, nnz = probed(pc, fp32)
+    assert per["cg_iteration"] == pytest.approx(row * N + entry * nnz, rel=1e-12)
+    # the passes by themselves (over the padded rows, with their partial sums)
+    parts = sum(per.get(k, 0.0) for k in ("k_cg_vec", "k_cg_spmv", "k_cg_apply"))
+    if pc != "ic0":
+        assert per["cg_iteration"] < parts < 1.04 * per["cg_iteration"]
