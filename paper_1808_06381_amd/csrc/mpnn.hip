@@ -427,9 +427,11 @@ __global__ __launch_bounds__(MP_THREADS) void k_mp_encode_mx(DevPtrs d, MpPtrs m
 // four per row, sixteen slots per wave and product: lane l gathers 16 bytes of
 // the bf16 row of entry l % 16, which is the A operand of a 16 x 16 x 32 MFMA
 // as it stands, so the gathered rows never pass through LDS.  A second product
-// over (e_0, e_1, e_2, 1, zeros) and (Q, c) completes y_j + Q e_ij + c (the same
-// instruction on purpose: a 16 x 16 x 16 product accumulating straight onto
-// the result of a 16 x 16 x 32 one gave wrong sums), and since
+// over (e_0, e_1, e_2, 1, zeros) and (Q, c) completes y_j + Q e_ij + c.  It is
+// the same instruction, most of it zeros, on purpose: a 16 x 16 x 16 product onto
+// the accumulator of a 16 x 16 x 32 one is issued right behind it (hipcc of ROCm
+// 7.2 puts no wait between them) and reads it too early -- half of the sums come
+// out wrong on the device, and right with a wait between.  Since
 // register r of a lane holds entry 4 (l / 16) + r of one feature, the four
 // messages of a group are clamped and added in the lane: what goes to LDS is one
 // partial sum per group, a quarter of the messages.  The lane that will supply
