@@ -246,7 +246,7 @@ __global__ void k_bcg_reset(DevPtrs d, BlockPtrs bp, double tol) {
   if (r >= d.nrep) return;
   BcgRep& B = bp.bcg[r];
   B.bb = -1.0;
-  B.rz = B.alpha = B.beta = B.rr = 0.0;
+  B.rz = B.alpha = B.rr = 0.0;
   B.tol2 = tol > 0.0 ? tol * tol : d.rep[r].tol2;
   B.state = 1;
   B.it = B.restarts = B.breakdown = 0;
@@ -548,8 +548,8 @@ __global__ __launch_bounds__(SUB_THREADS) void k_bcg_flush(DevPtrs d, BlockPtrs 
   }
 }
 
-// one block per replica: the sub-tile partials [(w, u), (r, u), (r, r)] in a
-// fixed order, then
+// per replica the sub-tile partials [(w, u), (r, u), (r, r)] in a fixed order
+// (one block's work, or several blocks', the last of which goes on), then
 //   mode 0 (after w = A u):   convergence of the recursive residual (-> a
 //                             residual round), else beta and alpha of the
 //                             next vector pass
@@ -633,7 +633,6 @@ __global__ __launch_bounds__(BFIN) void k_bcg_finish(DevPtrs d, BlockPtrs bp, in
     hs[1] = beta;
     hs[2] = gamma;
     B.pend += 1;
-    B.beta = beta;
     B.theta = al * bal;
     B.alpha = al;
     B.rz = gamma;

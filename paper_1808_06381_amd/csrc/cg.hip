@@ -13,10 +13,10 @@
 // its own last two values (the three-term form of the same iterates),
 //   r_{k+1} = r_k + theta_k (r_k - r_{k-1}) - alpha_k w_k,
 //   theta_k = alpha_k beta_k / alpha_{k-1},
-// and x = sum_k alpha_k p_k is a combination of the u_k.  The last U_RING of
+// and x = sum_k alpha_k p_k is a combination of the u_k.  The last `ring` of
 // them stay where they were written (a ring of slots), and k_cg_flush adds
 // them to x (and forms the direction that later terms build on) in one pass
-// every U_RING - 1 iterations and before a true-residual check.  Per row and
+// every ring - 1 iterations and before a true-residual check.  Per row and
 // iteration the vector work moves 96 bytes (r twice, w, the new r; with
 // Jacobi 32 more for 1/diag and u) and 30 for x, against 192 and 24 with p, s
 // and x kept: at N = 8e6 k_cg_vec 266 -> 131 us (learned).
@@ -981,7 +981,7 @@ __global__ __launch_bounds__(SUB_THREADS) void k_cg_vec(DevPtrs d, int mode, CgF
 // sub-tiles is one block's work.  Of a larger one, block b sums L1_SUBS
 // sub-tiles into partial2[b], and the last block to finish (last_block) adds
 // those sums in order and advances: one launch where two were (9.3 us at
-// N = 1e6, now 6.9).  `from`: the state to advance into
+// N = 1e6, now 5.6 traced, early returns included).  `from`: the state to advance into
 // d.cg (d.cg itself, or the other copy after an odd number of fused or merged
 // iterations; the block that advances moves it).
 __global__ __launch_bounds__(FINISH_THREADS) void k_cg_finish(DevPtrs d, int mode, int slot,

@@ -738,8 +738,11 @@ hipError_t launch_cell_sort(const DevPtrs& d, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_nbr_count(const DevPtrs& d, int32_t* slots, hipStream_t s) {
-  // few particles per cell only: with 4.2 (the paper's box) a row of cells is a
-  // long walk for one lane, 126 against 97 us
+  // few particles per cell only: a row of cells is then a short walk for one lane.
+  // Narrow / wide in us at 2.0, 2.5, 3.0 and 4.2 particles per cell: N = 1.3e5 75 /
+  // 70, 85 / 81, 92 / 107, 103 / 181; 8e4 75 / 50, 76 / 71, 85 / 81, 106 / 148; 3e4
+  // 66 / 35, 74 / 47, 80 / 55, 94 / 118; 1e3 85 / 14, 85 / 14, 111 / 61, 106 / 87: the
+  // line is where the largest handles break even
   if (d.rows <= SMALL_ROWS && d.rows <= 2.5 * d.ncell_entries) {
     hipLaunchKernelGGL(k_nbr_count_wide, dim3(xcd_grid(ROWS_PER_BLOCK / NBR_WIDE_ROWS * d.nblk)),
                        dim3(NBR_THREADS), 0, s, d, slots);

@@ -5,7 +5,7 @@
 
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 // exclusive scan of int32; too_many (optional, device) is set to 1 when the
-// total passes INT32_MAX (the int32 outputs are then not valid)
+// total passes INT32_MAX (outputs past it are INT32_MAX)
 hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t m, int32_t* bsum, hipStream_t s,
                        int32_t* too_many = nullptr);
 int64_t scan_bsum_len(int64_t m);
@@ -135,14 +135,14 @@ struct BlockRep {       // per replica: W = alpha w (a_perp I + (a_par - a_perp)
 struct BcgRep {         // per-replica scalars of the block CG (3n stacked unknowns)
   double bb;            // ||b||^2 (negative until the first residual round)
   double rz;            // gamma = (r, u) of the last vector pass (or residual round)
-  double alpha, beta;
+  double alpha;
   double rr;            // ||r||^2 (recursive while iterating, true after a residual round)
   double tol2;          // tolerance^2 of this solve
   int32_t state;        // 0 iterating, 1 residual round pending, 2 done
   int32_t it;
   int32_t restarts;
   int32_t breakdown;
-  int32_t first;        // 1: the next vector pass starts the recurrences (beta = 0)
+  int32_t first;        // 1: the next vector pass starts the recurrences (beta = 0, theta = 0)
   int32_t pend;         // ring terms not yet added to x, from slot cbase
   int32_t cbase;
   int32_t pad0;

@@ -9,9 +9,12 @@
 //   rowptr   int32[rows+1]   CSR of the off-diagonal part of A, full rows
 //   col/val  int32/double    -alpha*w_ij per directed pair (valf: FP32 copy)
 //   diag     double[rows]    gamma0 + alpha*sum_j w_ij (dinv = 1/diag)
-//   b, x, p, r, s, w      double[3*rows]  right-hand sides and the CG vectors
-//   u        double[U_RING][3*rows]  the last preconditioned residuals (the
-//                            scalar solve's ring; the block solve uses one)
+//   x, b, r, s, w, p      double[3*rows] each, one allocation: solution,
+//                            right-hand sides, the last two residuals, A u, the
+//                            ring's direction; while a system is built its
+//                            memory holds the kept neighbours
+//   u        double[ring][3*rows]  the last preconditioned residuals (both
+//                            solves' ring, 3 to U_RING slots)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -69,8 +72,10 @@ __host__ __device__ __forceinline__ int cell_key(const RepDev& R, int cx, int cy
   return bz * B * ny * nx + sz * (by * B) * nx + sz * sy * (bx * B) + (wz * sy + wy) * sx + wx;
 }
 
-// Per-replica conjugate-gradient scalars (three components), written only by
-// the finishing kernel and read by the row kernels that follow it.
+// Per-replica conjugate-gradient scalars (three components), advanced by the
+// finishing kernel, or by every block of a fused or merged iteration alike (in
+// LDS; the replica's first block stores them in the other of two copies), and
+// read by the row kernels that follow.
 struct CgRep {
   double bb[3];     // ||b||^2
   double rr[3];     // ||r||^2 (recursive while iterating, true after a check)
@@ -157,9 +162,9 @@ struct DevPtrs {
   double* x;
   double* p;
   double* r;
-  double* s;                // scalar CG: the residual before r (the two alternate); block CG: A p
+  double* s;                // the residual before r (the two alternate, in the block CG too)
   double* w;
-  double* u;                // scalar CG: the ring slot in use, of `ring`
+  double* u;                // the ring slot in use, of `ring`
   double* hist;             // [replicas][U_RING][3][3] alpha, beta, gamma of the ring's terms
   double* vel_orig;         // velocities of the last step, original order
   float* er;                // r_ij / rc per CSR entry (learned preconditioner input)
@@ -477,6 +482,12 @@ __device__ __forceinline__ double load_shared(const double* p) {
 // (store_shared): that wave waits for its stores to be performed and then
 // counts the block, so the last one finds every block's.  No block waits for
 // another.  The ticket is back at 0 for the next launch.
+// This rests on gfx950, not on the language: the accesses are relaxed, and no
+// release or acquire at agent scope orders them (that would write back and
+// invalidate an XCD's whole L2 in every reduction).  Agent-scope accesses go past
+// the XCD's L2 both ways, the wait is for every earlier store of the wave to have
+// been performed there, and the loads of the last block are issued after the
+// barrier that its ticket's value precedes.
 __device__ __forceinline__ bool last_block(int32_t* ticket, int count) {
   __shared__ int last;
   if (threadIdx.x < 64) {
