@@ -1307,14 +1307,15 @@ int sim_create_batch(const sim_params* params, int32_t replicas, const double* p
   }
   if ((rc = alloc_csr(s, cap)) != SIM_OK) { sim_destroy(s); return rc; }
   // slots of the ring of u: 64 (a whole solve of the usual length without an
-  // intermediate pass over x) while they take at most 512 MiB, else fewer, at
-  // least 16.  Times with 3 / 8 / 16 / 24 / 64 slots in ms: ten Jacobi steps at
-  // N = 1e3 6.79 / 5.81 / 5.44 / 5.39 / 5.29, two learned at 1e5 2.02 / 1.97 / 1.81 /
-  // 1.81 / 1.79; a step at 1e6 Jacobi 5.28 / 4.74 / 4.63 / 4.59 / 4.54, learned 3.98 /
-  // 3.74 / 3.64 / 3.64 / 3.61, at 8e6 learned 29.8 / 27.5 / 27.4 / 27.4.  64 slots at
-  // 1e6 are 1.5 kB per row beside 0.8 for everything else: not worth the last 1 %.
+  // intermediate pass over x) while they take at most 768 MiB, else fewer, at
+  // least 16.  Times with 3 / 8 / 16 / 32 / 64 slots in ms: ten Jacobi steps at
+  // N = 1e3 6.79 / 5.81 / 5.44 / 5.36 / 5.29, two learned at 1e5 2.02 / 1.97 / 1.81 /
+  // 1.79 / 1.79; a step at 1e6 Jacobi 5.28 / 4.74 / 4.63 / 4.57 / 4.54, learned 3.98 /
+  // 3.74 / 3.64 / 3.62 / 3.61, at 8e6 learned 29.8 / 27.5 / 27.4 and 27.4 with 24.  At
+  // 1e6 64 slots would be 1.5 kB per row beside 0.8 for everything else: half of
+  // them for the last half per cent.
   const int32_t slots = (int32_t)std::min<int64_t>(
-      U_RING, std::max<int64_t>(16, ((int64_t)1 << 29) / (24 * s->rows)));
+      U_RING, std::max<int64_t>(16, ((int64_t)3 << 28) / (24 * s->rows)));
   if ((rc = alloc_ring(s, slots)) != SIM_OK) { sim_destroy(s); return rc; }
   if (hipHostMalloc((void**)&s->ctrl_h, sizeof(Ctrl), 0) != hipSuccess ||
       hipHostMalloc((void**)&s->cg_h, sizeof(CgRep) * replicas, 0) != hipSuccess ||

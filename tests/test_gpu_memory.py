@@ -56,7 +56,7 @@ class Fill:
 
 def ring_bytes(n):
     rows = (n + 1023) // 1024 * 1024
-    return 24 * rows, min(64, max(16, (1 << 29) // (24 * rows)))
+    return 24 * rows, min(64, max(16, (3 << 28) // (24 * rows)))
 
 
 def make(cfg, pos, pc):
