@@ -16,7 +16,7 @@ kernels launch by launch, and a run of whole CG iterations (all kernels,
 the finisher and the gaps) between one event pair.  The roofline of the
 line is the CG iteration: the bytes its passes have to move (learned form:
 vector update 96, matrix product 60 + 12 k, M^-1 product 60 + 8 k per
-particle) over its measured time, against 8 TB/s; beside it the bytes of
+particle, and the pass over x where the run fills the ring of u) over its measured time, against 8 TB/s; beside it the bytes of
 textbook PCG (matrix 12(k+1)+4 and vectors 200, plus 12(k+1)+4 for the M^-1
 product), which a form that keeps p and x per iteration would move.
 
@@ -385,7 +385,8 @@ def iteration_roofline(r, copy_gbs, traffic):
                kernel="cg_iteration: k_cg_vec + k_cg_apply + k_cg_spmv + k_cg_groups and the "
                       "gaps between them",
                basis="bytes the CG iteration's passes move per particle: vector update 96 "
-                     "(Jacobi 128), product 60+12k, learned M^-1 product 60+8k",
+                     "(Jacobi 128), product 60+12k, learned M^-1 product 60+8k; and the ring's "
+                     "pass over x in runs that fill it",
                k_offdiag_per_row=r["rows"]["mean_offdiag_per_row"],
                bytes_per_iteration=round(it["bytes_per_launch"], 1),
                us_per_iteration=round(it["mean_us"], 2), iterations_timed=it["launches"],

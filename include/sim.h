@@ -426,7 +426,8 @@ int sim_debug_precond(sim_t* sim, int64_t* rows, int64_t* cols, double* vals, in
  * entries those of its passes: the vector update 128N (96N where a pass of its
  * own forms u = M^-1 r; 120N without a preconditioner), the matrix product 60N
  * + 12nnz (8nnz with FP32 values), the learned product 60N + 8nnz, the IC(0)
- * solves 128N + 12nnz.  Only iterations in which every component of
+ * solves 128N + 12nnz; and the pass over x (24N per u that it adds, 72N, after
+ * the first 96N) where the iterations fill the ring of u.  Only iterations in which every component of
  * every replica was still iterating are kept, so each kept record did the
  * full work of its iterations.  sample_every = 0 switches the probe off.   */
 typedef struct sim_kernel_prof {

@@ -846,7 +846,7 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
     // (60: row pointer 4, r 24, diagonal 8, u 24; column and FP32 value) or the
     // IC(0) solves (forward r 24, y 24, diagonal 8, row pointer and count 8;
     // backward y and z 48, diagonal 8, pointer and count 8; 12 per entry over
-    // both).  The ring's pass over x, once per ring, is not in it.
+    // both)
     double npart = 0.0;
     for (const RepDev& R : s->reph) npart += (double)R.n;
     double per_iter = npart * (vec_row + 60.0) + nnz * (s->d.spmv_fp32 ? 8.0 : 12.0);
@@ -861,7 +861,11 @@ static int cg_poll_loop(sim_t* s, int launched, sim_stats* st, bool* first_final
         sim_kernel_prof& acc = s->prof_acc[kProfIteration];
         acc.launches += m;
         acc.ms += ms;
-        acc.bytes += per_iter * m;
+        // the passes over x of a full ring among them: its ring - 1 terms, x read
+        // and written, the direction written and, after the first pass, read (the
+        // pass before the check round is not among them)
+        const double terms = d.ring - 1, full = std::floor((m - 1) / terms);
+        acc.bytes += per_iter * m + npart * (full * (24.0 * terms + 72.0) + 24.0 * std::max(full - 1.0, 0.0));
       }
       s->prof_run_n = 0;
     }
